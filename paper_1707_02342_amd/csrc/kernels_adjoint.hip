@@ -9,48 +9,166 @@
 // unit j = 16 r + c, two samples per wavefront, eight per block.
 //
 // Memory: the forward pass stored the full state every `ckpt_every` steps.  The
-// sweep walks the segments backwards; for each it re-runs the segment forward from
-// its checkpoint (network, kinematics and cost gradient, keeping each step's hidden
-// activations in registers and the per-step scalars in LDS) and then applies the
-// reverse-mode recurrences step by step:
-//   p <- p + w_k grad c(x_{t+1});  a3 = dt p[3:7];  dW3 += a3 h2^T;  a2 = (W3^T a3)(1-h2^2);
-//   dW2 += a2 h1^T;  a1 = (W2^T a2)(1-h1^2);  dW1 += a1 in^T;  g_in = W1^T a1;
-//   dJ/du_t += g'(v_t) g_in[4:6];  p <- (dF/dx_t)^T p.
+// sweep walks the segments backwards.  As in the forward pass only the dynamic states
+// x_d (the network never reads the pose) and their cotangents p_d form serial chains, so
+// each segment is taken in three phases:
+//   1. chain: the x_d recurrence from the checkpoint, 32 lanes per sample, keeping the
+//      states and both layers' activations in LDS;
+//   2. pose, lane-parallel over the segment's steps (at most 16, one 16-lane row, the two
+//      rows of a sample alike): heading and position by scans, the gradient of the cost at
+//      the post-step states, and -- since the cotangents of the pose depend on the network
+//      through nothing but these -- their suffix sums p_x, p_y, p_theta, which reduces the
+//      pose's part in the sweep to one known term per step ("drive"),
+//        D_t = (0, dt (p_x cos + p_y sin), dt (p_y cos - p_x sin), dt p_theta);
+//   3. reverse chain, one component of p_d per lane of each quad:
+//        a2 = (W3^T dt p_d)(1 - h2^2);  a1 = (W2^T a2)(1 - h1^2);  g_in = W1^T a1;
+//        dJ/du_t = g'(v_t) g_in[4:6];  p_d <- p_d + D_t + g_in[0:4] + dc/dx_d(x_t),
+//      with dW3 += dt p_d h2^T, dW1 += a1 in^T on the vector ALU and dW2 += a2 h1^T, the two
+//      samples of the wave together, as one v_mfma_f32_32x32x2_f32 per step: lane
+//      32 half + j holds element j of sample `half`, which is the product's operand layout
+//      as it stands (64 cycles against ~150 for the 32 DPP products it replaces).
 // The control-cost term gamma eps_t / Sigma weighted by w_k sums to gamma Delta_t / Sigma
-// and is added by the final reduction.  Layer 2's two products (dW2 and W2^T a2) read
-// the other lanes' a2 through row_ror DPP operands, as the forward pass does.
+// and is added by the final reduction.
+//
+// What bounds it: the vector ALU and the latency of the two chains, ~160 instructions per
+// step and wave.  Evaluating pose, cost gradient and their cotangents in all 32 lanes of
+// every step, unrolled over 16 steps with the activations in registers (266 registers, one
+// wave per SIMD, 86 KB of code), took 320-330 us at K = 4096, T = 100, C = 10; this
+// form (188 registers, 11 KB) 102-104 us, 32 TFLOP/s of the 8064 flop per sample-step.
 #include "wave_common.hip.h"
 
 namespace mppi {
 
-constexpr int kAdjMaxSeg = 16;
-constexpr int kSegStride = 20;   // per-step scalars: x(7) v(2) vc(2) cos sin gc(7)
+constexpr int kAdjMaxSeg = 16;   // steps of a segment (one 16-lane row)
 constexpr int kNP32 = 1412;      // parameters of the 6-32-32-4 network
 
-// Sum of v over the sample's 32 lanes, the same bits in every lane.
-__device__ __forceinline__ float allsum32(float v) {
-  v = v + dpp_f<kRowRor + 8>(v);
-  v = v + dpp_f<kRowRor + 4>(v);
-  v = v + dpp_f<kRowRor + 2>(v);
-  v = v + dpp_f<kRowRor + 1>(v);
-  return add_rows(v);
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+
+namespace {
+
+constexpr int kRowMirror = 0x140;   // lane i of a row reads lane 15 - i
+
+// Inclusive / exclusive sums over the 16 lanes of a row, and the sum over the lane itself
+// and all later lanes of its row (suffix), in DPP moves.
+__device__ __forceinline__ float row_incl(float v) {
+  v = v + dpp_upd<kRowShr + 1>(0.0f, v);
+  v = v + dpp_upd<kRowShr + 2>(0.0f, v);
+  v = v + dpp_upd<kRowShr + 4>(0.0f, v);
+  v = v + dpp_upd<kRowShr + 8>(0.0f, v);
+  return v;
+}
+__device__ __forceinline__ float row_excl(float v) { return row_incl(dpp_upd<kRowShr + 1>(0.0f, v)); }
+__device__ __forceinline__ float row_suffix(float v) { return dpp_f<kRowMirror>(row_incl(dpp_f<kRowMirror>(v))); }
+__device__ __forceinline__ float row_suffix_excl(float v) { return dpp_f<kRowMirror>(row_excl(dpp_f<kRowMirror>(v))); }
+
+// The value v holds in the first lane of the caller's 32-lane half.
+__device__ __forceinline__ float first_of_half(float v) {
+  const float lo = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 0));
+  const float hi = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 32));
+  return (threadIdx.x & 32) ? hi : lo;
 }
 
+// LDS that only one wave writes and reads: the order of its accesses for the compiler.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One row's part of a 32 x 32 product: P += sum_s wP[s] h[ror s], Q likewise (the row's
+// 16 values of h through row_ror), then the sums of the sample's two rows: lane (r, c)
+// returns output 16 r + c.  Four interleaved accumulators.
+__device__ __forceinline__ float mul32(float P, float Q, float h, const float (&wP)[16], const float (&wQ)[16]) {
+  P = __builtin_fmaf(wP[0], h, P);
+  Q = __builtin_fmaf(wQ[0], h, Q);
+  float P2 = wP[1] * dpp_f<kRowRor + 1>(h);
+  float Q2 = wQ[1] * dpp_f<kRowRor + 1>(h);
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_fmac_f32_dpp %0, %4, %5 row_ror:2 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %6 row_ror:2 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %7 row_ror:3 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %8 row_ror:3 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %9 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %10 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %11 row_ror:5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %12 row_ror:5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %13 row_ror:6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %14 row_ror:6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %15 row_ror:7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %16 row_ror:7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %17 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %18 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %19 row_ror:9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %20 row_ror:9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %21 row_ror:10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %22 row_ror:10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %23 row_ror:11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %24 row_ror:11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %25 row_ror:12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %26 row_ror:12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %27 row_ror:13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %28 row_ror:13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %29 row_ror:14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %30 row_ror:14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %31 row_ror:15 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %32 row_ror:15 row_mask:0xf bank_mask:0xf"
+      : "+v"(P), "+v"(Q), "+v"(P2), "+v"(Q2)
+      : "v"(h), "v"(wP[2]), "v"(wQ[2]), "v"(wP[3]), "v"(wQ[3]), "v"(wP[4]), "v"(wQ[4]), "v"(wP[5]), "v"(wQ[5]),
+        "v"(wP[6]), "v"(wQ[6]), "v"(wP[7]), "v"(wQ[7]), "v"(wP[8]), "v"(wQ[8]), "v"(wP[9]), "v"(wQ[9]),
+        "v"(wP[10]), "v"(wQ[10]), "v"(wP[11]), "v"(wQ[11]), "v"(wP[12]), "v"(wQ[12]), "v"(wP[13]), "v"(wQ[13]),
+        "v"(wP[14]), "v"(wQ[14]), "v"(wP[15]), "v"(wQ[15]));
+  P = P + P2;
+  Q = Q + Q2;
+  swap_rows(P, Q);
+  return P + Q;
+}
+
+// acc + sum_o x_o w[o], x_o the value of x in lane o of each quad.
+__device__ __forceinline__ float quad_dot(float acc, float x, float w0, float w1, float w2, float w3) {
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_fmac_f32_dpp %0, %1, %2 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %1, %3 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %1, %4 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %1, %5 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf"
+      : "+v"(acc) : "v"(x), "v"(w0), "v"(w1), "v"(w2), "v"(w3));
+  return acc;
+}
+
+// g[o] += x_o y, x_o the value of x in lane o of each quad.
+__device__ __forceinline__ void quad_axpy(float (&g)[4], float x, float y) {
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_fmac_f32_dpp %0, %4, %5 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %5 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %5 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %5 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf"
+      : "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]) : "v"(x), "v"(y));
+}
+
+}  // namespace
+
+// LDS: per sample the clamped controls (each step's entry later holds its dJ/du), then a
+// region for the segment's states, drives and activations that the block's reduction of
+// the parameter gradients reuses.
 size_t adjoint_smem_bytes(int T, int ckpt_every) {
-  return sizeof(float) * (2 * (size_t)T + kWaveSlots * (size_t)ckpt_every * kSegStride +
-                          kWaveSlots * 2 * (size_t)kAdjMaxSeg + kWaveSlots * 2 * (size_t)T + 4 * kNP32 + 16);
+  const size_t C = (size_t)ckpt_every;
+  const size_t seg = 2 * kWaveSlots * (C + 1) * 4 + 4 * C * 128;
+  const size_t red = 4 * (size_t)kNP32;
+  return sizeof(float) * (kWaveSlots * (size_t)((2 * T + 3) & ~3) + (seg > red ? seg : red));
 }
 
-__global__ __launch_bounds__(kWaveBlock) void adjoint_wave_kernel(AdjointArgs a) {
+__global__ __launch_bounds__(kWaveBlock, 2) void adjoint_wave_kernel(AdjointArgs a) {
   constexpr int HID = 32;
-  extern __shared__ float smem[];
+  extern __shared__ __attribute__((aligned(16))) float smem[];
   const int T = a.T, C = a.ckpt_every;
-  float* sU = smem;                                    // [2T]
-  float* sSeg = sU + 2 * T;                            // [8][C][20]
-  float* sEps = sSeg + kWaveSlots * C * kSegStride;    // [8][kAdjMaxSeg][2]
-  float* sGU = sEps + kWaveSlots * 2 * kAdjMaxSeg;     // [8][T][2]
-  float* sRed = sGU + kWaveSlots * 2 * T;              // [4][1412]
-  float* scratch = sRed + 4 * kNP32;                   // [16]
+  const int eStride = (2 * T + 3) & ~3;
+  float* sV = smem;                                    // [8][2T] clamped controls, then dJ/du
+  float* sX = sV + kWaveSlots * eStride;               // [8][C + 1][4] states x_d of the segment
+  float* sD = sX + kWaveSlots * (C + 1) * 4;           // [8][C + 1][4] drives (row n: see below)
+  float* sH = sD + kWaveSlots * (C + 1) * 4;           // [4 waves][C][2][64] activations h1, h2
+  float* sRed = sX;                                    // [4][1412], after every segment
 
   const int lane = threadIdx.x & 63;
   const int wv = threadIdx.x >> 6;
@@ -58,15 +176,14 @@ __global__ __launch_bounds__(kWaveBlock) void adjoint_wave_kernel(AdjointArgs a)
   const int c32 = lane & 31;
   const int r = c32 >> 4;
   const int col = lane & 15;
+  const int comp = lane & 3;
   const int slot = wv * 2 + half;
   const int k = blockIdx.x * kWaveSlots + slot;
   const bool valid = k < a.K;
-  float* mySeg = sSeg + slot * C * kSegStride;
-  float* myEps = sEps + slot * 2 * kAdjMaxSeg;
-  float* myGU = sGU + slot * 2 * T;
-
-  for (int i = threadIdx.x; i < 2 * T; i += kWaveBlock) sU[i] = a.U[i];
-  for (int i = c32; i < 2 * T; i += 32) myGU[i] = 0.0f;
+  float* myV = sV + slot * eStride;
+  float* myX = sX + slot * (C + 1) * 4;
+  float* myD = sD + slot * (C + 1) * 4;
+  float* myH = sH + wv * C * 128 + lane;
 
   // ---- network constants of this lane ----------------------------------------------
   const float* W1 = a.params;
@@ -76,10 +193,6 @@ __global__ __launch_bounds__(kWaveBlock) void adjoint_wave_kernel(AdjointArgs a)
   const float* W3 = b2 + HID;
   const float* b3 = W3 + 4 * HID;
   const int j = 16 * r + col;
-  float w1[6];
-#pragma unroll
-  for (int i = 0; i < 6; ++i) w1[i] = W1[j * 6 + i];
-  const float bb1 = b1[j];
   int src[16];
   src[0] = col;
   src[1] = ror_src<1>(col);   src[2] = ror_src<2>(col);   src[3] = ror_src<3>(col);
@@ -87,264 +200,199 @@ __global__ __launch_bounds__(kWaveBlock) void adjoint_wave_kernel(AdjointArgs a)
   src[7] = ror_src<7>(col);   src[8] = ror_src<8>(col);   src[9] = ror_src<9>(col);
   src[10] = ror_src<10>(col); src[11] = ror_src<11>(col); src[12] = ror_src<12>(col);
   src[13] = ror_src<13>(col); src[14] = ror_src<14>(col); src[15] = ror_src<15>(col);
-  float wP[16], wQ[16], wBo[16], wBx[16];
+  // forward: layers 1 and 2 form tanh's argument already multiplied by 2 log2(e), layer 3
+  // is a reduce-scatter over each quad times dt (see the wave kernel)
+  float w1[6];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) w1[i] = kTanhScale * W1[j * 6 + i];
+  const float bb1 = kTanhScale * b1[j];
+  float wP[16], wQ[16], tP[16], tQ[16];   // rows of W2 (forward) and columns of it (reverse)
 #pragma unroll
   for (int s = 0; s < 16; ++s) {
-    wP[s] = W2[col * HID + 16 * r + src[s]];
-    wQ[s] = W2[(16 + col) * HID + 16 * r + src[s]];
-    wBo[s] = W2[(16 * r + src[s]) * HID + j];          // W2[i][j], i in this row
-    wBx[s] = W2[(16 * (1 - r) + src[s]) * HID + j];    // W2[i][j], i in the other row
+    wP[s] = kTanhScale * W2[col * HID + 16 * r + src[s]];
+    wQ[s] = kTanhScale * W2[(16 + col) * HID + 16 * r + src[s]];
+    tP[s] = W2[(16 * r + src[s]) * HID + col];
+    tQ[s] = W2[(16 * r + src[s]) * HID + 16 + col];
   }
-  const float bP = (r == 0) ? b2[col] : 0.0f;
-  const float bQ = (r == 1) ? b2[16 + col] : 0.0f;
-  float w3[4], bb3[4];
-#pragma unroll
-  for (int o = 0; o < 4; ++o) {
-    w3[o] = W3[o * HID + j];
-    bb3[o] = b3[o];
-  }
+  const float bP = (r == 0) ? kTanhScale * b2[col] : 0.0f;
+  const float bQ = (r == 1) ? kTanhScale * b2[16 + col] : 0.0f;
+  const float wKA = a.dt * W3[comp * HID + j];
+  const float wKB = a.dt * W3[(comp ^ 2) * HID + j];
+  const float wSA = a.dt * W3[(comp ^ 1) * HID + j];
+  const float wSB = a.dt * W3[(comp ^ 3) * HID + j];
+  const float bKA = (c32 < 4) ? a.dt * b3[comp] : 0.0f;
+  // reverse: dt W3^T by output, W1^T as reduce-scatters (the state inputs over each quad, the
+  // two controls over lane pairs)
+  const float w30 = a.dt * W3[0 * HID + j], w31 = a.dt * W3[1 * HID + j];
+  const float w32 = a.dt * W3[2 * HID + j], w33 = a.dt * W3[3 * HID + j];
+  const float iKA = W1[j * 6 + comp], iKB = W1[j * 6 + (comp ^ 2)];
+  const float iSA = W1[j * 6 + (comp ^ 1)], iSB = W1[j * 6 + (comp ^ 3)];
+  const float uK = W1[j * 6 + 4 + (lane & 1)], uS = W1[j * 6 + 4 + ((lane & 1) ^ 1)];
 
   // ---- weight of this sample ---------------------------------------------------------
   const float rho = a.stats[0], eta = a.stats[1];
   const float Sk = valid ? a.S[k] : kInf;
   const float wk = (Sk < kInf && rho < kInf && eta > 0.0f) ? expf(-(Sk - rho) * a.inv_lambda) / eta : 0.0f;
+  // a sample with zero weight contributes nothing; it re-runs from the zero state so
+  // that no non-finite value of its own trajectory can reach the sums
+  const bool live = wk > 0.0f;
+
+  // ---- the controls of every step ----------------------------------------------------
+  for (int t = c32; t < T; t += 32) {
+    float e0, e1;
+    draw_eps((uint32_t)t, (uint32_t)k, a.nk, e0, e1);
+    myV[2 * t] = fminf(fmaxf(a.U[2 * t] + e0, a.u_lo0), a.u_hi0);
+    myV[2 * t + 1] = fminf(fmaxf(a.U[2 * t + 1] + e1, a.u_lo1), a.u_hi1);
+  }
+  const float lo_i = (lane & 1) ? a.u_lo1 : a.u_lo0, hi_i = (lane & 1) ? a.u_hi1 : a.u_hi0;
 
   // ---- accumulators -----------------------------------------------------------------
-  float gW1[6] = {0, 0, 0, 0, 0, 0}, gb1 = 0.0f, gb2 = 0.0f;
-  float gW2o[16], gW2x[16];
-#pragma unroll
-  for (int s = 0; s < 16; ++s) {
-    gW2o[s] = 0.0f;
-    gW2x[s] = 0.0f;
-  }
-  float gW3[4] = {0, 0, 0, 0}, gb3[4] = {0, 0, 0, 0};
-  float pa[kStateDim] = {0, 0, 0, 0, 0, 0, 0};
-  __syncthreads();
+  float gX[4] = {0, 0, 0, 0}, gV0 = 0.0f, gV1 = 0.0f, gb1 = 0.0f, gb2 = 0.0f;   // dW1 by input, db1, db2
+  float gW3[4] = {0, 0, 0, 0}, gb3 = 0.0f;                                      // over dt
+  f32x16 gW2 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  float pd = 0.0f;                            // cotangent of x_d, component comp
+  float pc0 = 0.0f, pc1 = 0.0f, pc2 = 0.0f;   // cotangents of p_x, p_y, theta
 
   const int nseg = (T + C - 1) / C;
   const int n_ckpt = a.n_ckpt;
+  // the checkpoint a segment starts from, loaded one segment ahead
+  const float* cp = a.ckpt + (size_t)(valid ? k : 0) * n_ckpt * kCkptStride;
+  float c_px, c_py, c_th, c_xd;
+  auto load_ckpt = [&](int sgi) {
+    const float* q = cp + (size_t)sgi * kCkptStride;
+    c_px = q[0];
+    c_py = q[1];
+    c_th = q[2];
+    c_xd = q[3 + comp];
+  };
+  load_ckpt(nseg - 1);
   for (int sgi = nseg - 1; sgi >= 0; --sgi) {
     const int t0 = sgi * C;
     const int n = min(C, T - t0);
-    // noise of the segment, one step per lane
-    if (c32 < n) {
-      float e0, e1;
-      draw_eps((uint32_t)(t0 + c32), (uint32_t)k, a.nk, e0, e1);
-      myEps[2 * c32] = e0;
-      myEps[2 * c32 + 1] = e1;
+    const float px0 = live ? c_px : 0.0f, py0 = live ? c_py : 0.0f, th0 = live ? c_th : 0.0f;
+    float xh = live ? c_xd : 0.0f;
+    if (sgi > 0) load_ckpt(sgi - 1);
+    // ---- 1. the chain of the segment from its checkpoint ----
+    myX[comp] = xh;   // every lane of a component holds and stores the same bits
+    wave_lds_fence();
+    float2 vc = *reinterpret_cast<const float2*>(myV + 2 * t0);
+    for (int q = 0; q < n; ++q) {
+      const float2 vn = *reinterpret_cast<const float2*>(myV + 2 * min(t0 + q + 1, T - 1));
+      float acc = __builtin_fmaf(w1[4], vc.x, bb1);
+      acc = __builtin_fmaf(w1[5], vc.y, acc);
+      const float h1 = tanh_prescaled(quad_dot(acc, xh, w1[0], w1[1], w1[2], w1[3]));
+      const float h2 = tanh_prescaled(mul32(bP, bQ, h1, wP, wQ));
+      const float A = __builtin_fmaf(wKA, h2, bKA) + dpp_f<kQuadXor1>(wSA * h2);
+      const float B = wKB * h2 + dpp_f<kQuadXor1>(wSB * h2);
+      float g = A + dpp_f<kQuadXor2>(B);
+      g = g + dpp_f<kRowRor + 8>(g);
+      g = g + dpp_f<kRowRor + 4>(g);
+      xh = xh + add_rows(g);
+      myH[q * 128] = h1;
+      myH[q * 128 + 64] = h2;
+      myX[4 * (q + 1) + comp] = xh;
+      vc = vn;
     }
-    __syncthreads();
-    // ---- forward re-run of the segment from its checkpoint ----
-    float x[kStateDim];
-    const float* cp = a.ckpt + ((size_t)(valid ? k : 0) * n_ckpt + sgi) * kCkptStride;
-    // a sample with zero weight contributes nothing; it re-runs from the zero state so
-    // that no non-finite value of its own trajectory can reach the sums
-    const bool live = wk > 0.0f;
-#pragma unroll
-    for (int i = 0; i < kStateDim; ++i) x[i] = live ? cp[i] : 0.0f;
-    float h1s[kAdjMaxSeg], h2s[kAdjMaxSeg];
-#pragma unroll
-    for (int q = 0; q < kAdjMaxSeg; ++q) {
-      h1s[q] = 0.0f;
-      h2s[q] = 0.0f;
-      if (q < n) {
-        const int t = t0 + q;
-        const float u0 = sU[2 * t], u1 = sU[2 * t + 1];
-        const float v0 = u0 + myEps[2 * q], v1 = u1 + myEps[2 * q + 1];
-        const float vc0 = fminf(fmaxf(v0, a.u_lo0), a.u_hi0);
-        const float vc1 = fminf(fmaxf(v1, a.u_lo1), a.u_hi1);
-        float acc = bb1;
-        acc = __builtin_fmaf(w1[0], x[3], acc);
-        acc = __builtin_fmaf(w1[1], x[4], acc);
-        acc = __builtin_fmaf(w1[2], x[5], acc);
-        acc = __builtin_fmaf(w1[3], x[6], acc);
-        acc = __builtin_fmaf(w1[4], vc0, acc);
-        acc = __builtin_fmaf(w1[5], vc1, acc);
-        const float h1 = tanh_f(acc);
-        float P = __builtin_fmaf(wP[0], h1, bP);
-        float Q = __builtin_fmaf(wQ[0], h1, bQ);
-        float P2 = wP[1] * dpp_f<kRowRor + 1>(h1);
-        float Q2 = wQ[1] * dpp_f<kRowRor + 1>(h1);
-        FMAC_DPP_FIRST(P, h1, wP[2], "row_ror:2");
-        FMAC_DPP(Q, h1, wQ[2], "row_ror:2");
-        FMAC_DPP(P2, h1, wP[3], "row_ror:3");
-        FMAC_DPP(Q2, h1, wQ[3], "row_ror:3");
-        FMAC_DPP(P, h1, wP[4], "row_ror:4");
-        FMAC_DPP(Q, h1, wQ[4], "row_ror:4");
-        FMAC_DPP(P2, h1, wP[5], "row_ror:5");
-        FMAC_DPP(Q2, h1, wQ[5], "row_ror:5");
-        FMAC_DPP(P, h1, wP[6], "row_ror:6");
-        FMAC_DPP(Q, h1, wQ[6], "row_ror:6");
-        FMAC_DPP(P2, h1, wP[7], "row_ror:7");
-        FMAC_DPP(Q2, h1, wQ[7], "row_ror:7");
-        FMAC_DPP(P, h1, wP[8], "row_ror:8");
-        FMAC_DPP(Q, h1, wQ[8], "row_ror:8");
-        FMAC_DPP(P2, h1, wP[9], "row_ror:9");
-        FMAC_DPP(Q2, h1, wQ[9], "row_ror:9");
-        FMAC_DPP(P, h1, wP[10], "row_ror:10");
-        FMAC_DPP(Q, h1, wQ[10], "row_ror:10");
-        FMAC_DPP(P2, h1, wP[11], "row_ror:11");
-        FMAC_DPP(Q2, h1, wQ[11], "row_ror:11");
-        FMAC_DPP(P, h1, wP[12], "row_ror:12");
-        FMAC_DPP(Q, h1, wQ[12], "row_ror:12");
-        FMAC_DPP(P2, h1, wP[13], "row_ror:13");
-        FMAC_DPP(Q2, h1, wQ[13], "row_ror:13");
-        FMAC_DPP(P, h1, wP[14], "row_ror:14");
-        FMAC_DPP(Q, h1, wQ[14], "row_ror:14");
-        FMAC_DPP(P2, h1, wP[15], "row_ror:15");
-        FMAC_DPP(Q2, h1, wQ[15], "row_ror:15");
-        P = P + P2;
-        Q = Q + Q2;
-        swap_rows(P, Q);
-        const float h2 = tanh_f(P + Q);
-        float f[4];
-#pragma unroll
-        for (int o = 0; o < 4; ++o) f[o] = allsum32(w3[o] * h2) + bb3[o];
-        float sth, cth;
-        sincosf(x[2], &sth, &cth);
-        float xn[kStateDim];
-        xn[0] = x[0] + a.dt * (cth * x[4] - sth * x[5]);
-        xn[1] = x[1] + a.dt * (sth * x[4] + cth * x[5]);
-        xn[2] = x[2] + a.dt * x[6];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) xn[3 + i] = x[3 + i] + a.dt * f[i];
-        float gpx, gpy, gvx, gvy;
-        state_cost_grad(a.cost, a.map, xn[0], xn[1], xn[4], xn[5], gpx, gpy, gvx, gvy);
-        if (c32 == 0) {
-          float* row = mySeg + q * kSegStride;
-#pragma unroll
-          for (int i = 0; i < kStateDim; ++i) row[i] = x[i];
-          row[7] = v0;
-          row[8] = v1;
-          row[9] = vc0;
-          row[10] = vc1;
-          row[11] = cth;
-          row[12] = sth;
-          row[13] = wk * gpx;
-          row[14] = wk * gpy;
-          row[15] = 0.0f;
-          row[16] = 0.0f;
-          row[17] = wk * gvx;
-          row[18] = wk * gvy;
-          row[19] = 0.0f;
-        }
-        h1s[q] = h1;
-        h2s[q] = h2;
-#pragma unroll
-        for (int i = 0; i < kStateDim; ++i) x[i] = xn[i];
+    wave_lds_fence();
+    // ---- 2. pose, cost gradient and drives: lane `col` takes step t0 + col ----
+    {
+      const bool lq = col < n;
+      const int qc = min(col, n - 1);
+      const float4 xs = *reinterpret_cast<const float4*>(myX + 4 * qc);
+      const float4 xn = *reinterpret_cast<const float4*>(myX + 4 * qc + 4);
+      const float th = th0 + row_excl(lq ? a.dt * xs.w : 0.0f);
+      float sth, cth;
+      sincosf(th, &sth, &cth);
+      const float px = px0 + row_incl(lq ? a.dt * (cth * xs.y - sth * xs.z) : 0.0f);
+      const float py = py0 + row_incl(lq ? a.dt * (sth * xs.y + cth * xs.z) : 0.0f);
+      float gpx, gpy, gvx, gvy;
+      state_cost_grad(a.cost, a.map, px, py, xn.y, xn.z, gpx, gpy, gvx, gvy);
+      const bool lw = lq && live;
+      gvx = lw ? wk * gvx : 0.0f;
+      gvy = lw ? wk * gvy : 0.0f;
+      const float p0 = pc0 + row_suffix(lw ? wk * gpx : 0.0f);
+      const float p1 = pc1 + row_suffix(lw ? wk * gpy : 0.0f);
+      const float e = lq ? a.dt * (p0 * (-sth * xs.y - cth * xs.z) + p1 * (cth * xs.y - sth * xs.z)) : 0.0f;
+      const float p2 = pc2 + row_suffix_excl(e);   // before this step's own term
+      // row q: D_q and the cost gradient at the state before step q (the post-step state of
+      // step q - 1); row n: the cost gradient at the segment's last post-step state
+      const float d1 = a.dt * (p0 * cth + p1 * sth) + dpp_upd<kRowShr + 1>(0.0f, gvx);
+      const float d2 = a.dt * (p1 * cth - p0 * sth) + dpp_upd<kRowShr + 1>(0.0f, gvy);
+      if (lq) {
+        *reinterpret_cast<float4*>(myD + 4 * col) = make_float4(0.0f, d1, d2, a.dt * p2);
+        if (col == n - 1) *reinterpret_cast<float4*>(myD + 4 * n) = make_float4(0.0f, gvx, gvy, 0.0f);
       }
+      pc0 = first_of_half(p0);
+      pc1 = first_of_half(p1);
+      pc2 = first_of_half(p2 + e);
     }
-    __syncthreads();
-    // ---- reverse sweep of the segment ----
-#pragma unroll
-    for (int q = kAdjMaxSeg - 1; q >= 0; --q) {
-      if (q < n) {
-        const int t = t0 + q;
-        const float* row = mySeg + q * kSegStride;
-        pa[0] += row[13];
-        pa[1] += row[14];
-        pa[4] += row[17];
-        pa[5] += row[18];
-        const float h1 = h1s[q], h2 = h2s[q];
-        float a3[4];
-#pragma unroll
-        for (int o = 0; o < 4; ++o) {
-          a3[o] = a.dt * pa[3 + o];
-          gb3[o] += a3[o];
-          gW3[o] = __builtin_fmaf(a3[o], h2, gW3[o]);
-        }
-        float gh2 = w3[0] * a3[0];
-        gh2 = __builtin_fmaf(w3[1], a3[1], gh2);
-        gh2 = __builtin_fmaf(w3[2], a3[2], gh2);
-        gh2 = __builtin_fmaf(w3[3], a3[3], gh2);
-        const float a2 = gh2 * (1.0f - h2 * h2);
-        gb2 += a2;
-        float xa = a2, ya = a2;
-        swap_rows(xa, ya);
-        const float a2x = (r == 0) ? ya : xa;            // a2 of the other row, same column
-        gW2o[0] = __builtin_fmaf(a2, h1, gW2o[0]);
-        gW2x[0] = __builtin_fmaf(a2x, h1, gW2x[0]);
-        float gh1a = a2 * wBo[0];
-        float gh1b = a2x * wBx[0];
-        FMAC_DPP_FIRST(gW2o[1], a2, h1, "row_ror:1");
-        FMAC_DPP_FIRST(gW2x[1], a2x, h1, "row_ror:1");
-        FMAC_DPP(gh1a, a2, wBo[1], "row_ror:1");
-        FMAC_DPP(gh1b, a2x, wBx[1], "row_ror:1");
-#define ADJ_STEP(S)                                        \
-  FMAC_DPP(gW2o[S], a2, h1, "row_ror:" #S);                \
-  FMAC_DPP(gW2x[S], a2x, h1, "row_ror:" #S);               \
-  FMAC_DPP(gh1a, a2, wBo[S], "row_ror:" #S);               \
-  FMAC_DPP(gh1b, a2x, wBx[S], "row_ror:" #S);
-        ADJ_STEP(2) ADJ_STEP(3) ADJ_STEP(4) ADJ_STEP(5) ADJ_STEP(6) ADJ_STEP(7) ADJ_STEP(8)
-        ADJ_STEP(9) ADJ_STEP(10) ADJ_STEP(11) ADJ_STEP(12) ADJ_STEP(13) ADJ_STEP(14) ADJ_STEP(15)
-#undef ADJ_STEP
-        const float a1 = (gh1a + gh1b) * (1.0f - h1 * h1);
-        gb1 += a1;
-        const float in[6] = {row[3], row[4], row[5], row[6], row[9], row[10]};
-        float gin[6];
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {
-          gW1[i] = __builtin_fmaf(a1, in[i], gW1[i]);
-          gin[i] = allsum32(w1[i] * a1);
-        }
-        if (c32 == 0) {
-          const float v0 = row[7], v1 = row[8];
-          myGU[2 * t] = (v0 > a.u_lo0 && v0 < a.u_hi0) ? gin[4] : 0.0f;
-          myGU[2 * t + 1] = (v1 > a.u_lo1 && v1 < a.u_hi1) ? gin[5] : 0.0f;
-        }
-        // p_t = (dF/dx_t)^T p_{t+1}
-        const float cth = row[11], sth = row[12], vx = row[4], vy = row[5];
-        const float np2 = pa[2] + a.dt * (pa[0] * (-sth * vx - cth * vy) + pa[1] * (cth * vx - sth * vy));
-        const float np3 = pa[3] + gin[0];
-        const float np4 = pa[4] + a.dt * (pa[0] * cth + pa[1] * sth) + gin[1];
-        const float np5 = pa[5] + a.dt * (-pa[0] * sth + pa[1] * cth) + gin[2];
-        const float np6 = pa[6] + a.dt * pa[2] + gin[3];
-        pa[2] = np2;
-        pa[3] = np3;
-        pa[4] = np4;
-        pa[5] = np5;
-        pa[6] = np6;
-      }
+    wave_lds_fence();
+    // ---- 3. the reverse chain ----
+    pd = pd + myD[4 * n + comp];
+    float h1 = myH[(n - 1) * 128], h2 = myH[(n - 1) * 128 + 64];
+    float xq = myX[4 * (n - 1) + comp], dr = myD[4 * (n - 1) + comp];
+    vc = *reinterpret_cast<const float2*>(myV + 2 * (t0 + n - 1));
+    for (int q = n - 1; q >= 0; --q) {
+      // the next step's values are read one step ahead
+      const int qn = max(q - 1, 0);
+      const float h1n = myH[qn * 128], h2n = myH[qn * 128 + 64];
+      const float xqn = myX[4 * qn + comp], drn = myD[4 * qn + comp];
+      const float2 vn = *reinterpret_cast<const float2*>(myV + 2 * (t0 + qn));
+      const float a2 = quad_dot(0.0f, pd, w30, w31, w32, w33) * __builtin_fmaf(-h2, h2, 1.0f);
+      quad_axpy(gW3, pd, h2);
+      gb3 += pd;
+      gb2 += a2;
+      gW2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a2, h1, gW2, 0, 0, 0);
+      const float a1 = mul32(0.0f, 0.0f, a2, tP, tQ) * __builtin_fmaf(-h1, h1, 1.0f);
+      const float A = iKA * a1 + dpp_f<kQuadXor1>(iSA * a1);
+      const float B = iKB * a1 + dpp_f<kQuadXor1>(iSB * a1);
+      float u = uK * a1 + dpp_f<kQuadXor1>(uS * a1);
+      float g = A + dpp_f<kQuadXor2>(B);
+      u = u + dpp_f<kQuadXor2>(u);
+      g = g + dpp_f<kRowRor + 8>(g);
+      u = u + dpp_f<kRowRor + 8>(u);
+      g = g + dpp_f<kRowRor + 4>(g);
+      u = u + dpp_f<kRowRor + 4>(u);
+      pd = (pd + dr) + add_rows(g);
+      u = add_rows(u);
+      gb1 += a1;
+      quad_axpy(gX, xq, a1);
+      gV0 = __builtin_fmaf(vc.x, a1, gV0);
+      gV1 = __builtin_fmaf(vc.y, a1, gV1);
+      // g' = 1 strictly inside the bounds (where the clamped control is v itself), else 0
+      const float vi = (lane & 1) ? vc.y : vc.x;
+      myV[2 * (t0 + q) + (lane & 1)] = (vi > lo_i && vi < hi_i) ? u : 0.0f;
+      h1 = h1n;
+      h2 = h2n;
+      xq = xqn;
+      dr = drn;
+      vc = vn;
     }
-    __syncthreads();
+    wave_lds_fence();
   }
 
   // ---- block reduction of the parameter gradients -------------------------------------
-  // Lane (r, c) of every sample holds the same parameter entries, so the two samples
-  // of a wave are added through a cross-half shuffle and the four waves through LDS.
-  auto pair = [&](float v) { return v + __shfl_xor(v, 32, 64); };
+  // Lane (r, c) of every sample holds the same parameter entries (dW2 already sums the two
+  // samples of the wave), so the two samples are added across the halves and the four
+  // waves through LDS.
+  auto pair = [&](float v) { return v + other_half(v); };
+  __syncthreads();   // the segments' LDS of every wave is no longer read
   float* red = sRed + wv * kNP32;
-  // every value is paired by all 64 lanes (the shuffle needs them all), half 0 stores
-  float vals[6];
-#pragma unroll
-  for (int i = 0; i < 6; ++i) vals[i] = pair(gW1[i]);
+  const float v1[8] = {pair(gX[0]), pair(gX[1]), pair(gX[2]), pair(gX[3]), pair(gV0), pair(gV1), pair(gb1), pair(gb2)};
+  const float v3[5] = {a.dt * pair(gW3[0]), a.dt * pair(gW3[1]), a.dt * pair(gW3[2]), a.dt * pair(gW3[3]),
+                       a.dt * pair(gb3)};
   if (half == 0) {
 #pragma unroll
-    for (int i = 0; i < 6; ++i) red[j * 6 + i] = vals[i];
-  }
-  const float vb1 = pair(gb1);
-  if (half == 0) red[192 + j] = vb1;
+    for (int i = 0; i < 6; ++i) red[j * 6 + i] = v1[i];
+    red[192 + j] = v1[6];
+    red[1248 + j] = v1[7];
 #pragma unroll
-  for (int s = 0; s < 16; ++s) {
-    const float vo = pair(gW2o[s]);
-    const float vx2 = pair(gW2x[s]);
-    if (half == 0) {
-      red[224 + (16 * r + src[s]) * HID + j] = vo;
-      red[224 + (16 * (1 - r) + src[s]) * HID + j] = vx2;
-    }
+    for (int o = 0; o < 4; ++o) red[1280 + o * HID + j] = v3[o];
+    if (c32 < 4) red[1408 + c32] = v3[4];
   }
-  const float vb2 = pair(gb2);
-  if (half == 0) red[1248 + j] = vb2;
+  // item v of the product's accumulator: row (a2) 8 (v / 4) + 4 half + v % 4, column (h1) c32
 #pragma unroll
-  for (int o = 0; o < 4; ++o) {
-    const float v = pair(gW3[o]);
-    if (half == 0) red[1280 + o * HID + j] = v;
-  }
-#pragma unroll
-  for (int o = 0; o < 4; ++o) {
-    const float v = pair(gb3[o]);
-    if (lane == 0) red[1408 + o] = v;
-  }
+  for (int v = 0; v < 16; ++v) red[224 + (8 * (v >> 2) + 4 * half + (v & 3)) * HID + c32] = gW2[v];
   __syncthreads();
   const int stride = kNP32 + 2 * T;
   float* out = a.gpart + (size_t)blockIdx.x * stride;
@@ -353,7 +401,7 @@ __global__ __launch_bounds__(kWaveBlock) void adjoint_wave_kernel(AdjointArgs a)
   for (int o = threadIdx.x; o < 2 * T; o += kWaveBlock) {
     float acc = 0.0f;
 #pragma unroll
-    for (int sl = 0; sl < kWaveSlots; ++sl) acc += sGU[sl * 2 * T + o];
+    for (int sl = 0; sl < kWaveSlots; ++sl) acc += sV[sl * eStride + o];
     out[kNP32 + o] = acc;
   }
 }

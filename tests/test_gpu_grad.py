@@ -76,6 +76,17 @@ def test_checkpoint_interval_does_not_change_the_gradient(M, orc):
             assert np.abs(gth - ref[1]).max() <= 1e-4 * s
 
 
+@pytest.mark.parametrize("K,T,ckpt", [(1, 1, 16), (8, 16, 16), (9, 17, 16), (17, 256, 16), (7, 33, 1), (24, 128, 15)])
+def test_gradient_segment_edges(M, orc, K, T, ckpt):
+    """Segments that end at, before and after the horizon, the shortest and longest of each,
+    with biases, the slip term, samples at the clamp bounds and a horizon whose controls
+    fill the LDS layout."""
+    cost = synth.CostParams(w_map=100.0, w_speed=1.0, w_slip=2.0, v_des=6.0)
+    prob = synth.with_(synth.c5_problem(seed=6), K=K, T=T, cost=cost, u_lo=(-0.4, -0.3), u_hi=(0.5, 0.6), lam=20.0)
+    _grad_check(M, orc, prob, synth.C1_X0, synth.random_controls(T, K, scale=0.2), it=3, ckpt=ckpt,
+                params=synth.mlp_params(32, 6, bias_scale=0.3))
+
+
 @pytest.mark.parametrize("seed", [0, 1, 2, 3, 4])
 def test_gradient_full_size(M, orc, seed):
     """The differentiation workload: K=4096, T=100, checkpoints every 10 steps, seeds 0-4
