@@ -26,9 +26,18 @@ struct U32x4 {
   uint32_t x, y, z, w;
 };
 
+// a ^ b ^ c, and a with its bits under b & c flipped, each as one v_bitop3_b32.
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+}
+__device__ __forceinline__ float flip_sign(float v, uint32_t bits) {   // -v when bit 31 of bits is set
+  return __builtin_bit_cast(float, __builtin_amdgcn_bitop3_b32(__builtin_bit_cast(int, v), (int)bits, (int)0x80000000u, 0x78));
+}
+
 // WIDE: each round's 32 x 32 -> 64-bit products as one v_mad_u64_u32 each (~30 % more
-// Philox calls per second on gfx950 than a v_mul_lo_u32 and a v_mul_hi_u32 each); the
-// same words either way.
+// Philox calls per second on gfx950 than a v_mul_lo_u32 and a v_mul_hi_u32 each, which
+// have the shorter latency: for a launch of one or two waves per SIMD); the same words
+// either way.
 template <bool WIDE = true>
 __device__ __forceinline__ U32x4 philox10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                           uint32_t k0, uint32_t k1) {
@@ -48,8 +57,8 @@ __device__ __forceinline__ U32x4 philox10(uint32_t c0, uint32_t c1, uint32_t c2,
       lo_b = c2 * 0xCD9E8D57u;
       hi_b = __umulhi(c2, 0xCD9E8D57u);
     }
-    const uint32_t y0 = hi_b ^ c1 ^ k0;
-    const uint32_t y2 = hi_a ^ c3 ^ k1;
+    const uint32_t y0 = xor3(hi_b, c1, k0);
+    const uint32_t y2 = xor3(hi_a, c3, k1);
     c0 = y0;
     c1 = lo_b;
     c2 = y2;
@@ -70,13 +79,21 @@ __device__ __forceinline__ U32x4 philox10(uint32_t c0, uint32_t c1, uint32_t c2,
 // P(z) = 1/3 + z/5 + z^2/7 + z^3/9 + z^4/11 (FP32 coefficients, Horner with fma).
 __device__ __forceinline__ float noise_ln(uint32_t w) {
   const uint32_t n = ((w >> 9) << 1) | 1u;
-  int e = 31 - __builtin_clz(n);
-  float f = __builtin_ldexpf((float)n, -e);
+  const uint32_t b = __builtin_bit_cast(uint32_t, (float)n);   // exact: n < 2^24
+  int e = (int)(b >> 23) - 127;
+  float f = __builtin_bit_cast(float, (b & 0x007FFFFFu) | 0x3F800000u);
   if (f >= 0x1.6a09e6p+0f) {
     f = f * 0.5f;
     e += 1;
   }
-  const float s = (f - 1.0f) / (f + 1.0f);
+  // s = (f - 1) / (f + 1), rounded as the division rounds it: a Newton step on the
+  // reciprocal and one residual correction of the quotient (no scaling: the operands are
+  // of order one; equal for all 2^23 words)
+  const float num = f - 1.0f, den = f + 1.0f;
+  float y = __builtin_amdgcn_rcpf(den);
+  y = __builtin_fmaf(__builtin_fmaf(-den, y, 1.0f), y, y);
+  float s = num * y;
+  s = __builtin_fmaf(__builtin_fmaf(-den, s, num), y, s);
   const float z = s * s;
   float p = 0x1.745d18p-4f;          // 1/11
   p = __builtin_fmaf(p, z, 0x1.c71c72p-4f);   // 1/9
@@ -85,6 +102,19 @@ __device__ __forceinline__ float noise_ln(uint32_t w) {
   p = __builtin_fmaf(p, z, 0x1.555556p-2f);   // 1/3
   const float at = __builtin_fmaf(s * z, p, s);
   return __builtin_fmaf((float)(e - 24), 0x1.62e430p-1f, 2.0f * at);   // + (e-24) ln 2
+}
+
+// sqrt of x = -2 ln u, rounded as sqrtf rounds it: x is between 2^-23 and 34, so the reciprocal
+// square root needs no scaling; one coupled Newton step and one residual correction
+// (equal for all 2^23 words).
+__device__ __forceinline__ float noise_sqrt(float x) {
+  const float y = __builtin_amdgcn_rsqf(x);
+  float g = x * y;
+  float h = 0.5f * y;
+  const float r = __builtin_fmaf(-h, g, 0.5f);
+  g = __builtin_fmaf(g, r, g);
+  h = __builtin_fmaf(h, r, h);
+  return __builtin_fmaf(__builtin_fmaf(-g, g, x), h, g);
 }
 
 // cos(2 pi u), sin(2 pi u).  2 pi u = (pi/2)(q + r): q = nearest quadrant from the
@@ -110,11 +140,10 @@ __device__ __forceinline__ void noise_cs(uint32_t w, float& c_out, float& s_out)
   pc = __builtin_fmaf(pc, r2, 0x1.03c1f0p-2f);    // m = 4
   pc = __builtin_fmaf(pc, r2, -0x1.3bd3ccp+0f);   // m = 2
   const float cs = __builtin_fmaf(pc, r2, 1.0f);
-  const uint32_t qq = q & 3u;
-  const float a = (qq & 1u) ? sn : cs;            // |cos| candidate
-  const float b = (qq & 1u) ? cs : sn;            // |sin| candidate
-  c_out = (qq == 1u || qq == 2u) ? -a : a;
-  s_out = (qq >= 2u) ? -b : b;
+  const float a = (q & 1u) ? sn : cs;             // |cos| candidate
+  const float b = (q & 1u) ? cs : sn;             // |sin| candidate
+  c_out = flip_sign(a, (q + 1u) << 30);           // quadrants 1 and 2
+  s_out = flip_sign(b, q << 30);                  // quadrants 2 and 3
 }
 
 // eps_{k,t} for iteration `iter`: sqrt(Sigma_ii) * (R cos, R sin), R = sqrt(-2 ln u1).
@@ -125,7 +154,7 @@ __device__ __forceinline__ void draw_eps(uint32_t t, uint32_t k, const NoiseKey&
                                          float& e1) {
   const U32x4 r = philox10<WIDE>(t, nk.k_base + k, nk.iter, nk.instance, nk.key_lo, nk.key_hi);
   const float L = noise_ln(r.x);
-  const float R = __builtin_sqrtf(-2.0f * L);
+  const float R = noise_sqrt(-2.0f * L);
   float c, s;
   noise_cs(r.y, c, s);
   e0 = nk.sig0 * (R * c);
@@ -297,15 +326,38 @@ __device__ __forceinline__ void grid_coord(float ph, float pl, float o, float re
 __device__ __forceinline__ void map_taps(const CostArgs& c, float pxh, float pxl, float pyh, float pyl,
                                          int idx[4], float& fx, float& fy) {
   int j0, i0;
-  const float inv_res = 1.0f / c.res;
-  grid_coord(pxh, pxl, c.ox, c.res, inv_res, c.W, j0, fx);
-  grid_coord(pyh, pyl, c.oy, c.res, inv_res, c.H, i0, fy);
+  grid_coord(pxh, pxl, c.ox, c.res, c.inv_res, c.W, j0, fx);
+  grid_coord(pyh, pyl, c.oy, c.res, c.inv_res, c.H, i0, fy);
   const int ja = min(max(j0, 0), c.W - 1), jb = min(max(j0 + 1, 0), c.W - 1);
   const int ia = min(max(i0, 0), c.H - 1), ib = min(max(i0 + 1, 0), c.H - 1);
   idx[0] = ia * c.W + ja;
   idx[1] = ia * c.W + jb;
   idx[2] = ib * c.W + ja;
   idx[3] = ib * c.W + jb;
+}
+
+// min(max(v, 0), hi) for hi >= 0, as one v_med3_i32.
+__device__ __forceinline__ int clamp_index(int v, int hi) {
+  int r;
+  asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(v), "s"(hi));
+  return r;
+}
+
+// map_taps with the corners as byte offsets from the map's start: a map holds at most 2^30
+// cells, so they fit 32 bits and the loads need no 64-bit address arithmetic.
+__device__ __forceinline__ void map_taps_bytes(const CostArgs& c, float pxh, float pxl, float pyh, float pyl,
+                                               uint32_t off[4], float& fx, float& fy) {
+  int j0, i0;
+  grid_coord(pxh, pxl, c.ox, c.res, c.inv_res, c.W, j0, fx);
+  grid_coord(pyh, pyl, c.oy, c.res, c.inv_res, c.H, i0, fy);
+  const uint32_t ja = (uint32_t)clamp_index(j0, c.W - 1), jb = (uint32_t)clamp_index(j0 + 1, c.W - 1);
+  const uint32_t ia = (uint32_t)clamp_index(i0, c.H - 1), ib = (uint32_t)clamp_index(i0 + 1, c.H - 1);
+  const uint32_t W4 = (uint32_t)c.W * 4u;
+  off[0] = ia * W4 + (ja << 2);
+  const uint32_t dj = (jb - ja) << 2, di = ib != ia ? W4 : 0u;
+  off[1] = off[0] + dj;
+  off[2] = off[0] + di;
+  off[3] = off[2] + dj;
 }
 
 __device__ __forceinline__ float bilerp(const float m[4], float fx, float fy) {
@@ -323,13 +375,20 @@ __device__ __forceinline__ float costmap_at2(const CostArgs& c, const float* __r
   return bilerp(m, fx, fy);
 }
 
-// c(x, t) given the map value h at the post-step position and fl32(decay^t).
-__device__ __forceinline__ float state_cost_h(const CostArgs& c, float h, float decay_t, float vx, float vy) {
+// The side-slip angle zeta, or 0 where neither slip term can count.  Formed before the map
+// values are used, so that it runs while they are loaded.
+__device__ __forceinline__ float slip_angle(const CostArgs& c, float vx, float vy) {
+  float zeta = 0.0f;
+  if (c.slip_on) zeta = -atan2f(vy, fabsf(vx));
+  return zeta;
+}
+
+// c(x, t) given the map value h at the post-step position, fl32(decay^t) and the slip angle.
+__device__ __forceinline__ float state_cost_h(const CostArgs& c, float h, float decay_t, float vx, float zeta) {
   float cost = c.w_map * h;
   if (h > c.map_thresh) cost += c.crash_cost * decay_t;
   const float dv = vx - c.v_des;
   cost += c.w_speed * (dv * dv);
-  const float zeta = -atan2f(vy, fabsf(vx));
   cost += c.w_slip * (zeta * zeta);
   if (fabsf(zeta) > c.slip_thresh) cost += c.slip_cost;
   return cost;
@@ -339,23 +398,12 @@ __device__ __forceinline__ float state_cost_h(const CostArgs& c, float h, float 
 __device__ __forceinline__ float state_cost2(const CostArgs& c, const float* __restrict__ map,
                                              const float* __restrict__ decay, float pxh, float pxl,
                                              float pyh, float pyl, float vx, float vy, int t) {
-  const float h = costmap_at2(c, map, pxh, pxl, pyh, pyl);
-  return state_cost_h(c, h, decay[t], vx, vy);
-}
-
-// c(x, t) on the post-step state: track (+ decaying impulse), speed, side slip.
-__device__ __forceinline__ float state_cost(const CostArgs& c, const float* __restrict__ map,
-                                            const float* __restrict__ decay, float px, float py,
-                                            float vx, float vy, int t) {
-  const float h = costmap_at(c, map, px, py);
-  float cost = c.w_map * h;
-  if (h > c.map_thresh) cost += c.crash_cost * decay[t];
-  const float dv = vx - c.v_des;
-  cost += c.w_speed * (dv * dv);
-  const float zeta = -atan2f(vy, fabsf(vx));
-  cost += c.w_slip * (zeta * zeta);
-  if (fabsf(zeta) > c.slip_thresh) cost += c.slip_cost;
-  return cost;
+  int idx[4];
+  float fx, fy;
+  map_taps(c, pxh, pxl, pyh, pyl, idx, fx, fy);
+  const float m[4] = {map[idx[0]], map[idx[1]], map[idx[2]], map[idx[3]]};
+  const float zeta = slip_angle(c, vx, vy);
+  return state_cost_h(c, bilerp(m, fx, fy), decay[t], vx, zeta);
 }
 
 // Gradient of the smooth part of c(x) with respect to (p_x, p_y, v_x, v_y): the

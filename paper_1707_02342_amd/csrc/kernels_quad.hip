@@ -18,8 +18,8 @@
 // Kinematics and cost run in chunks of 16 steps, lane-parallel: lane group g takes
 // four consecutive steps of the chunk for its sample, with exclusive scans over the
 // four lane groups (v_permlane16_swap / v_permlane32_swap).  The noise of a chunk is
-// drawn before the chunk (four draws per lane) and regenerated for the weighted
-// perturbation sum at the end.
+// drawn before the chunk (four draws per lane) and kept in memory for the weighted
+// perturbation sum at the end (drawn again where there is no such memory).
 #include "kernels_common.hip.h"
 
 namespace mppi {
@@ -30,6 +30,10 @@ constexpr int kQuadBlock = 256;
 constexpr int kQuadWaves = 4;
 constexpr int kQuadSamples = 64;   // per block
 constexpr int kQuadChunk = 16;     // steps per chunk
+// floats of the chunk's clamped controls, [4 waves][16 steps][16 samples][2] and a row of
+// padding (the chain reads one step ahead); later the block's N row (2T)
+constexpr int kQuadControls = kQuadWaves * kQuadChunk * 16 * 2 + 32;
+static_assert(kQuadControls >= 2 * kTMax, "the N row reuses the controls' space");
 
 __device__ __forceinline__ float q_as_f(uint32_t v) { return __builtin_bit_cast(float, v); }
 __device__ __forceinline__ uint32_t q_as_u(float v) { return __builtin_bit_cast(uint32_t, v); }
@@ -54,9 +58,11 @@ __device__ __forceinline__ void scan4_excl2(float hi, float lo, int g, float& ph
   float H[4], L[4];
   all4(hi, H);
   all4(lo, L);
-  float sh = 0.0f, sl = 0.0f;
+  float sh = H[0], sl = L[0];
+  ph = 0.0f;
+  pl = 0.0f;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 1; i < 4; ++i) {
     if (i == g) {
       ph = sh;
       pl = sl;
@@ -68,6 +74,50 @@ __device__ __forceinline__ void scan4_excl2(float hi, float lo, int g, float& ph
   }
   th = sh;
   tl = sl;
+}
+
+// v + v in the lanes 8, 4, 2 and 1 apart of each 16-lane row in turn: the row's sum in every
+// lane (DPP moves; once the lanes 8 apart agree, rotating by 4 meets the lane 4 apart).
+template <int CTRL>
+__device__ __forceinline__ float q_dpp(float v) {
+  return q_as_f((uint32_t)__builtin_amdgcn_mov_dpp((int)q_as_u(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kQRor8 = 0x128, kQRor4 = 0x124, kQXor2 = 0x4E, kQXor1 = 0xB1;
+__device__ __forceinline__ float row_sum(float v) {
+  v += q_dpp<kQRor8>(v);
+  v += q_dpp<kQRor4>(v);
+  v += q_dpp<kQXor2>(v);
+  v += q_dpp<kQXor1>(v);
+  return v;
+}
+__device__ __forceinline__ float row_min(float v) {
+  v = fminf(v, q_dpp<kQRor8>(v));
+  v = fminf(v, q_dpp<kQRor4>(v));
+  v = fminf(v, q_dpp<kQXor2>(v));
+  v = fminf(v, q_dpp<kQXor1>(v));
+  return v;
+}
+
+// tanh of four values, PRE: of x from x * kTanhScale.  The empty asm statements keep the four
+// in step: each stage's results are used only after all four have been issued, so the
+// latency of one exp or rcp is covered by the others' (the compiler, short of
+// registers, ran them one after the other: K = 65536, FP32, two waves per SIMD 745 -> 702
+// us; K = 16384, FP32, h = 32, one wave 116 -> 107 us).  The values are tanh_f's and
+// tanh_prescaled's.
+template <bool PRE>
+__device__ __forceinline__ void tanh4(const qf32x4 d, float h[4]) {
+  float e[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(PRE ? d[r] : d[r] * kTanhScale);
+  asm("" : "+v"(e[0]), "+v"(e[1]), "+v"(e[2]), "+v"(e[3]));
+#pragma unroll
+  for (int r = 0; r < 4; ++r) e[r] = e[r] + 1.0f;
+  asm("" : "+v"(e[0]), "+v"(e[1]), "+v"(e[2]), "+v"(e[3]));
+#pragma unroll
+  for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_rcpf(e[r]);
+  asm("" : "+v"(e[0]), "+v"(e[1]), "+v"(e[2]), "+v"(e[3]));
+#pragma unroll
+  for (int r = 0; r < 4; ++r) h[r] = __builtin_fmaf(-2.0f, e[r], 1.0f);
 }
 
 constexpr int kQPrecFP32 = 0;
@@ -126,8 +176,7 @@ struct QuadNet<kQPrecFP32, HID> {
       qf32x4 d = {0.0f, 0.0f, 0.0f, 0.0f};
       d = __builtin_amdgcn_mfma_f32_16x16x4f32(A1[m][0], b0, d, 0, 0, 0);
       d = __builtin_amdgcn_mfma_f32_16x16x4f32(A1[m][1], b1, d, 0, 0, 0);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) h1[m][r] = tanh_prescaled(d[r]);
+      tanh4<true>(d, h1[m]);
     }
     float h2[NM][4];
     qf32x4 d2[NM];
@@ -141,9 +190,7 @@ struct QuadNet<kQPrecFP32, HID> {
         for (int m = 0; m < NM; ++m)
           d2[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(A2[m][mi][r], h1[mi][r], d2[m], 0, 0, 0);
 #pragma unroll
-    for (int m = 0; m < NM; ++m)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) h2[m][r] = tanh_prescaled(d2[m][r]);
+    for (int m = 0; m < NM; ++m) tanh4<true>(d2[m], h2[m]);
     qf32x4 d3 = C3;   // lane (g, i): d3[o] = group g's part of output o of sample i
 #pragma unroll
     for (int m = 0; m < NM; ++m)
@@ -208,11 +255,6 @@ struct QuadNet {
   qf32x4 C3;
 
   static constexpr float kPre = PREC == kQPrecBF16 ? kTanhScale : 1.0f;
-  static __device__ __forceinline__ float act(float d) {
-    if constexpr (PREC == kQPrecBF16) return tanh_prescaled(d);
-    else return tanh_f(d);
-  }
-
   static __device__ __forceinline__ int neuron(int kb, int g, int c) {
     return 16 * (2 * kb + (c >> 2)) + 4 * g + (c & 3);
   }
@@ -262,8 +304,7 @@ struct QuadNet {
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
       const qf32x4 d = Ops::mma(A1[m], B1, qf32x4{0.0f, 0.0f, 0.0f, 0.0f});
-#pragma unroll
-      for (int r = 0; r < 4; ++r) h1[m][r] = act(d[r]);
+      tanh4<PREC == kQPrecBF16>(d, h1[m]);
     }
     vec B2[NKB];
 #pragma unroll
@@ -278,8 +319,7 @@ struct QuadNet {
       qf32x4 d = C2[m];
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb) d = Ops::mma(A2[m][kb], B2[kb], d);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) h2[m][r] = act(d[r]);
+      tanh4<PREC == kQPrecBF16>(d, h2[m]);
     }
     qf32x4 d3 = C3;
 #pragma unroll
@@ -292,19 +332,34 @@ struct QuadNet {
   }
 };
 
-// One tile of 64 samples (tile * 64 ... + 63) of one problem; lds_f: the block's LDS.
+// One tile of 64 samples (tile * 64 ... + 63) of one problem.
+//
+// What bounds it: issue.  A matrix-core instruction and a vector instruction do not overlap
+// on gfx950, also from different waves (microbenchmarks: 32 cycles per 16x16x4 FP32
+// product plus 4.4 per vector instruction, 2.2 for an FP32 add, multiply or fma that two
+// waves issue together, 8.2 per exp or rcp), so a step of 16 samples costs its 704 (h = 32)
+// matrix cycles plus every vector instruction.  Hence everything that does not belong to
+// the chain is done once per sample and step, in the lane that draws the step's noise (the
+// clamped control and the control cost) or that evaluates its cost, and trajectories are
+// checked for non-finite states at their end: a state that is not finite stays so, since
+// every step adds to it.  242 -> ~196 vector instructions per wave-step beside the matrix
+// products; with tanh4 below, before -> after: batched form (512 instances, 1.01e8 steps)
+// 4.69 -> 4.44 ms; h = 64, T = 100: FP32 K = 65536 759 -> 702 us, BF16 332 -> 284 us, FP16 365 ->
+// 317 us, K = 16384 (one wave per SIMD) FP32 226 -> 197, BF16 124 -> 100, FP16 129 -> 106 us.
 template <int PREC, int HID, bool RECEDE = true>
 __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, float* sE, float* sX,
                                   float* red) {
-  const int T = a.T;
+  const int T = __builtin_amdgcn_readfirstlane(a.T);
   const int lane = threadIdx.x & 63;
-  const int wv = threadIdx.x >> 6;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4;
   const int j = lane & 15;
   const int k = tile * kQuadSamples + wv * 16 + j;
   const bool valid = k < a.K;
   const bool zm = k >= a.K_imp;   // exploration sample: v = eps, delta = eps - u
-  float* wE = sE + wv * (kQuadChunk * 16 * 2);          // [chunk step][sample][2]
+  // v = eps + m_u u, delta = eps - m_z u, with one of the two 1 and the other 0 (exact)
+  const float m_u = zm ? 0.0f : 1.0f, m_z = zm ? 1.0f : 0.0f;
+  float* wE = sE + wv * (kQuadChunk * 16 * 2);          // [chunk step][sample][2] clamped controls
   float* wX = sX + wv * ((kQuadChunk + 1) * 16 * 4);    // [chunk step 0..16][sample][4]
   // the stored noise of the wave's 16 samples ([T][16][2]), or null
   float* wS = a.eps_store ? a.eps_store + ((size_t)tile * kQuadWaves + wv) * (size_t)T * 32 : nullptr;
@@ -316,169 +371,144 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
   float x0v[kStateDim];
 #pragma unroll
   for (int i = 0; i < kStateDim; ++i) x0v[i] = a.x0_dev ? a.x0_dev[i] : a.x0[i];
-  const float lo_g = g == 0 ? a.u_lo0 : a.u_lo1;
-  const float hi_g = g == 0 ? a.u_hi0 : a.u_hi1;
-  const float gcs_g = g == 0 ? a.gcs0 : a.gcs1;
+  const float b_const = g == 2 ? 1.0f : 0.0f;   // the network's input of lane groups 2 and 3
 
   Acc xd{x0v[3 + g], 0.0f};          // state component g (roll, v_x, v_y, theta_dot)
   // pose carries (compensated), the same in the four lanes of a sample
   float th_h = x0v[2], th_l = 0.0f, px_h = x0v[0], px_l = 0.0f, py_h = x0v[1], py_l = 0.0f;
   Acc Sacc{0.0f, 0.0f};
-  bool ok = true;
   wX[j * 4 + g] = xd.hi;             // chunk row 0 = the state entering the chunk
-
-  // noise pair p = lane + 64 q of the chunk starting at step c0 -> (step c0 + p / 16,
-  // sample p % 16): drawn, then kept in the chunk's rows and (stored noise) at (step,
-  // sample), where the lane that reads it back below is this lane
-  auto draw_pair = [&](int c0, int q, float& e0, float& e1) {
-    const int p = lane + 64 * q;
-    draw_eps((uint32_t)min(c0 + (p >> 4), T - 1), (uint32_t)(tile * kQuadSamples + wv * 16 + (p & 15)), a.nk, e0, e1);
-  };
-  auto keep_pair = [&](int c0, int q, float e0, float e1) {
-    const int p = lane + 64 * q;
-    wE[p * 2] = e0;
-    wE[p * 2 + 1] = e1;
-    if (wS && c0 + (p >> 4) < T) *reinterpret_cast<float2*>(wS + (size_t)(c0 * 16 + p) * 2) = make_float2(e0, e1);
-  };
-  // step s of the chunk starting at cs (the serial chain); lane groups 0 and 1 take control
-  // component g, 2 and 3 the constant inputs (both read by every lane and selected: no
-  // branch in the step, which with this code's shape kept the compiler from spilling
-  // registers of the h = 32 kernels)
-  auto chain_step = [&](int cs, int s) {
-    const int t = cs + s;
-    const int gc = g & 1;
-    const float e = wE[(s * 16 + j) * 2 + gc];
-    const float u = sU[2 * t + gc];
-    const float vc = fminf(fmaxf(zm ? e : u + e, lo_g), hi_g);
-    const float b1v = g < 2 ? vc : (g == 2 ? 1.0f : 0.0f);
-    if (g < 2) Sacc.add(gcs_g * (u * (zm ? e - u : e)));   // the control-cost term, one component per lane
-    const float f = net.eval(xd.hi, b1v);
-    xd.add(a.dt * f);
-    wX[((s + 1) * 16 + j) * 4 + g] = xd.value();
-  };
 
   for (int cs = 0; cs < T; cs += kQuadChunk) {
     const int n = min(kQuadChunk, T - cs);
+    // the noise of the chunk: lane (g, j) draws steps cs + g + 4 q of its own sample
+    // (past the horizon a clamped step, discarded), forms their clamped controls for the
+    // chain and their control cost, and keeps the noise where it reads it back below
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
+      const int s = 4 * q + g;
+      const int t = min(cs + s, T - 1);
       float e0, e1;
-      draw_pair(cs, q, e0, e1);
-      keep_pair(cs, q, e0, e1);
+      draw_eps((uint32_t)t, (uint32_t)k, a.nk, e0, e1);
+      const float2 u = *reinterpret_cast<const float2*>(sU + 2 * t);
+      const float v0 = __builtin_amdgcn_fmed3f(__builtin_fmaf(u.x, m_u, e0), a.u_lo0, a.u_hi0);
+      const float v1 = __builtin_amdgcn_fmed3f(__builtin_fmaf(u.y, m_u, e1), a.u_lo1, a.u_hi1);
+      *reinterpret_cast<float2*>(wE + (s * 16 + j) * 2) = make_float2(v0, v1);
+      if (s < n) {
+        if (wS) *reinterpret_cast<float2*>(wS + (uint32_t)((t * 16 + j) * 2)) = make_float2(e0, e1);
+        Sacc.add(a.gcs0 * (u.x * __builtin_fmaf(-u.x, m_z, e0)));
+        Sacc.add(a.gcs1 * (u.y * __builtin_fmaf(-u.y, m_z, e1)));
+      }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // the serial chain over the chunk
-    for (int s = 0; s < n; ++s) chain_step(cs, s);
+    // the serial chain over the chunk: lane groups 0 and 1 take control component g (read
+    // one step ahead; the row past the last is padding), 2 and 3 their constant
+    {
+      const float* pe = wE + j * 2 + (g & 1);
+      float* px = wX + 64 + j * 4 + g;
+      float v = pe[0];
+      for (int s = 0; s < n; ++s) {
+        pe += 32;
+        const float vn = pe[0];
+        const float f = net.eval(xd.hi, g < 2 ? v : b_const);
+        xd.add(a.dt * f);
+        px[0] = xd.value();
+        px += 64;
+        v = vn;
+      }
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // kinematics and cost of the chunk: lane group g takes steps cs + 4 g .. cs + 4 g + 3
-    float tdh = 0.0f, tdl = 0.0f;
+    // kinematics and cost of the chunk: lane group g takes steps cs + 4 g .. cs + 4 g + 3;
+    // a step past the horizon adds zeros
+    const float* row = wX + (4 * g * 16 + j) * 4;   // the state before the lane's first step
+    bool live[4];
+    float dth[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int s = 4 * g + q;
-      if (s < n) {
-        float s_, e_;
-        two_sum(tdh, a.dt * wX[(s * 16 + j) * 4 + 3], s_, e_);
-        tdh = s_;
-        tdl += e_;
-      }
+      live[q] = 4 * g + q < n;
+      dth[q] = live[q] ? a.dt * row[q * 64 + 3] : 0.0f;
+    }
+    float tdh = dth[0], tdl = 0.0f;
+#pragma unroll
+    for (int q = 1; q < 4; ++q) {
+      float s_, e_;
+      two_sum(tdh, dth[q], s_, e_);
+      tdh = s_;
+      tdl += e_;
     }
     float pth, ptl, Tth, Ttl;
     scan4_excl2(tdh, tdl, g, pth, ptl, Tth, Ttl);
-    float th = th_h, thl = th_l;
-    {
-      float s_, e_;
-      two_sum(th, pth, s_, e_);
-      th = s_;
-      thl = thl + (ptl + e_);
-    }
     float dpx[4], dpy[4];
-    float dxh = 0.0f, dxl = 0.0f, dyh = 0.0f, dyl = 0.0f;
     {
-      float th2 = th, thl2 = thl;
+      float th, thl, e_;
+      two_sum(th_h, pth, th, e_);
+      thl = th_l + (ptl + e_);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int s = 4 * g + q;
-        dpx[q] = 0.0f;
-        dpy[q] = 0.0f;
-        if (s < n) {
-          const float4 xs = *reinterpret_cast<const float4*>(wX + (s * 16 + j) * 4);
-          float sn, c_;
-          sincosf(th2 + thl2, &sn, &c_);
-          dpx[q] = a.dt * (c_ * xs.y - sn * xs.z);
-          dpy[q] = a.dt * (sn * xs.y + c_ * xs.z);
-          float s_, e_;
-          two_sum(dxh, dpx[q], s_, e_);
-          dxh = s_;
-          dxl += e_;
-          two_sum(dyh, dpy[q], s_, e_);
-          dyh = s_;
-          dyl += e_;
-          two_sum(th2, a.dt * xs.w, s_, e_);
-          th2 = s_;
-          thl2 += e_;
+        const float vx = row[q * 64 + 1], vy = row[q * 64 + 2];
+        float sn, c_;
+        sincosf(th + thl, &sn, &c_);
+        const float ax = a.dt * (c_ * vx - sn * vy), ay = a.dt * (sn * vx + c_ * vy);
+        dpx[q] = live[q] ? ax : 0.0f;
+        dpy[q] = live[q] ? ay : 0.0f;
+        if (q < 3) {
+          float s_;
+          two_sum(th, dth[q], s_, e_);
+          th = s_;
+          thl += e_;
         }
       }
+    }
+    float dxh = dpx[0], dxl = 0.0f, dyh = dpy[0], dyl = 0.0f;
+#pragma unroll
+    for (int q = 1; q < 4; ++q) {
+      float s_, e_;
+      two_sum(dxh, dpx[q], s_, e_);
+      dxh = s_;
+      dxl += e_;
+      two_sum(dyh, dpy[q], s_, e_);
+      dyh = s_;
+      dyl += e_;
     }
     float pxh, pxl, Txh, Txl, pyh, pyl, Tyh, Tyl;
     scan4_excl2(dxh, dxl, g, pxh, pxl, Txh, Txl);
     scan4_excl2(dyh, dyl, g, pyh, pyl, Tyh, Tyl);
-    float ph_x = px_h, pl_x = px_l, ph_y = py_h, pl_y = py_l;
+    // positions after each of the lane's steps, and every map and decay load at once
+    float mv[4][4], fxv[4], fyv[4], dec[4];
     {
-      float s_, e_;
-      two_sum(ph_x, pxh, s_, e_);
-      ph_x = s_;
-      pl_x = pl_x + (pxl + e_);
-      two_sum(ph_y, pyh, s_, e_);
-      ph_y = s_;
-      pl_y = pl_y + (pyl + e_);
-    }
-    // positions after each of the lane's steps, then every map and decay load at once
-    float qxh[4], qxl[4], qyh[4], qyl[4], qth[4];
-    {
-      float th2 = th, thl2 = thl;
+      float ph_x, pl_x, ph_y, pl_y, e_;
+      two_sum(px_h, pxh, ph_x, e_);
+      pl_x = px_l + (pxl + e_);
+      two_sum(py_h, pyh, ph_y, e_);
+      pl_y = py_l + (pyl + e_);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int s = 4 * g + q;
-        if (s < n) {
-          float s_, e_;
-          two_sum(ph_x, dpx[q], s_, e_);
-          ph_x = s_;
-          pl_x += e_;
-          two_sum(ph_y, dpy[q], s_, e_);
-          ph_y = s_;
-          pl_y += e_;
-          two_sum(th2, a.dt * wX[(s * 16 + j) * 4 + 3], s_, e_);
-          th2 = s_;
-          thl2 += e_;
-        }
-        qxh[q] = ph_x;
-        qxl[q] = pl_x;
-        qyh[q] = ph_y;
-        qyl[q] = pl_y;
-        qth[q] = th2 + thl2;
+        float s_;
+        two_sum(ph_x, dpx[q], s_, e_);
+        ph_x = s_;
+        pl_x += e_;
+        two_sum(ph_y, dpy[q], s_, e_);
+        ph_y = s_;
+        pl_y += e_;
+        uint32_t off[4];
+        map_taps_bytes(a.cost, ph_x, pl_x, ph_y, pl_y, off, fxv[q], fyv[q]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          mv[q][i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.map) + off[i]);
+        dec[q] = a.decay[(uint32_t)(min(cs + 4 * g + q, T - 1) + 1)];
       }
     }
-    float mv[4][4], fxv[4], fyv[4], dec[4];
+    float zeta[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) zeta[q] = slip_angle(a.cost, row[(q + 1) * 64 + 1], row[(q + 1) * 64 + 2]);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      int idx[4];
-      map_taps(a.cost, qxh[q], qxl[q], qyh[q], qyl[q], idx, fxv[q], fyv[q]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) mv[q][i] = a.map[idx[i]];
-      dec[q] = a.decay[min(cs + 4 * g + q, T - 1) + 1];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int s = 4 * g + q;
-      if (s < n) {
-        const float4 xn = *reinterpret_cast<const float4*>(wX + ((s + 1) * 16 + j) * 4);
-        Sacc.add(state_cost_h(a.cost, bilerp(mv[q], fxv[q], fyv[q]), dec[q], xn.y, xn.z));
-        ok = ok && finite_f(qxh[q] + qxl[q]) && finite_f(qyh[q] + qyl[q]) && finite_f(qth[q]) &&
-             finite_f(xn.x) && finite_f(xn.y) && finite_f(xn.z) && finite_f(xn.w);
-      }
+      const float c = state_cost_h(a.cost, bilerp(mv[q], fxv[q], fyv[q]), dec[q], row[(q + 1) * 64 + 1], zeta[q]);
+      Sacc.add(live[q] ? c : 0.0f);
     }
     // carries into the next chunk
     {
@@ -496,12 +526,13 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // the chunk's last state enters the next chunk as its row 0
-    wX[j * 4 + g] = wX[(n * 16 + j) * 4 + g];
+    // the chunk's last state (as the cost reads it) enters the next chunk as its row 0
+    wX[j * 4 + g] = xd.value();
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
+  const bool ok = finite_f(xd.value()) && finite_f(th_h + th_l) && finite_f(px_h + px_l) && finite_f(py_h + py_l);
 
   // S_k: the four lanes' sums
   float H[4], L[4];
@@ -542,35 +573,25 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
 
   // ---- the block's softmin partial ----------------------------------------------------
   float* scratch = red + kQuadWaves * 2 * kTMax;   // [8]
-  float wmin = S;
-#pragma unroll
-  for (int m = 8; m >= 1; m >>= 1) wmin = fminf(wmin, __shfl_xor(wmin, m, 16));
+  const float wmin = row_min(S);
   if (lane == 0) scratch[wv] = wmin;
   __syncthreads();
   const float rho = fminf(fminf(scratch[0], scratch[1]), fminf(scratch[2], scratch[3]));
   const float e = rel_weight(S, rho, a.inv_lambda);
-  float esum = e;
-#pragma unroll
-  for (int m = 8; m >= 1; m >>= 1) esum += __shfl_xor(esum, m, 16);
+  const float esum = row_sum(e);
   if (lane == 0) scratch[4 + wv] = esum;
   // N[t] = sum_k e_k delta_{k,t}: lane group g takes steps t = g, g + 4, ... of its sample
   // (the stored noise, written by this lane in the chunk draws, or drawn again) and the 16
-  // samples of a row are summed with shuffles
+  // samples of a row are summed in DPP moves.  A sample past K has weight zero.
+  const bool any_zm = a.K_imp < a.K;
   auto add_step = [&](int t, float e0, float e1) {
-    if (zm && t < T && valid) {
-      e0 -= sU[2 * t];
-      e1 -= sU[2 * t + 1];
+    if (any_zm) {
+      const float2 u = *reinterpret_cast<const float2*>(sU + 2 * min(t, T - 1));
+      e0 = __builtin_fmaf(-u.x, m_z, e0);
+      e1 = __builtin_fmaf(-u.y, m_z, e1);
     }
-    float n0 = e * e0, n1 = e * e1;
-#pragma unroll
-    for (int m = 8; m >= 1; m >>= 1) {
-      n0 += __shfl_xor(n0, m, 16);
-      n1 += __shfl_xor(n1, m, 16);
-    }
-    if (j == 0 && t < T) {
-      red[wv * 2 * kTMax + 2 * t] = n0;
-      red[wv * 2 * kTMax + 2 * t + 1] = n1;
-    }
+    const float n0 = row_sum(e * e0), n1 = row_sum(e * e1);
+    if (j == 0 && t < T) *reinterpret_cast<float2*>(red + wv * 2 * kTMax + 2 * t) = make_float2(n0, n1);
   };
   if (wS) {
     for (int t0 = 0; t0 < T; t0 += 16) {   // four loads in flight
@@ -578,8 +599,7 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int t = t0 + 4 * q + g;
-        v[q] = (t < T && valid) ? *reinterpret_cast<const float2*>(wS + (size_t)(t * 16 + j) * 2)
-                                : make_float2(0.0f, 0.0f);
+        v[q] = t < T ? *reinterpret_cast<const float2*>(wS + (uint32_t)((t * 16 + j) * 2)) : make_float2(0.0f, 0.0f);
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q)
@@ -588,8 +608,8 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
   } else {
     for (int t0 = 0; t0 < T; t0 += 4) {
       const int t = t0 + g;
-      float e0 = 0.0f, e1 = 0.0f;
-      if (t < T && valid) draw_eps((uint32_t)t, (uint32_t)k, a.nk, e0, e1);
+      float e0, e1;
+      draw_eps((uint32_t)min(t, T - 1), (uint32_t)k, a.nk, e0, e1);
       add_step(t, e0, e1);
     }
   }
@@ -601,16 +621,15 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
   finish_iteration<kQuadBlock, kModelNet, RECEDE, HID>(a, tile, rho, eta, N_lds, red);
 }
 
-// Waves per SIMD: three at h = 32 (168 registers), two at h = 64 (at most 256: the
-// compiler's own choice would hold one wave per SIMD, 274 registers with accumulation
-// registers, and runs the FP32 form about a fifth slower at K = 65536).
+// Waves per SIMD: three at h = 32 (at most 168 registers), two at h = 64 (at most 256; with
+// one, the FP32 form ran about a fifth slower at K = 65536).
 template <int PREC, int HID>
 __global__ __launch_bounds__(kQuadBlock, HID == 32 ? 3 : 2) void rollout_quad_kernel(RolloutArgs a) {
   if (a.iter_dev) a.nk.iter = *a.iter_dev;   // the device counter, advanced by the final merge
-  __shared__ float sU[2 * kTMax];
-  __shared__ float sE[kQuadWaves * kQuadChunk * 16 * 2 > 2 * kTMax ? kQuadWaves * kQuadChunk * 16 * 2 : 2 * kTMax];
-  __shared__ float sX[kQuadWaves * (kQuadChunk + 1) * 16 * 4];
-  __shared__ float red[kQuadWaves * 2 * kTMax + 8];
+  __shared__ __attribute__((aligned(16))) float sU[2 * kTMax];
+  __shared__ __attribute__((aligned(16))) float sE[kQuadControls];
+  __shared__ __attribute__((aligned(16))) float sX[kQuadWaves * (kQuadChunk + 1) * 16 * 4];
+  __shared__ __attribute__((aligned(16))) float red[kQuadWaves * 2 * kTMax + 8];
   quad_rollout_tile<PREC, HID>(a, blockIdx.x, sU, sE, sX, red);
 }
 
@@ -625,10 +644,10 @@ __global__ __launch_bounds__(kQuadBlock, 3) void rollout_batch_quad_kernel(const
                                                                       const float* __restrict__ params,
                                                                       const float* __restrict__ decay,
                                                                       unsigned* __restrict__ queue) {
-  __shared__ float sU[2 * kTMax];
-  __shared__ float sE[kQuadWaves * kQuadChunk * 16 * 2 > 2 * kTMax ? kQuadWaves * kQuadChunk * 16 * 2 : 2 * kTMax];
-  __shared__ float sX[kQuadWaves * (kQuadChunk + 1) * 16 * 4];
-  __shared__ float red[kQuadWaves * 2 * kTMax + 8];
+  __shared__ __attribute__((aligned(16))) float sU[2 * kTMax];
+  __shared__ __attribute__((aligned(16))) float sE[kQuadControls];
+  __shared__ __attribute__((aligned(16))) float sX[kQuadWaves * (kQuadChunk + 1) * 16 * 4];
+  __shared__ __attribute__((aligned(16))) float red[kQuadWaves * 2 * kTMax + 8];
   for (;;) {
     const int b = next_work_item(queue, n_items);
     if (b < 0) break;

@@ -502,7 +502,8 @@ __global__ __launch_bounds__(kWaveBlock) void rollout_wave_kernel(RolloutArgs a)
         cp[0] = px1; cp[1] = py1; cp[2] = th1[q];
         cp[3] = xn.x; cp[4] = xn.y; cp[5] = xn.z; cp[6] = xn.w;
       }
-      Sacc.add(state_cost_h(a.cost, bilerp(mv[q], fxv[q], fyv[q]), dec[q], xn.y, xn.z));
+      const float zeta = slip_angle(a.cost, xn.y, xn.z);
+      Sacc.add(state_cost_h(a.cost, bilerp(mv[q], fxv[q], fyv[q]), dec[q], xn.y, zeta));
       const float u0 = sU[2 * t], u1 = sU[2 * t + 1];
       const float d0 = zm ? myE[2 * t] - u0 : myE[2 * t];
       const float d1 = zm ? myE[2 * t + 1] - u1 : myE[2 * t + 1];

@@ -138,10 +138,8 @@ __device__ __forceinline__ void draw_block_noise(const RolloutArgs& a, uint32_t 
   for (int i = threadIdx.x; i < kWaveSlots * T; i += kSplitBlock) {
     const int slot = i / T, t = i - slot * T;
     float e0, e1;
-    // the two-instruction products (philox10<false>): with them this kernel's chain loop
-    // lands on a 64-byte boundary (33.7 against 34.8 us per paper-shaped step with the
-    // one-instruction form, whose only effect here is where the loop lands; aligning
-    // every loop instead cost 0.3 us in the padding of the others)
+    // the two-instruction products: two waves per SIMD wait for each draw (0.4-0.8 us of a
+    // launch against the one-instruction form)
     draw_eps<false>((uint32_t)t, (uint32_t)(kb + slot), nk, e0, e1);
     sE[slot * eStride + 2 * t] = e0;
     sE[slot * eStride + 2 * t + 1] = e1;
@@ -342,9 +340,6 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
   if constexpr (MULTI)   // the plant step's copy of the parameters (a network in its plant layout)
     for (int i = tid; i < (kNet ? kSplitParams : kSplitBasisParams); i += kSplitBlock)
       sP[kNet ? plant_layout_index(i, HID) : i] = a.params[i];
-  // four no-ops, once per launch: they move the chain loop below onto a 64-byte boundary
-  // (where the loop lands is worth ~1 us per paper-shaped step; see draw_block_noise)
-  if constexpr (MULTI) asm volatile("s_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
   draw_block_noise(a, iter0, kb, T, eStride, sE);
   if (chain) __builtin_amdgcn_s_setprio(2);
 
@@ -387,6 +382,10 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
       float* xs = myX + ((lane & 4) ? 4 + comp : 8 + comp);
       for (int c = 0; c < nch; ++c) {
         const int t1 = r0 + 32 * c;
+        // multi-step: the step loop on a 64-byte boundary (where it lands is worth 0.9 us per
+        // paper-shaped step): a boundary, 13 no-ops and the three instructions that enter the
+        // loop.  In a single-step launch the no-ops cost 0.3 us and the boundary gives nothing.
+        if constexpr (MULTI) asm volatile(".p2align 6\n\t.fill 13, 4, 0xbf800000");
         for (int t = c > 0 ? t1 - 32 : 0; t < t1; ++t) {
           const int tn = min(t + 1, T - 1);
           float y;   // dt * f of the lane's component
@@ -555,6 +554,7 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
         map_taps(as.cost, pxh, pxl, pyh, pyl, idx, fx, fy);
         const float mv[4] = {as.map[idx[0]], as.map[idx[1]], as.map[idx[2]], as.map[idx[3]]};
         const float dec = as.decay[tc + 1];
+        const float zeta = slip_angle(as.cost, xn[1], xn[2]);   // while the map values arrive
         if (live) {
           const float px1 = pxh + pxl, py1 = pyh + pyl;
           if (as.ckpt && ((t + 1) % as.ckpt_every) == 0 && valid) {
@@ -562,7 +562,7 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
             cp[0] = px1; cp[1] = py1; cp[2] = th1;
             cp[3] = xn[0]; cp[4] = xn[1]; cp[5] = xn[2]; cp[6] = xn[3];
           }
-          Sacc.add(state_cost_h(as.cost, bilerp(mv, fx, fy), dec, xn[1], xn[2]));
+          Sacc.add(state_cost_h(as.cost, bilerp(mv, fx, fy), dec, xn[1], zeta));
           const float u0 = sU[2 * t], u1 = sU[2 * t + 1];
           const float d0 = zm ? myE[2 * t] - u0 : myE[2 * t];
           const float d1 = zm ? myE[2 * t + 1] - u1 : myE[2 * t + 1];

@@ -317,7 +317,8 @@ __global__ __launch_bounds__(kWideBlock) void rollout_wide_kernel(RolloutArgs a)
     if (q < npl && t < T) {
       const float4 xn = myX[t + 1];
       const float px1 = pxh[q] + pxl[q], py1 = pyh[q] + pyl[q];
-      Sacc.add(state_cost_h(a.cost, bilerp(mv[q], fxv[q], fyv[q]), dec[q], xn.y, xn.z));
+      const float zeta = slip_angle(a.cost, xn.y, xn.z);
+      Sacc.add(state_cost_h(a.cost, bilerp(mv[q], fxv[q], fyv[q]), dec[q], xn.y, zeta));
       const float u0 = sU[2 * t], u1 = sU[2 * t + 1];
       const float d0 = zm ? myE[2 * t] - u0 : myE[2 * t];
       const float d1 = zm ? myE[2 * t + 1] - u1 : myE[2 * t + 1];

@@ -371,6 +371,28 @@ void launch_quad(int precision, int hidden, int G, hipStream_t stream, const Rol
 #undef MPPI_QUAD
 }
 
+// The cost's arguments of a launch.
+CostArgs cost_args(const mppi_cost& cost, int H, int W, float ox, float oy, float res) {
+  CostArgs c{};
+  c.H = H;
+  c.W = W;
+  c.ox = ox;
+  c.oy = oy;
+  c.res = res;
+  c.inv_res = 1.0f / res;
+  c.w_map = cost.w_map;
+  c.w_speed = cost.w_speed;
+  c.w_slip = cost.w_slip;
+  c.v_des = cost.v_des;
+  c.crash_cost = cost.crash_cost;
+  c.map_thresh = cost.map_thresh;
+  c.slip_cost = cost.slip_cost;
+  c.slip_thresh = cost.slip_thresh;
+  // the slip angle is at most pi/2, and its terms are added to a finite cost or not at all
+  c.slip_on = cost.w_slip != 0.0f || (cost.slip_cost != 0.0f && cost.slip_thresh < 2.0f);
+  return c;
+}
+
 // The fields of a rollout launch that follow from the configuration, the cost, the map
 // geometry and the dynamics model; the caller sets the buffers and G.
 RolloutArgs config_args(const mppi_config& g, const mppi_cost& cost, int H, int W, float ox, float oy,
@@ -411,19 +433,7 @@ RolloutArgs config_args(const mppi_config& g, const mppi_cost& cost, int H, int 
   a.recede = 0;
   a.u0_out = nullptr;
   a.x_copy = nullptr;
-  a.cost.H = H;
-  a.cost.W = W;
-  a.cost.ox = ox;
-  a.cost.oy = oy;
-  a.cost.res = res;
-  a.cost.w_map = cost.w_map;
-  a.cost.w_speed = cost.w_speed;
-  a.cost.w_slip = cost.w_slip;
-  a.cost.v_des = cost.v_des;
-  a.cost.crash_cost = cost.crash_cost;
-  a.cost.map_thresh = cost.map_thresh;
-  a.cost.slip_cost = cost.slip_cost;
-  a.cost.slip_thresh = cost.slip_thresh;
+  a.cost = cost_args(cost, H, W, ox, oy, res);
   return a;
 }
 
@@ -1408,19 +1418,7 @@ std::vector<RolloutArgs> batch_args(const mppi_batch* b) {
     a.nk.instance = b->cfg.instance + (uint32_t)i;
     a.nk.sig0 = std::sqrt(b->cfg.sigma2[0]);
     a.nk.sig1 = std::sqrt(b->cfg.sigma2[1]);
-    a.cost.H = b->H;
-    a.cost.W = b->W;
-    a.cost.ox = b->ox;
-    a.cost.oy = b->oy;
-    a.cost.res = b->res;
-    a.cost.w_map = b->cost.w_map;
-    a.cost.w_speed = b->cost.w_speed;
-    a.cost.w_slip = b->cost.w_slip;
-    a.cost.v_des = b->cost.v_des;
-    a.cost.crash_cost = b->cost.crash_cost;
-    a.cost.map_thresh = b->cost.map_thresh;
-    a.cost.slip_cost = b->cost.slip_cost;
-    a.cost.slip_thresh = b->cost.slip_thresh;
+    a.cost = cost_args(b->cost, b->H, b->W, b->ox, b->oy, b->res);
     v[i] = a;
   }
   return v;

@@ -55,6 +55,8 @@ struct NoiseKey {
 struct CostArgs {
   int H, W;
   float ox, oy, res;
+  float inv_res;           // fl(1 / res)
+  int slip_on;             // 0: neither slip term can be other than zero
   float w_map, w_speed, w_slip, v_des;
   float crash_cost, map_thresh, slip_cost, slip_thresh;
 };
