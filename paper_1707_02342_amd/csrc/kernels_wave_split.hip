@@ -32,24 +32,28 @@
 // compensation terms and of the kinematic scans.
 //
 // Multi-step receding launch (the MULTI instances with n_steps > 1, launched
-// cooperatively so that every block is resident): G rollout blocks and one merger block
-// per merge group.  A rollout block loops over the steps, keeping the chain's network
-// constants in registers and the model's parameters (for the plant step) in LDS.  At the
-// end of step s it writes its row through, waits for those stores, and writes the step
-// into its arrival word; it draws step s + 1's noise (which does not depend on U) and
-// waits until its copy of the group words shows step s for every group; it then merges
-// the group rows and runs the final stage itself -- normalisation, smoothing, update,
-// shift, plant step -- so that step s + 1 starts from U and the plant state in its own
-// LDS with no further memory round trip.  Every block computes the same values in the
-// same order; block 0 alone writes U, the plant state, the statistics and the histories.
-// A merger block waits until its group's arrival words show step s, merges the group's
-// rows into the group row and writes the step into every copy of its group word.  Every
-// signal is a word written through after the data it announces has reached the device's
-// point of coherence, and read with device-coherent loads; every word holds a step
-// number that only grows, so none is reset.  (Counting arrivals with atomic adds and
-// polling the count took ~4.5 us to be seen by the poller, against ~0.6 us for a written
-// word.)  Every wait is bounded: a block that gives up sets the status and leaves.  The
-// results equal those of one launch per step bit for bit.
+// cooperatively so that every block is resident): G rollout blocks and up to 16 merger
+// blocks.  A rollout block loops over the steps, keeping the chain's network constants in
+// registers and the model's parameters (for the plant step) in LDS.  At the end of step s
+// each thread writes its column of the block's partial row through as a word that also
+// holds the step's number (see kMergeCopies); the block draws step s + 1's noise (which
+// does not depend on U) and then polls the merged row, each thread its own column, and
+// runs the final stage itself -- normalisation, smoothing, update, shift, plant step -- so
+// that step s + 1 starts from U and the plant state in its own LDS with no further memory
+// round trip.  Every block computes the same values in the same order; block 0 alone
+// writes U, the plant state, the statistics and the histories.  A merger block owns a
+// sixteenth of the columns: it reads these of all G rows (one 128-byte line each), merges
+// them in the two levels of finish_iteration in the same order, and writes its part of the
+// merged row.  A word is never overwritten while another block may still need it: a
+// rollout block writes step s + 1's row after it has read step s's merged row, which
+// every merger wrote after reading all of step s's rows.  Every wait is bounded: a block
+// that gives up sets the status and leaves.  The results equal those of one launch per
+// step bit for bit.
+//
+// What bounds a step (paper-shaped): the latency of the chain (~20 us), then of the
+// exchange.  Replaced: a merger per group of 16 rows (each row written, waited for and
+// flagged, the group row likewise, and all 15 group rows merged again by every rollout
+// block): 32.0 -> 29.9 us per paper-shaped step (basis-function model 28.9 -> 26.2).
 #include "wave_common.hip.h"
 
 namespace mppi {
@@ -146,24 +150,29 @@ __device__ __forceinline__ void draw_block_noise(const RolloutArgs& a, uint32_t 
   }
 }
 
-// A word that blocks of a multi-step launch poll, written through to the device's point
-// of coherence.
-__device__ __forceinline__ void store_word(unsigned* p, unsigned v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// A word of a multi-step launch: a value and the number of its step, written through to
+// the device's point of coherence / read from there.
+__device__ __forceinline__ void store_word(uint64_t* p, float v, unsigned step) {
+  __hip_atomic_store(p, ((uint64_t)step << 32) | as_u(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t load_word(const uint64_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool word_ready(uint64_t w, unsigned step) { return (unsigned)(w >> 32) == step; }
+__device__ __forceinline__ float word_value(uint64_t w) { return as_f((uint32_t)w); }
+
+// The smallest value of each 16-lane row, in every lane.
+__device__ __forceinline__ float row16_min(float v) {
+  v = fminf(v, dpp_f<kRowRor + 8>(v));
+  v = fminf(v, dpp_f<kRowRor + 4>(v));
+  v = fminf(v, dpp_f<kQuadXor2>(v));
+  return fminf(v, dpp_f<kQuadXor1>(v));
 }
 
-// Bounded wait of wave 0 (all 64 lanes call it) until each of the n words w[0..n)
-// (n <= 64), written by other blocks with store_word, holds `target` or a later step
-// (wrapping comparison): at most `limit` polls; false when they ran out.  The same in
-// every lane.
-__device__ __forceinline__ bool wait_words(const unsigned* w, int n, unsigned target, unsigned limit) {
-  const int lane = threadIdx.x & 63;
-  for (unsigned i = 0; i < limit; ++i) {
-    const unsigned v = lane < n ? __hip_atomic_load(w + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : target;
-    if (__all((int)(v - target) >= 0)) return true;
-    __builtin_amdgcn_s_sleep(1);
-  }
-  return false;
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 }  // namespace
@@ -186,49 +195,125 @@ constexpr int kStatusTimeout = 6;   // a multi-step launch gave up waiting for a
 // 1 << 20: each poll waits for its load, so of the order of a second).
 __device__ __forceinline__ unsigned spin_limit(const RolloutArgs& a) { return a.spin_limit ? a.spin_limit : (1u << 20); }
 
-// Multi-step launch, merger block of group grp = blockIdx.x - G: at every step, waits
-// (bounded) until the arrival word of each of the group's n_in rollout blocks shows the
-// step, merges their rows into this step's group row (two buffers, alternating by step: a
-// slow block may still read step s's group rows while step s + 1's are written), and
-// writes the step into every copy of the group's signal word.  Inlined into the kernel,
-// since it reads the arguments with reload_args().
-__device__ __forceinline__ void merge_group_rows(int n_steps, float* lds) {
-  __shared__ float s_small[2 * kMergeChunk];
+// Multi-step launch, merger block m = blockIdx.x - G (8 waves, G <= 256 rows): at every step
+// reads its columns of every rollout block's row as they arrive, merges them as the
+// blocks of one launch are merged -- per group of 16 rows relative to the group's minimum,
+// then the group rows, every sum in row order, so that the merged row has the same bits --
+// and writes its part of the merged row in kMergeCopies copies.  lds: (cw + 3) G +
+// 18 * 32 floats.  Inlined into the kernel, since it reads the arguments with
+// reload_args().
+__device__ __forceinline__ void merge_columns_block(int n_steps, float* lds) {
+  constexpr int kPass = 8;   // rows per thread: 256 rows of at most 16 lanes over 512 threads
   __shared__ unsigned s_stop;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (tid == 0) s_stop = 0u;
+  __syncthreads();
   for (int step = 0; step < n_steps; ++step) {
     const RolloutArgs& as = reload_args();
-    const int T2 = 2 * as.T, stride = 2 + T2;
-    const int gsz = merge_group_size(as.G);
-    const int ngrp = (as.G + gsz - 1) / gsz;
-    const int grp = (int)blockIdx.x - as.G;
-    const int n_in = min(gsz, as.G - grp * gsz);
+    const int G = as.G, T2 = 2 * as.T, M = merge_blocks(as.T), cw = merge_columns(as.T), LW = merge_line_words(cw);
+    const int m = (int)blockIdx.x - G;
+    const int words = 2 + min(cw, T2 - m * cw);   // of the line that carry a value
     const unsigned target = as.step_base + (unsigned)step + 1u;
-    if (tid < 64) {
-      const bool ok = wait_words(as.sync + kArriveOffset + grp * gsz, n_in, target, spin_limit(as));
-      if (tid == 0) {
-        if (!ok) __hip_atomic_store(as.status, kStatusTimeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_stop = ok ? 0u : 1u;
+    const unsigned limit = spin_limit(as);
+    const int vs = cw + 1;                        // columns of a row in LDS: eta, then the cw columns
+    float* sRho = lds;                            // [G]
+    float* sV = sRho + G;                         // [G][vs]
+    float* sS = sV + G * vs;                      // [256] the rows' scales
+    float* sN = sS + 256;                         // [16][18] per group: rho_g, then eta_g and the columns
+    // ---- every row's line: LW / 2 lanes per row, two words a lane -------------------------
+    const int sh = LW == 16 ? 3 : 4, l2 = 2 * (tid & ((1 << sh) - 1)), r0 = tid >> sh, dr = kSplitBlock >> sh;
+    const uint64_t* src = as.sync + ((size_t)r0 * M + m) * LW + l2;
+    const size_t ds = (size_t)dr * M * LW;
+    const bool two = l2 + 1 < words;
+    uint64_t w0[kPass], w1[kPass];
+    bool ok = false;
+    // until the wave's first rows are there, one word each; then everything at once
+    for (unsigned i = 0; i < limit && !ok; ++i) {
+      const bool act = r0 < G && l2 == 0;
+      const uint64_t w = act ? load_word(src) : 0;
+      ok = __all(!act || word_ready(w, target));
+      if (!ok) __builtin_amdgcn_s_sleep(1);
+    }
+    if (ok) {
+      ok = false;
+      for (unsigned i = 0; i < limit && !ok; ++i) {
+#pragma unroll
+        for (int p = 0; p < kPass; ++p) {
+          const bool act = r0 + p * dr < G && l2 < words;
+          w0[p] = act ? load_word(src + p * ds) : 0;
+          w1[p] = act && two ? load_word(src + p * ds + 1) : 0;
+        }
+        bool all = true;
+#pragma unroll
+        for (int p = 0; p < kPass; ++p) {
+          const bool act = r0 + p * dr < G && l2 < words;
+          all = all && (!act || (word_ready(w0[p], target) && (!two || word_ready(w1[p], target))));
+        }
+        ok = __all(all);
+      }
+    }
+    if (!ok && lane == 0) {
+      s_stop = 1u;
+      __hip_atomic_store(as.status, kStatusTimeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (ok) {
+#pragma unroll
+      for (int p = 0; p < kPass; ++p) {
+        const int row = r0 + p * dr;
+        if (row < G && l2 < words) {
+          if (l2 == 0) sRho[row] = word_value(w0[p]);
+          else sV[row * vs + l2 - 1] = word_value(w0[p]);
+          if (two) sV[row * vs + l2] = word_value(w1[p]);
+        }
       }
     }
     __syncthreads();
     if (s_stop) return;
-    float rho, eta;
-    merge_rows<kSplitBlock>(as.part + (size_t)grp * gsz * stride, n_in, stride, T2, as.inv_lambda, lds, s_small,
-                            rho, eta);
-    __syncthreads();
-    if (tid < 64) {
-      // the group row is written through and its stores complete before the signal words
-      float* dst = as.part2 + ((size_t)(step & 1) * ngrp + grp) * stride;
-      if (tid == 0) {
-        store_through(dst, rho);
-        store_through(dst + 1, eta);
+    const int ngrp = (G + 15) >> 4;               // merge_group_size(G) is 16 up to 256 rows
+    // ---- group level: a 16-lane row per group, lane i its row i, then its columns i - 1, i + 15
+    if (tid < 256) {
+      const int g = tid >> 4, i = tid & 15;
+      const int n_in = min(16, G - 16 * g);
+      const bool in = i < n_in;
+      const float rr = in ? sRho[16 * g + i] : kInf;
+      const float ee = in ? sV[(16 * g + i) * vs] : 0.0f;
+      const float rho = row16_min(rr);
+      sS[tid] = ee > 0.0f ? expf(-(rr - rho) * as.inv_lambda) : 0.0f;
+      wave_lds_fence();
+      float acc0 = 0.0f, acc1 = 0.0f;
+      const float* v = sV + 16 * g * vs;
+      const bool c0 = i < words - 1, c1 = i + 16 < words - 1;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const float s = sS[16 * g + q];
+        acc0 = __builtin_fmaf(s, (q < n_in && c0) ? v[q * vs + i] : 0.0f, acc0);
+        if (LW > 16) acc1 = __builtin_fmaf(s, (q < n_in && c1) ? v[q * vs + i + 16] : 0.0f, acc1);
       }
-      for (int o = tid; o < T2; o += 64) store_through(dst + 2 + o, lds[o]);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      if (tid < kSignalCopies) store_word(as.sync + tid * kSignalSpacing + grp, target);
+      float* n = sN + g * 18;
+      if (i == 0) n[0] = rho;
+      n[1 + i] = acc0;
+      if (i == 0) n[17] = acc1;                   // column 16, there when cw = 16
     }
     __syncthreads();
+    // ---- the group rows, in one wave: lane i of each row its group i, then word l of the line
+    if (tid < 64) {
+      const int i = lane & 15;
+      const float rg = i < ngrp ? sN[i * 18] : kInf;
+      const float eg = i < ngrp ? sN[i * 18 + 1] : 0.0f;
+      const float rho = row16_min(rg);
+      const float sg = eg > 0.0f ? expf(-(rg - rho) * as.inv_lambda) : 0.0f;
+      const int l = lane & (LW - 1);              // word l: rho, eta, columns
+      float acc = 0.0f;
+      const float* n = sN + max(min(l, 17), 1);
+#pragma unroll
+      for (int g = 0; g < 16; ++g)
+        acc = __builtin_fmaf(lane_value(sg, g), g < ngrp ? n[g * 18] : 0.0f, acc);
+      const float out = l == 0 ? rho : acc;
+      if (l < words) {
+        uint64_t* dst = as.sync + ((size_t)G * M + m) * LW + l;
+        for (int c = lane >> (sh + 1); c < kMergeCopies; c += 64 >> (sh + 1)) store_word(dst + (size_t)c * M * LW, out, target);
+      }
+    }
   }
 }
 
@@ -239,7 +324,6 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
   extern __shared__ float smem[];
   __shared__ unsigned s_abort;
   __shared__ float s_xn[kStateDim];                  // multi-step: the next step's plant state
-  __shared__ float s_small[2 * kMergeChunk];         // multi-step: the merge's row scales
   const int T = a.T;
   const int T4 = (T + 4) & ~3;
   const int eStride = (2 * T + 3) & ~3;
@@ -259,8 +343,8 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
   float* N_lds = kNet ? sV : sB;
   float* lds = sX;
   if constexpr (MULTI) {
-    if ((int)blockIdx.x >= a.G) {   // a merger block (blocks G .. G + ngrp - 1)
-      merge_group_rows(n_steps, sX);
+    if ((int)blockIdx.x >= a.G) {   // a merger block
+      merge_columns_block(n_steps, smem);
       return;
     }
   }
@@ -600,7 +684,7 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
       wgt[q] = rel_weight(Sk[q], rho, as.inv_lambda);
       eta += wgt[q];
     }
-    for (int o = tid; o < 2 * T; o += kSplitBlock) {
+    const auto column = [&](int o) {   // N_g of column o
       const float u = sU[o];
       float n = 0.0f;
 #pragma unroll
@@ -608,49 +692,58 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
         const float e = sE[q * eStride + o];
         n = __builtin_fmaf(wgt[q], (kb + q >= as.K_imp) ? e - u : e, n);
       }
-      N_lds[o] = n;
-    }
+      return n;
+    };
     if constexpr (MULTI) {
-      // ---- multi-step launch: the row goes to the group's merger block; this block then
-      // merges the group rows and runs the final stage itself ---------------------------
-      const int T2 = 2 * T, stride = 2 + T2;
-      const int gsz = merge_group_size(as.G);
-      const int ngrp = (as.G + gsz - 1) / gsz;
+      // ---- multi-step launch: the row goes to the merger blocks, the merged row comes back
+      // and this block runs the final stage itself (2T <= 256: a column per thread) -------
+      const int T2 = 2 * T, M = merge_blocks(T), cw = merge_columns(T), LW = merge_line_words(cw);
       const unsigned target = as.step_base + (unsigned)step + 1u;
+      uint64_t* const row = as.sync + (size_t)blockIdx.x * M * LW;
+      const int m = tid / cw;
+      const int word = m * LW + 2 + (tid - m * cw);
+      if (tid < T2) {
+        store_word(row + word, column(tid), target);
+      } else if (tid >= 256 && tid < 256 + 2 * M) {
+        const int h = tid - 256;
+        store_word(row + (h >> 1) * LW + (h & 1), (h & 1) ? eta : rho, target);
+      }
       FinalStage<kSplitBlock, MODEL, true, HID, kNet> fs;
       fs.prefetch_local(as, sU, x0v);
-      __syncthreads();   // the block's N row is complete
-      if (tid < 64) {
-        // the row is written through and its stores complete before the arrival word
-        float* dst = as.part + (size_t)blockIdx.x * stride;
-        if (tid == 0) {
-          store_through(dst, rho);
-          store_through(dst + 1, eta);
-        }
-        for (int o = tid; o < T2; o += 64) store_through(dst + 2 + o, N_lds[o]);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (tid == 0) store_word(as.sync + kArriveOffset + blockIdx.x, target);
-      }
-      // the next step's noise does not depend on its U: drawn while the merges complete
+      __syncthreads();   // the block's noise and costs are no longer read
+      // the next step's noise does not depend on its U: drawn while the merge completes
       if (step + 1 < n_steps) draw_block_noise(as, iter + 1u, kb, T, eStride, sE);
-      if (tid < 64) {
-        const bool ok = wait_words(as.sync + (blockIdx.x % kSignalCopies) * kSignalSpacing, ngrp, target,
-                                   spin_limit(as));
-        if (tid == 0 && !ok) {
+      float rho_m = 0.0f, eta_m = 0.0f;
+      if (tid < 256) {   // whole waves: every thread of a column polls its own word and its line's head
+        const uint64_t* src = as.sync + (size_t)(as.G + (int)(blockIdx.x % kMergeCopies)) * M * LW;
+        const bool act = tid < T2;
+        const unsigned limit = spin_limit(as);
+        uint64_t w = 0, h0 = 0, h1 = 0;
+        bool ok = false;
+        for (unsigned i = 0; i < limit && !ok; ++i) {
+          if (act) {
+            w = load_word(src + word);
+            h0 = load_word(src + m * LW);
+            h1 = load_word(src + m * LW + 1);
+          }
+          ok = __all(!act || (word_ready(w, target) && word_ready(h0, target) && word_ready(h1, target)));
+        }
+        if (act) lds[tid] = word_value(w);
+        rho_m = word_value(h0);
+        eta_m = word_value(h1);
+        if (!ok && lane == 0) {
           s_abort = 1u;
           __hip_atomic_store(as.status, kStatusTimeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
       }
       __syncthreads();
       if (s_abort) break;
-      float rho_m, eta_m;
-      merge_rows<kSplitBlock>(as.part2 + (size_t)(step & 1) * ngrp * stride, ngrp, stride, T2, as.inv_lambda, lds,
-                              s_small, rho_m, eta_m);
       const bool fin = (rho_m < kInf) && (eta_m > 0.0f);
       fs.apply(as, lds, fin, fin ? 1.0f / eta_m : 0.0f, sP, rho_m, fin ? eta_m : 0.0f, iter, u0_out, x_copy,
                blockIdx.x == 0, sU, s_xn);
       __syncthreads();   // the next step's U (sU) and plant state (s_xn)
     } else {
+      for (int o = tid; o < 2 * T; o += kSplitBlock) N_lds[o] = column(o);
       const StepTarget target{iter, u0_out, x_copy};
       finish_iteration<kSplitBlock, MODEL, true, HID>(as, blockIdx.x, rho, eta, N_lds, lds, as.params, &target);
     }

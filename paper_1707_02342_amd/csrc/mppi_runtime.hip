@@ -108,14 +108,13 @@ struct mppi_ctx {
   float* d_gout = nullptr;    // reduced gradient [1412 + 2T]
   float* d_gred = nullptr;    // chunk sums of the gradient partials [16][1412 + 2T]
   unsigned* d_iter = nullptr; // the iteration counter (Philox counter word 3), advanced on the device
-  unsigned* d_sync = nullptr; // signal words of multi-step receding launches ([kSyncWords(part_cap)])
+  uint64_t* d_sync = nullptr; // exchange words of multi-step receding launches ([merge_words(G, T)]), or null
   unsigned step_count = 0;    // steps of the multi-step launches enqueued so far (their signal base)
   int ckpt_cap = 0;           // n_ckpt the checkpoint buffer holds
   bool objective_ready = false;
   int obj_ckpt_every = 0;
   uint32_t obj_iter = 0;
   int part_cap = 0;          // partial rows allocated
-  int ngrp_cap = 0;          // group rows allocated (arrival counters: ngrp_cap + 1)
   uint32_t iter = 0;
   int schedule = MPPI_SCHED_LANE;
   float sig[2] = {0, 0};
@@ -546,16 +545,21 @@ mppi_status enqueue_iteration(mppi_ctx* c, const float* x0_host, const float* x0
   return MPPI_OK;
 }
 
-// Whether n receding steps can run as one multi-step launch of the split wave kernel:
-// the wave schedule's split form (T <= 128) with its rollout blocks and one merger block
-// per merge group fitting one block per compute unit (K <= 1920 on 256 CUs), Algorithm
-// 2's weights, and a device that launches cooperatively (every block resident at once).
+// Whether the split wave kernel's multi-step launch can hold this context's problem: T <=
+// 128 (a column of the merged row per thread) and one block per compute unit for its
+// rollout blocks and one merger block per merge group (K <= 1920 on 256 CUs; the mergers
+// number at most 16, and at most 256 rows are merged in groups of 16).
+bool multi_step_fits(const mppi_ctx* c) {
+  const int T = c->cfg.T, G = blocks_for(c, MPPI_SCHED_WAVE);
+  return c->cfg.weighting == MPPI_WEIGHTS_IT && T <= kWaveSplitMaxT && G <= 256 &&
+         G + std::max(merge_groups(G), merge_blocks(T)) <= device_cus();
+}
+
+// Whether n receding steps can run as one multi-step launch of the split wave kernel: the
+// wave schedule, a problem that fits, and a device that launches cooperatively (every block
+// resident at once).
 bool multi_step_ok(const mppi_ctx* c) {
-  if (c->schedule != MPPI_SCHED_WAVE || c->cfg.weighting != MPPI_WEIGHTS_IT || c->cfg.T > kWaveSplitMaxT) return false;
-  // the rollout blocks and one merger block per merge group, one block per compute unit;
-  // a group's arrival words and the group words are each polled by one wave's lanes
-  const int G = blocks_for(c, MPPI_SCHED_WAVE);
-  if (G + merge_groups(G) > device_cus() || merge_group_size(G) > 64 || merge_groups(G) > 64) return false;
+  if (c->schedule != MPPI_SCHED_WAVE || !c->d_sync) return false;
   int coop = 0;
   if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, c->device) != hipSuccess) return false;
   return coop != 0;
@@ -579,8 +583,6 @@ mppi_status enqueue_receding_steps(mppi_ctx* c, float* x_dev, int n, float* u_hi
   }
   const int G = blocks_for(c, MPPI_SCHED_WAVE);
   if (G > c->part_cap) return fail(c, MPPI_E_INVAL, "internal: %d partial blocks > capacity %d", G, c->part_cap);
-  const int ngrp = merge_groups(G);
-  if (ngrp > c->ngrp_cap) return fail(c, MPPI_E_INVAL, "internal: %d merge groups > capacity %d", ngrp, c->ngrp_cap);
   c->objective_ready = false;
   RolloutArgs a = rollout_args(c, nullptr, x_dev);
   a.G = G;
@@ -603,7 +605,7 @@ mppi_status enqueue_receding_steps(mppi_ctx* c, float* x_dev, int n, float* u_hi
   const void* fn = c->model == kModelBasis
                        ? reinterpret_cast<const void*>(&rollout_wave_split_kernel<kModelBasis, true>)
                        : reinterpret_cast<const void*>(&rollout_wave_split_kernel<kModelNet, true>);
-  HIP_TRY(c, hipLaunchCooperativeKernel(fn, dim3(G + ngrp), dim3(kWaveSplitBlockThreads), args,
+  HIP_TRY(c, hipLaunchCooperativeKernel(fn, dim3(G + merge_blocks(c->cfg.T)), dim3(kWaveSplitBlockThreads), args,
                                         (unsigned)wave_split_smem_bytes(c->cfg.T, c->model), c->stream));
   if (c->timing) {
     HIP_TRY(c, hipEventRecord(pt.e1, c->stream));
@@ -622,7 +624,7 @@ mppi_status read_status(mppi_ctx* c) {
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   if (st == MPPI_E_NONFINITE) return fail(c, MPPI_E_NONFINITE, "no sample had a finite cost; U unchanged");
   if (st == kStatusTimeoutHost) {
-    // the launch left mid-step; the signal words it wrote hold steps below every later
+    // the launch left mid-step; the words it wrote hold step numbers below every later
     // launch's, so only the status is cleared for the next launch
     (void)hipMemsetAsync(c->d_status, 0, sizeof(int), c->stream);
     (void)hipStreamSynchronize(c->stream);
@@ -744,9 +746,7 @@ mppi_status mppi_create(const mppi_config* cfg, const mppi_cost* cost, int devic
                                    merge_groups(blocks_for(c, MPPI_SCHED_WAVE)),
                                    merge_groups(blocks_for(c, MPPI_SCHED_WIDE)),
                                    merge_groups(blocks_for(c, MPPI_SCHED_QUAD))});
-    // two sets of group rows: a multi-step receding launch alternates them by step
-    HIP_TRY(c, hipMalloc(&c->d_part2, sizeof(float) * (size_t)2 * ngrp_cap * (2 + 2 * T)));
-    c->ngrp_cap = ngrp_cap;
+    HIP_TRY(c, hipMalloc(&c->d_part2, sizeof(float) * (size_t)ngrp_cap * (2 + 2 * T)));
     HIP_TRY(c, hipMalloc(&c->d_cnt, sizeof(unsigned) * (ngrp_cap + 1)));
     HIP_TRY(c, hipMemsetAsync(c->d_cnt, 0, sizeof(unsigned) * (ngrp_cap + 1), c->stream));
     HIP_TRY(c, hipMalloc(&c->d_stats, sizeof(float) * (2 + 2 * T)));
@@ -755,8 +755,11 @@ mppi_status mppi_create(const mppi_config* cfg, const mppi_cost* cost, int devic
     HIP_TRY(c, hipMemsetAsync(c->d_status, 0, sizeof(int), c->stream));
     HIP_TRY(c, hipMalloc(&c->d_iter, sizeof(unsigned)));
     HIP_TRY(c, hipMemsetAsync(c->d_iter, 0, sizeof(unsigned), c->stream));
-    HIP_TRY(c, hipMalloc(&c->d_sync, sizeof(unsigned) * kSyncWords(c->part_cap)));
-    HIP_TRY(c, hipMemsetAsync(c->d_sync, 0, sizeof(unsigned) * kSyncWords(c->part_cap), c->stream));
+    if (multi_step_fits(c)) {
+      const size_t words = merge_words(blocks_for(c, MPPI_SCHED_WAVE), T);
+      HIP_TRY(c, hipMalloc(&c->d_sync, sizeof(uint64_t) * words));
+      HIP_TRY(c, hipMemsetAsync(c->d_sync, 0, sizeof(uint64_t) * words, c->stream));
+    }
     HIP_TRY(c, hipMalloc(&c->d_x, sizeof(float) * kStateDim));
     HIP_TRY(c, hipMalloc(&c->d_u0, sizeof(float) * 2));
     std::vector<float> decay(T + 1);

@@ -9,19 +9,25 @@ namespace mppi {
 
 constexpr int kStateDim = 7;
 
-// Multi-step receding launch: the words its blocks signal each other through (a device
-// buffer of kSyncWords(G) words per context, zero when the context is created).  Every
-// word holds a step number, step_base + s + 1 for step s of a launch, which grows over
-// the context's multi-step launches, so no word is ever reset.
-//   copy c < kSignalCopies of group word g: the last step whose group row g is out (the
-//     copies kSignalSpacing words, 4 KiB, apart; rollout block b polls copy
-//     b mod kSignalCopies, so that not every block polls the same memory);
-//   arrival word b (at kArriveOffset + b, b < G): the last step whose row of rollout
-//     block b is out.
-constexpr int kSignalCopies = 16;
-constexpr int kSignalSpacing = 1024;
-constexpr int kArriveOffset = kSignalCopies * kSignalSpacing;
-constexpr inline int kSyncWords(int G) { return kArriveOffset + G; }
+// Multi-step receding launch: how its blocks exchange their rows.  Every value travels in an
+// 8-byte word with the number of its step (step_base + s + 1 for step s of a launch), which
+// one store writes and one load reads as a whole, so a reader that finds its step's number
+// holds its step's value: no flag, no wait for the writer's stores and no second round
+// trip.  The words of a context are zero when it is created and step numbers start at 1
+// and grow over its launches, so none is ever reset.
+//   M merger blocks share the 2T columns, cw = merge_columns(T) of them each (the last
+//   fewer); a line of merge_line_words(cw) words holds {rho, eta, cw columns}:
+//   rows    [G][M] lines: rollout block b's partial row, split over the mergers;
+//   merged  [kMergeCopies][M] lines: merger m's columns of the merged row (rollout block b
+//           reads copy b mod kMergeCopies, so that not every block polls the same memory).
+constexpr int kMergeCopies = 16;
+constexpr int kMaxMergers = 16;
+__host__ __device__ constexpr inline int merge_columns(int T) { return (2 * T + kMaxMergers - 1) / kMaxMergers; }
+__host__ __device__ constexpr inline int merge_blocks(int T) { return (2 * T + merge_columns(T) - 1) / merge_columns(T); }
+__host__ __device__ constexpr inline int merge_line_words(int cw) { return cw + 2 <= 16 ? 16 : 32; }   // whole 128-byte lines
+constexpr inline size_t merge_words(int G, int T) {
+  return (size_t)(G + kMergeCopies) * merge_blocks(T) * merge_line_words(merge_columns(T));
+}
 constexpr int kCtrlDim = 2;
 constexpr int kNetIn = 6;
 constexpr int kNetOut = 4;
@@ -75,7 +81,7 @@ struct RolloutArgs {
   const float* x0_dev;     // nullable: read x0 from here instead of x0[]
   float* S;                // [K] trajectory costs
   float* part;             // [G][2 + 2T] per-block (rho_g, eta_g, N_g[T][2])
-  float* part2;            // [2][merge_groups(G)][2 + 2T] per-group merges (the second set: multi-step)
+  float* part2;            // [merge_groups(G)][2 + 2T] per-group merges
   unsigned* cnt;           // [merge_groups(G) + 1] arrival counters, zero between launches
   const float* sg;         // [T][sg_window] smoothing rows (null when window == 1)
   float* Uout;             // [T][2], updated in place by the last block
@@ -117,13 +123,13 @@ struct RolloutArgs {
   // to a later merge of every shard's row (merge_update_kernel).
   float* row_out;
   // Multi-step receding launch (the split wave kernel, launched cooperatively with G
-  // rollout blocks and merge_groups(G) merger blocks): n_steps receding steps in one launch
-  // (0 or 1: one step), step s signalled as step_base + s + 1 in the words of sync
-  // ([kSyncWords(G)], see kSignalCopies); u0_out and x_copy then point to [n_steps][2]
+  // rollout blocks and merge_blocks(T) merger blocks): n_steps receding steps in one launch
+  // (0 or 1: one step), step s numbered step_base + s + 1 in the words of sync
+  // ([merge_words(G, T)], see kMergeCopies); u0_out and x_copy then point to [n_steps][2]
   // and [n_steps][7] histories (step s writes entry s).
   int n_steps;
-  unsigned* sync;
   unsigned step_base;
+  uint64_t* sync;
   unsigned spin_limit;   // polls of one wait before the launch gives up (0: 1 << 20)
 };
 

@@ -140,6 +140,23 @@ def test_multi_step_other_forms(env, case):
     assert np.isfinite(a[0]).all()
 
 
+@pytest.mark.parametrize("K,T", [(1, 1), (9, 2), (17, 8), (128, 9), (129, 112), (136, 113), (1920, 128), (1913, 33)])
+def test_multi_step_exchange_edges(env, K, T):
+    """Rows and columns where the exchange between rollout and merger blocks changes shape: one
+    row, one and several groups of 16 rows, a partial last group, one column per merger, a
+    last merger with fewer columns, and lines of 16 and of 32 words (T up to 112 and
+    beyond): equal to single steps bit for bit."""
+    M, torch = env
+    prob = synth.with_(synth.c1_problem(seed=K + T), K=K, T=T, lam=5.0)
+    U0 = synth.random_controls(T, K, scale=0.2)
+    _say(f"case: K={K} T={T}")
+    a = _run(M, torch, prob, synth.ring_map(), synth.mlp_params(32, 1), synth.C1_X0, U0, 4, True)
+    b = _run(M, torch, prob, synth.ring_map(), synth.mlp_params(32, 1), synth.C1_X0, U0, 4, False)
+    for x, y in zip(a[:4], b[:4]):
+        np.testing.assert_array_equal(x, y)
+    assert np.isfinite(a[0]).all()
+
+
 def test_run_receding_device_rejects_bad_arguments(env):
     M, torch = env
     prob = synth.c1_problem()
