@@ -343,13 +343,25 @@ __device__ __forceinline__ int clamp_index(int v, int hi) {
   return r;
 }
 
-// map_taps with the corners as byte offsets from the map's start: a map holds at most 2^30
-// cells, so they fit 32 bits and the loads need no 64-bit address arithmetic.
-__device__ __forceinline__ void map_taps_bytes(const CostArgs& c, float pxh, float pxl, float pyh, float pyl,
-                                               uint32_t off[4], float& fx, float& fy) {
+// Grid coordinate (p - o) / res of a 64-bit position, clamped to [-1, n] like grid_coord:
+// cell and fraction (which may round to 1).  A coordinate in 64 bits is eight instructions
+// of the rate of one FP32 instruction that does not dual-issue.
+__device__ __forceinline__ void grid_coord64(double p, double o, double inv_res, int n, int& i0, float& f) {
+  double q = (p - o) * inv_res;
+  q = __builtin_fmin(__builtin_fmax(q, -1.0), (double)n);   // a NaN becomes -1
+  const double fl = __builtin_floor(q);
+  i0 = (int)fl;
+  f = (float)(q - fl);
+}
+
+// The corners of a 64-bit position's cell as byte offsets from the map's start (a map holds
+// at most 2^30 cells, so they fit 32 bits and the loads need no 64-bit address
+// arithmetic), clamped to the edge, and the fractions.
+__device__ __forceinline__ void map_taps64(const CostArgs& c, double px, double py, uint32_t off[4], float& fx,
+                                           float& fy) {
   int j0, i0;
-  grid_coord(pxh, pxl, c.ox, c.res, c.inv_res, c.W, j0, fx);
-  grid_coord(pyh, pyl, c.oy, c.res, c.inv_res, c.H, i0, fy);
+  grid_coord64(px, c.ox64, c.inv_res64, c.W, j0, fx);
+  grid_coord64(py, c.oy64, c.inv_res64, c.H, i0, fy);
   const uint32_t ja = (uint32_t)clamp_index(j0, c.W - 1), jb = (uint32_t)clamp_index(j0 + 1, c.W - 1);
   const uint32_t ia = (uint32_t)clamp_index(i0, c.H - 1), ib = (uint32_t)clamp_index(i0 + 1, c.H - 1);
   const uint32_t W4 = (uint32_t)c.W * 4u;

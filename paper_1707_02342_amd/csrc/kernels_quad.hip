@@ -14,7 +14,7 @@
 //            the activations never leave their lane; b2 enters as the accumulator;
 //   layer 3: output o is placed in row 4 o, so it lands in lane group o, item 0: each
 //            lane receives derivative g of its own sample, and lane group g carries
-//            state component g (compensated two-sum update).
+//            state component g (summed in 64 bits beside the FP32 running sum that the network reads).
 // Kinematics and cost run in chunks of 16 steps, lane-parallel: lane group g takes
 // four consecutive steps of the chunk for its sample, with exclusive scans over the
 // four lane groups (v_permlane16_swap / v_permlane32_swap).  The noise of a chunk is
@@ -25,15 +25,18 @@
 namespace mppi {
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float qf32x4;
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float qf32x2;
 
 constexpr int kQuadBlock = 256;
 constexpr int kQuadWaves = 4;
 constexpr int kQuadSamples = 64;   // per block
 constexpr int kQuadChunk = 16;     // steps per chunk
-// floats of the chunk's clamped controls, [4 waves][16 steps][16 samples][2] and a row of
-// padding (the chain reads one step ahead); later the block's N row (2T)
-constexpr int kQuadControls = kQuadWaves * kQuadChunk * 16 * 2 + 32;
-static_assert(kQuadControls >= 2 * kTMax, "the N row reuses the controls' space");
+// A wave's LDS: rows 0..16 of kQuadRow floats, row s holding the network's inputs of its 16
+// samples at step s of the chunk: [16][4] state components (row 16: the state after the
+// chunk) and [16][4] of (v_0, v_1, 1, 0), the clamped control and the constants of lane
+// groups 2 and 3.  One address serves both and the state's write to the next row.
+constexpr int kQuadRow = 128;
+constexpr int kQuadWaveLds = (kQuadChunk + 1) * kQuadRow;
 
 __device__ __forceinline__ float q_as_f(uint32_t v) { return __builtin_bit_cast(float, v); }
 __device__ __forceinline__ uint32_t q_as_u(float v) { return __builtin_bit_cast(uint32_t, v); }
@@ -51,29 +54,30 @@ __device__ __forceinline__ void all4(float x, float v[4]) {
   v[3] = q_as_f(q1[1]);
 }
 
-// Compensated (hi, lo) of the four lane groups: exclusive prefix for lane group g and
-// the total, the same bits in the four lanes of a column.
-__device__ __forceinline__ void scan4_excl2(float hi, float lo, int g, float& ph, float& pl, float& th,
-                                            float& tl) {
-  float H[4], L[4];
-  all4(hi, H);
-  all4(lo, L);
-  float sh = H[0], sl = L[0];
-  ph = 0.0f;
-  pl = 0.0f;
+// The same for a 64-bit value.
+__device__ __forceinline__ void all4(double x, double v[4]) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  float lo[4], hi[4];
+  all4(q_as_f((uint32_t)b), lo);
+  all4(q_as_f((uint32_t)(b >> 32)), hi);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    v[i] = __builtin_bit_cast(double, ((uint64_t)q_as_u(hi[i]) << 32) | q_as_u(lo[i]));
+}
+
+// Exclusive prefix of the four lane groups' values for lane group g, and their sum, the
+// same bits in the four lanes of a column.
+__device__ __forceinline__ double scan4_excl(double v, int g, double& total) {
+  double V[4];
+  all4(v, V);
+  double s = V[0], p = 0.0;
 #pragma unroll
   for (int i = 1; i < 4; ++i) {
-    if (i == g) {
-      ph = sh;
-      pl = sl;
-    }
-    float s_, e_;
-    two_sum(sh, H[i], s_, e_);
-    sh = s_;
-    sl = sl + (L[i] + e_);
+    p = i == g ? s : p;
+    s = s + V[i];
   }
-  th = sh;
-  tl = sl;
+  total = s;
+  return p;
 }
 
 // v + v in the lanes 8, 4, 2 and 1 apart of each 16-lane row in turn: the row's sum in every
@@ -340,15 +344,15 @@ struct QuadNet {
 // waves issue together, 8.2 per exp or rcp), so a step of 16 samples costs its 704 (h = 32)
 // matrix cycles plus every vector instruction.  Hence everything that does not belong to
 // the chain is done once per sample and step, in the lane that draws the step's noise (the
-// clamped control and the control cost) or that evaluates its cost, and trajectories are
-// checked for non-finite states at their end: a state that is not finite stays so, since
-// every step adds to it.  242 -> ~196 vector instructions per wave-step beside the matrix
-// products; with tanh4 below, before -> after: batched form (512 instances, 1.01e8 steps)
-// 4.69 -> 4.44 ms; h = 64, T = 100: FP32 K = 65536 759 -> 702 us, BF16 332 -> 284 us, FP16 365 ->
-// 317 us, K = 16384 (one wave per SIMD) FP32 226 -> 197, BF16 124 -> 100, FP16 129 -> 106 us.
+// clamped control and the control cost) or that evaluates its cost; poses are checked for
+// non-finite values once per chunk and x_d at the end: what is not finite stays so, since
+// every step adds to it.  242 -> ~170 vector instructions per wave-step beside the matrix
+// products (a third of that from the 64-bit sums); with tanh4 above, before -> after: batched
+// form (512 instances, 1.01e8 steps) 4.69 -> 4.07 ms; T = 100, h = 64: FP32 K = 65536 759 -> 678
+// us, BF16 332 -> 264 us, FP16 365 -> 296 us, K = 16384 (one wave per SIMD) FP32 226 -> 188, BF16
+// 124 -> 91, FP16 129 -> 99 us; h = 32, FP32, K = 16384 131 -> 91 us.
 template <int PREC, int HID, bool RECEDE = true>
-__device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, float* sE, float* sX,
-                                  float* red) {
+__device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, float* sX, float* red) {
   const int T = __builtin_amdgcn_readfirstlane(a.T);
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -359,10 +363,13 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
   const bool zm = k >= a.K_imp;   // exploration sample: v = eps, delta = eps - u
   // v = eps + m_u u, delta = eps - m_z u, with one of the two 1 and the other 0 (exact)
   const float m_u = zm ? 0.0f : 1.0f, m_z = zm ? 1.0f : 0.0f;
-  float* wE = sE + wv * (kQuadChunk * 16 * 2);          // [chunk step][sample][2] clamped controls
-  float* wX = sX + wv * ((kQuadChunk + 1) * 16 * 4);    // [chunk step 0..16][sample][4]
-  // the stored noise of the wave's 16 samples ([T][16][2]), or null
-  float* wS = a.eps_store ? a.eps_store + ((size_t)tile * kQuadWaves + wv) * (size_t)T * 32 : nullptr;
+  float* wX = sX + wv * kQuadWaveLds;
+  // The stored noise of the wave's 16 samples ([T][16] pairs), or null.  Marked as global
+  // memory: in the batched form the pointer is itself read from memory and would be taken
+  // for a generic one, whose stores the next LDS read waits for.
+  typedef __attribute__((address_space(1))) qf32x2 global_pair;
+  global_pair* wS = a.eps_store ? (global_pair*)(a.eps_store + ((size_t)tile * kQuadWaves + wv) * (size_t)T * 32)
+                                : nullptr;
 
   for (int i = threadIdx.x; i < 2 * T; i += kQuadBlock) sU[i] = a.U[i];
   __syncthreads();
@@ -371,16 +378,24 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
   float x0v[kStateDim];
 #pragma unroll
   for (int i = 0; i < kStateDim; ++i) x0v[i] = a.x0_dev ? a.x0_dev[i] : a.x0[i];
-  const float b_const = g == 2 ? 1.0f : 0.0f;   // the network's input of lane groups 2 and 3
-
-  Acc xd{x0v[3 + g], 0.0f};          // state component g (roll, v_x, v_y, theta_dot)
-  // pose carries (compensated), the same in the four lanes of a sample
-  float th_h = x0v[2], th_l = 0.0f, px_h = x0v[0], px_l = 0.0f, py_h = x0v[1], py_l = 0.0f;
-  Acc Sacc{0.0f, 0.0f};
-  wX[j * 4 + g] = xd.hi;             // chunk row 0 = the state entering the chunk
+  // Sums over the steps are held in 64 bits: state component g (roll, v_x, v_y, theta_dot),
+  // of which the network reads the FP32 running sum xh, the pose entering the chunk (the
+  // same in the four lanes of a sample) and the cost.  A 64-bit add takes as long as one
+  // FP32 instruction; the error-free FP32 sums it replaces took seven or eight.
+  float xh = x0v[3 + g];
+  double xd = xh, th_c = x0v[2], px_c = x0v[0], py_c = x0v[1], S64 = 0.0;
+  bool ok = true;
+  wX[j * 4 + g] = xh;                // row 0 = the state entering the chunk
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    *reinterpret_cast<float2*>(wX + (4 * q + g) * kQuadRow + 64 + j * 4 + 2) = make_float2(1.0f, 0.0f);
+  // a horizon of less than a chunk leaves rows that no step writes: their sums are
+  // multiplied by a zero step, so they must be finite
+  if (T < kQuadChunk)
+    for (int s = 1; s <= kQuadChunk; ++s) wX[s * kQuadRow + j * 4 + g] = 0.0f;
 
   for (int cs = 0; cs < T; cs += kQuadChunk) {
-    const int n = min(kQuadChunk, T - cs);
+    const int n = __builtin_amdgcn_readfirstlane(min(kQuadChunk, T - cs));
     // the noise of the chunk: lane (g, j) draws steps cs + g + 4 q of its own sample
     // (past the horizon a clamped step, discarded), forms their clamped controls for the
     // chain and their control cost, and keeps the noise where it reads it back below
@@ -393,160 +408,114 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
       const float2 u = *reinterpret_cast<const float2*>(sU + 2 * t);
       const float v0 = __builtin_amdgcn_fmed3f(__builtin_fmaf(u.x, m_u, e0), a.u_lo0, a.u_hi0);
       const float v1 = __builtin_amdgcn_fmed3f(__builtin_fmaf(u.y, m_u, e1), a.u_lo1, a.u_hi1);
-      *reinterpret_cast<float2*>(wE + (s * 16 + j) * 2) = make_float2(v0, v1);
+      *reinterpret_cast<float2*>(wX + s * kQuadRow + 64 + j * 4) = make_float2(v0, v1);
       if (s < n) {
-        if (wS) *reinterpret_cast<float2*>(wS + (uint32_t)((t * 16 + j) * 2)) = make_float2(e0, e1);
-        Sacc.add(a.gcs0 * (u.x * __builtin_fmaf(-u.x, m_z, e0)));
-        Sacc.add(a.gcs1 * (u.y * __builtin_fmaf(-u.y, m_z, e1)));
+        if (wS) wS[(uint32_t)(t * 16 + j)] = qf32x2{e0, e1};
+        S64 += (double)(a.gcs0 * (u.x * __builtin_fmaf(-u.x, m_z, e0)));
+        S64 += (double)(a.gcs1 * (u.y * __builtin_fmaf(-u.y, m_z, e1)));
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // the serial chain over the chunk: lane groups 0 and 1 take control component g (read
-    // one step ahead; the row past the last is padding), 2 and 3 their constant
+    // the serial chain over the chunk; the step's control (or constant) is read one step ahead
+    // (row 16's place for controls is read and not used)
     {
-      const float* pe = wE + j * 2 + (g & 1);
-      float* px = wX + 64 + j * 4 + g;
-      float v = pe[0];
+      float* p = wX + j * 4 + g;
+      float v = p[64];
       for (int s = 0; s < n; ++s) {
-        pe += 32;
-        const float vn = pe[0];
-        const float f = net.eval(xd.hi, g < 2 ? v : b_const);
-        xd.add(a.dt * f);
-        px[0] = xd.value();
-        px += 64;
+        const float vn = p[kQuadRow + 64];
+        const float y = a.dt * net.eval(xh, v);
+        xh = xh + y;
+        xd = xd + (double)y;
+        p += kQuadRow;
+        p[0] = (float)xd;
         v = vn;
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // kinematics and cost of the chunk: lane group g takes steps cs + 4 g .. cs + 4 g + 3;
-    // a step past the horizon adds zeros
-    const float* row = wX + (4 * g * 16 + j) * 4;   // the state before the lane's first step
+    // kinematics and cost of the chunk: lane group g takes steps cs + 4 g .. cs + 4 g + 3; a
+    // step past the horizon has a zero time step
+    const float* row = wX + 4 * g * kQuadRow + j * 4;   // the state before the lane's first step
     bool live[4];
-    float dth[4];
+    float dq[4], dth[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       live[q] = 4 * g + q < n;
-      dth[q] = live[q] ? a.dt * row[q * 64 + 3] : 0.0f;
+      dq[q] = live[q] ? a.dt : 0.0f;
+      dth[q] = dq[q] * row[q * kQuadRow + 3];
     }
-    float tdh = dth[0], tdl = 0.0f;
-#pragma unroll
-    for (int q = 1; q < 4; ++q) {
-      float s_, e_;
-      two_sum(tdh, dth[q], s_, e_);
-      tdh = s_;
-      tdl += e_;
-    }
-    float pth, ptl, Tth, Ttl;
-    scan4_excl2(tdh, tdl, g, pth, ptl, Tth, Ttl);
-    float dpx[4], dpy[4];
+    // heading before each of the lane's steps
+    double th[4], th_sum;
     {
-      float th, thl, e_;
-      two_sum(th_h, pth, th, e_);
-      thl = th_l + (ptl + e_);
+      const double d1 = (double)dth[0] + (double)dth[1], d2 = d1 + (double)dth[2];
+      th[0] = th_c + scan4_excl(d2 + (double)dth[3], g, th_sum);
+      th[1] = th[0] + (double)dth[0];
+      th[2] = th[0] + d1;
+      th[3] = th[0] + d2;
+    }
+    // position after each of them
+    double px[4], py[4], px_sum, py_sum;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float vx = row[q * kQuadRow + 1], vy = row[q * kQuadRow + 2];
+      float sn, c_;
+      sincosf((float)th[q], &sn, &c_);
+      const double dx = (double)(dq[q] * (c_ * vx - sn * vy)), dy = (double)(dq[q] * (sn * vx + c_ * vy));
+      px[q] = q == 0 ? dx : px[q - 1] + dx;
+      py[q] = q == 0 ? dy : py[q - 1] + dy;
+    }
+    {
+      const double bx = px_c + scan4_excl(px[3], g, px_sum), by = py_c + scan4_excl(py[3], g, py_sum);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const float vx = row[q * 64 + 1], vy = row[q * 64 + 2];
-        float sn, c_;
-        sincosf(th + thl, &sn, &c_);
-        const float ax = a.dt * (c_ * vx - sn * vy), ay = a.dt * (sn * vx + c_ * vy);
-        dpx[q] = live[q] ? ax : 0.0f;
-        dpy[q] = live[q] ? ay : 0.0f;
-        if (q < 3) {
-          float s_;
-          two_sum(th, dth[q], s_, e_);
-          th = s_;
-          thl += e_;
-        }
+        px[q] = bx + px[q];
+        py[q] = by + py[q];
       }
     }
-    float dxh = dpx[0], dxl = 0.0f, dyh = dpy[0], dyl = 0.0f;
-#pragma unroll
-    for (int q = 1; q < 4; ++q) {
-      float s_, e_;
-      two_sum(dxh, dpx[q], s_, e_);
-      dxh = s_;
-      dxl += e_;
-      two_sum(dyh, dpy[q], s_, e_);
-      dyh = s_;
-      dyl += e_;
-    }
-    float pxh, pxl, Txh, Txl, pyh, pyl, Tyh, Tyl;
-    scan4_excl2(dxh, dxl, g, pxh, pxl, Txh, Txl);
-    scan4_excl2(dyh, dyl, g, pyh, pyl, Tyh, Tyl);
-    // positions after each of the lane's steps, and every map and decay load at once
+    // every map and decay load at once
     float mv[4][4], fxv[4], fyv[4], dec[4];
-    {
-      float ph_x, pl_x, ph_y, pl_y, e_;
-      two_sum(px_h, pxh, ph_x, e_);
-      pl_x = px_l + (pxl + e_);
-      two_sum(py_h, pyh, ph_y, e_);
-      pl_y = py_l + (pyl + e_);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float s_;
-        two_sum(ph_x, dpx[q], s_, e_);
-        ph_x = s_;
-        pl_x += e_;
-        two_sum(ph_y, dpy[q], s_, e_);
-        ph_y = s_;
-        pl_y += e_;
-        uint32_t off[4];
-        map_taps_bytes(a.cost, ph_x, pl_x, ph_y, pl_y, off, fxv[q], fyv[q]);
+    for (int q = 0; q < 4; ++q) {
+      uint32_t off[4];
+      map_taps64(a.cost, px[q], py[q], off, fxv[q], fyv[q]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          mv[q][i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.map) + off[i]);
-        dec[q] = a.decay[(uint32_t)(min(cs + 4 * g + q, T - 1) + 1)];
-      }
+      for (int i = 0; i < 4; ++i)
+        mv[q][i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.map) + off[i]);
+      dec[q] = a.decay[(uint32_t)(min(cs + 4 * g + q, T - 1) + 1)];
     }
     float zeta[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) zeta[q] = slip_angle(a.cost, row[(q + 1) * 64 + 1], row[(q + 1) * 64 + 2]);
+    for (int q = 0; q < 4; ++q) zeta[q] =
+          slip_angle(a.cost, row[(q + 1) * kQuadRow + 1], row[(q + 1) * kQuadRow + 2]);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const float c = state_cost_h(a.cost, bilerp(mv[q], fxv[q], fyv[q]), dec[q], row[(q + 1) * 64 + 1], zeta[q]);
-      Sacc.add(live[q] ? c : 0.0f);
+      const float c =
+          state_cost_h(a.cost, bilerp(mv[q], fxv[q], fyv[q]), dec[q], row[(q + 1) * kQuadRow + 1], zeta[q]);
+      S64 += (double)(live[q] ? c : 0.0f);
     }
-    // carries into the next chunk
-    {
-      float s_, e_;
-      two_sum(th_h, Tth, s_, e_);
-      th_h = s_;
-      th_l = th_l + (Ttl + e_);
-      two_sum(px_h, Txh, s_, e_);
-      px_h = s_;
-      px_l = px_l + (Txl + e_);
-      two_sum(py_h, Tyh, s_, e_);
-      py_h = s_;
-      py_l = py_l + (Tyl + e_);
-    }
+    // the pose entering the next chunk
+    th_c += th_sum;
+    px_c += px_sum;
+    py_c += py_sum;
+    ok = ok && finite_f((float)th_c) && finite_f((float)px_c) && finite_f((float)py_c);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     // the chunk's last state (as the cost reads it) enters the next chunk as its row 0
-    wX[j * 4 + g] = xd.value();
+    wX[j * 4 + g] = (float)xd;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  const bool ok = finite_f(xd.value()) && finite_f(th_h + th_l) && finite_f(px_h + px_l) && finite_f(py_h + py_l);
+  ok = ok && finite_f(xh) && finite_f((float)xd);
 
   // S_k: the four lanes' sums
-  float H[4], L[4];
-  all4(Sacc.hi, H);
-  all4(Sacc.lo, L);
-  float Sh = 0.0f, Sl = 0.0f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float s_, e_;
-    two_sum(Sh, H[i], s_, e_);
-    Sh = s_;
-    Sl = Sl + (L[i] + e_);
-  }
-  float S = Sh + Sl;
+  double S4[4];
+  all4(S64, S4);
+  float S = (float)(((S4[0] + S4[1]) + S4[2]) + S4[3]);
   float okv[4];
   all4(ok ? 1.0f : 0.0f, okv);
   const bool okc = okv[0] != 0.0f && okv[1] != 0.0f && okv[2] != 0.0f && okv[3] != 0.0f;
@@ -595,15 +564,15 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
   };
   if (wS) {
     for (int t0 = 0; t0 < T; t0 += 16) {   // four loads in flight
-      float2 v[4];
+      qf32x2 v[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int t = t0 + 4 * q + g;
-        v[q] = t < T ? *reinterpret_cast<const float2*>(wS + (uint32_t)((t * 16 + j) * 2)) : make_float2(0.0f, 0.0f);
+        v[q] = t < T ? wS[(uint32_t)(t * 16 + j)] : qf32x2{0.0f, 0.0f};
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        if (t0 + 4 * q < T) add_step(t0 + 4 * q + g, v[q].x, v[q].y);
+        if (t0 + 4 * q < T) add_step(t0 + 4 * q + g, v[q][0], v[q][1]);
     }
   } else {
     for (int t0 = 0; t0 < T; t0 += 4) {
@@ -614,7 +583,7 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
     }
   }
   __syncthreads();
-  float* N_lds = sE;   // the noise chunks are no longer read
+  float* N_lds = sX;   // the chunks are no longer read
   for (int o = threadIdx.x; o < 2 * T; o += kQuadBlock)
     N_lds[o] = ((red[o] + red[2 * kTMax + o]) + red[2 * 2 * kTMax + o]) + red[3 * 2 * kTMax + o];
   const float eta = ((scratch[4] + scratch[5]) + scratch[6]) + scratch[7];
@@ -627,10 +596,9 @@ template <int PREC, int HID>
 __global__ __launch_bounds__(kQuadBlock, HID == 32 ? 3 : 2) void rollout_quad_kernel(RolloutArgs a) {
   if (a.iter_dev) a.nk.iter = *a.iter_dev;   // the device counter, advanced by the final merge
   __shared__ __attribute__((aligned(16))) float sU[2 * kTMax];
-  __shared__ __attribute__((aligned(16))) float sE[kQuadControls];
-  __shared__ __attribute__((aligned(16))) float sX[kQuadWaves * (kQuadChunk + 1) * 16 * 4];
+  __shared__ __attribute__((aligned(16))) float sX[kQuadWaves * kQuadWaveLds];
   __shared__ __attribute__((aligned(16))) float red[kQuadWaves * 2 * kTMax + 8];
-  quad_rollout_tile<PREC, HID>(a, blockIdx.x, sU, sE, sX, red);
+  quad_rollout_tile<PREC, HID>(a, blockIdx.x, sU, sX, red);
 }
 
 // Batched form on quad tiles: each block takes items (instance, tile of 64 samples)
@@ -645,8 +613,7 @@ __global__ __launch_bounds__(kQuadBlock, 3) void rollout_batch_quad_kernel(const
                                                                       const float* __restrict__ decay,
                                                                       unsigned* __restrict__ queue) {
   __shared__ __attribute__((aligned(16))) float sU[2 * kTMax];
-  __shared__ __attribute__((aligned(16))) float sE[kQuadControls];
-  __shared__ __attribute__((aligned(16))) float sX[kQuadWaves * (kQuadChunk + 1) * 16 * 4];
+  __shared__ __attribute__((aligned(16))) float sX[kQuadWaves * kQuadWaveLds];
   __shared__ __attribute__((aligned(16))) float red[kQuadWaves * 2 * kTMax + 8];
   for (;;) {
     const int b = next_work_item(queue, n_items);
@@ -657,7 +624,7 @@ __global__ __launch_bounds__(kQuadBlock, 3) void rollout_batch_quad_kernel(const
     a.params = params;
     a.decay = decay;
     a.nk.iter = *a.iter_dev;
-    quad_rollout_tile<kQPrecFP32, 32, false>(a, it.y, sU, sE, sX, red);
+    quad_rollout_tile<kQPrecFP32, 32, false>(a, it.y, sU, sX, red);
   }
 }
 

@@ -379,6 +379,9 @@ CostArgs cost_args(const mppi_cost& cost, int H, int W, float ox, float oy, floa
   c.oy = oy;
   c.res = res;
   c.inv_res = 1.0f / res;
+  c.ox64 = ox;
+  c.oy64 = oy;
+  c.inv_res64 = 1.0 / (double)res;
   c.w_map = cost.w_map;
   c.w_speed = cost.w_speed;
   c.w_slip = cost.w_slip;

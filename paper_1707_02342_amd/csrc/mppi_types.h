@@ -62,6 +62,7 @@ struct CostArgs {
   int H, W;
   float ox, oy, res;
   float inv_res;           // fl(1 / res)
+  double ox64, oy64, inv_res64;   // ox, oy and 1 / res in 64 bits
   int slip_on;             // 0: neither slip term can be other than zero
   float w_map, w_speed, w_slip, v_des;
   float crash_cost, map_thresh, slip_cost, slip_thresh;
