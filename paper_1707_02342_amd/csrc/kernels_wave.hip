@@ -22,7 +22,8 @@
 //                exchanges for bits 0 and 1 of the lane, row_ror 8 and 4 for bits 3
 //                and 2) leaves output (lane & 3) in every lane, and a second
 //                permlane16 swap adds the two rows;
-//       update:  x_d += dt f in compensated (two-sum) form, one component per lane;
+//       update:  x_d += dt f, one component per lane, with the exact sum kept beside the FP32
+//                running sum that the network reads (see kDefer below);
 //     with the basis-function model (MODEL = kModelBasis) phase A also forms, for
 //     each of the lane's steps, everything that depends on the control alone (sin and
 //     tan of the steering and the four basis functions of the throttle and steering
@@ -31,7 +32,7 @@
 //     of the state (normalisers folded into its column of Theta) and lane (component c)
 //     sums its own output: no cross-lane reduction and no transcendental on the chain;
 //  C. kinematics and cost, lane-parallel over t: theta and the position are prefix
-//     sums of their Euler increments (scans across the 32 lanes), then the cost at
+//     sums of their Euler increments (64-bit scans across the 32 lanes), then the cost at
 //     every post-step state and the control-cost term, summed over t;
 //  D. the block's softmin partial (rho_g, eta_g, N_g) for the merge kernel.
 //
@@ -41,14 +42,17 @@
 
 namespace mppi {
 
+// Waves per SIMD: with its 64-bit sums the compiler's own choice is one less than the bound
+// here (137 and 210 registers), which costs more than the few registers that then spill:
+// K = 6001, T = 150 124 -> 110 us (114 with error-free FP32 sums), K = 8192, T = 100 85 -> 82.
 template <int HID, int NQ, int MODEL>
-__global__ __launch_bounds__(kWaveBlock) void rollout_wave_kernel(RolloutArgs a) {
+__global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kernel(RolloutArgs a) {
   if (a.iter_dev) a.nk.iter = *a.iter_dev;   // the device counter, advanced by the final merge
   static_assert(HID == 32, "the wave schedule maps 32 hidden units onto 32 lanes");
   extern __shared__ float smem[];
   // Up to 128 steps (NQ = 4) the chain stores the uncompensated state hi_t and each
   // increment y_t, and phase C forms the compensated sums from them lane-parallel;
-  // beyond (NQ = 8) the chain keeps the compensation itself (less LDS per block).
+  // beyond (NQ = 8) the chain keeps the exact sum itself, in 64 bits (less LDS per block).
   constexpr bool kDefer = NQ <= 4;
   constexpr int kXW = kDefer ? 8 : 4;                // floats per step in sX
   constexpr bool kNetV = MODEL == kModelNet;         // the chain reads the clamped controls from sV
@@ -195,8 +199,8 @@ __global__ __launch_bounds__(kWaveBlock) void rollout_wave_kernel(RolloutArgs a)
       }
     }
   }
-  Acc xd{x0v[3 + comp], 0.0f};       // NQ = 8: compensated in the chain
-  float xh = x0v[3 + comp];           // NQ = 4: the uncompensated state hi_t
+  float xh = x0v[3 + comp];           // the FP32 running sum hi_t that the network reads
+  double xd = xh;                     // NQ = 8: the state's exact sum, kept by the chain
   if (c32 < 4) sX[slot * T4 * kXW + c32] = x0v[3 + c32];
   if (a.ckpt && valid && c32 < kStateDim)
     a.ckpt[(size_t)k * (T / a.ckpt_every + 1) * kCkptStride + c32] = x0v[c32];
@@ -230,7 +234,7 @@ __global__ __launch_bounds__(kWaveBlock) void rollout_wave_kernel(RolloutArgs a)
     }
     const float vc0 = vc.x, vc1 = vc.y;
     float y;   // dt * f of the lane's component
-    const float xcur = kDefer ? xh : xd.hi;
+    const float xcur = xh;
     if constexpr (MODEL == kModelBasis) {
       // bq = {sin u_delta, -tan u_delta, u_delta, 0}, cq = the control-only terms
       const float4 bq_next = *reinterpret_cast<const float4*>(myB + 8 * tn);
@@ -329,12 +333,12 @@ __global__ __launch_bounds__(kWaveBlock) void rollout_wave_kernel(RolloutArgs a)
     }
     // every lane of a component holds the same bits (y and the update are formed alike
     // in all of them), so all lanes store: no branch in the step loop
+    xh = xh + y;
     if constexpr (kDefer) {
-      xh = xh + y;
       sX[xs_off + t * kXW] = (lane & 4) ? y : xh;   // y_t at entry t, hi_{t+1} at entry t + 1
     } else {
-      xd.add(y);
-      sX[slot * T4 * kXW + (t + 1) * kXW + comp] = xd.value();
+      xd = xd + (double)y;
+      sX[slot * T4 * kXW + (t + 1) * kXW + comp] = (float)xd;
     }
     u = u_next;
     e = e_next;
@@ -346,8 +350,7 @@ __global__ __launch_bounds__(kWaveBlock) void rollout_wave_kernel(RolloutArgs a)
   // ---- C: kinematics and cost, parallel over t ---------------------------------------
   // Lane c owns the contiguous steps [c*npl, (c+1)*npl).  theta(t) = theta_0 + dt sum_{s<t}
   // theta_dot(s) and p(t+1) = p_0 + dt sum_{s<=t} R(theta(s)) v(s) are formed as
-  // compensated lane sums plus compensated exclusive scans across the 32 lanes.  The
-  // positions of all the lane's steps are formed first, then every map and decay load
+  // 64-bit lane sums plus 64-bit scans across the 32 lanes.  The positions of all the lane's steps are formed first, then every map and decay load
   // is issued before the first is used (one memory round trip), then the costs.
   const int npl = NT;
   const int tb = c32 * npl;
@@ -395,126 +398,76 @@ __global__ __launch_bounds__(kWaveBlock) void rollout_wave_kernel(RolloutArgs a)
   auto xpost = [&](int q) -> float4 {  // x_d after step tb + q
     if constexpr (kDefer) return xv[q + 1]; else return myX[tb + q + 1];
   };
-  float th_h = 0.0f, th_l = 0.0f;
+  // theta before each of the lane's steps and after the last: sums and scans in 64 bits
+  // (dead slots add zero and keep the last live pose)
+  double th[NQ + 1];
+  th[0] = 0.0;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+    th[q + 1] = th[q] + (double)((q < npl && tb + q < T) ? a.dt * xpre(q).w : 0.0f);
+  {
+    const double base = x0v[2] + (scan32_incl64(th[NQ]) - th[NQ]);
+#pragma unroll
+    for (int q = 0; q <= NQ; ++q) th[q] = base + th[q];
+  }
+  double px[NQ], py[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
-    const int t = tb + q;
-    if (q < npl && t < T) {
-      float s_, e_;
-      two_sum(th_h, a.dt * xpre(q).w, s_, e_);
-      th_h = s_;
-      th_l += e_;
+    double dx = 0.0, dy = 0.0;
+    if (q < npl && tb + q < T) {
+      const float4 xs = xpre(q);
+      float sn, cs;
+      sincosf((float)th[q], &sn, &cs);
+      dx = (double)(a.dt * (cs * xs.y - sn * xs.z));
+      dy = (double)(a.dt * (sn * xs.y + cs * xs.z));
     }
+    px[q] = q == 0 ? dx : px[q - 1] + dx;
+    py[q] = q == 0 ? dy : py[q - 1] + dy;
   }
-  scan32_excl2(th_h, th_l, c32);
   {
-    float s_, e_;
-    two_sum(x0v[2], th_h, s_, e_);
-    th_h = s_;
-    th_l = th_l + e_;
-  }
-  // theta at the lane's first step; walk the steps for the position increments
-  float dpx[NQ], dpy[NQ];
-  float px_h = 0.0f, px_l = 0.0f, py_h = 0.0f, py_l = 0.0f;
-  {
-    float th = th_h, thl = th_l;
+    const double bx = x0v[0] + (scan32_incl64(px[NQ - 1]) - px[NQ - 1]);
+    const double by = x0v[1] + (scan32_incl64(py[NQ - 1]) - py[NQ - 1]);
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-      dpx[q] = 0.0f;
-      dpy[q] = 0.0f;
-      const int t = tb + q;
-      if (q < npl && t < T) {
-        const float4 xs = xpre(q);
-        float sn, cs;
-        sincosf(th + thl, &sn, &cs);
-        dpx[q] = a.dt * (cs * xs.y - sn * xs.z);
-        dpy[q] = a.dt * (sn * xs.y + cs * xs.z);
-        float s_, e_;
-        two_sum(px_h, dpx[q], s_, e_);
-        px_h = s_;
-        px_l += e_;
-        two_sum(py_h, dpy[q], s_, e_);
-        py_h = s_;
-        py_l += e_;
-        two_sum(th, a.dt * xs.w, s_, e_);
-        th = s_;
-        thl += e_;
-      }
-    }
-  }
-  scan32_excl2(px_h, px_l, c32);
-  scan32_excl2(py_h, py_l, c32);
-  {
-    float s_, e_;
-    two_sum(x0v[0], px_h, s_, e_);
-    px_h = s_;
-    px_l += e_;
-    two_sum(x0v[1], py_h, s_, e_);
-    py_h = s_;
-    py_l += e_;
-  }
-  // post-step poses of the lane's steps (dead slots keep the last live pose)
-  float pxh[NQ], pxl[NQ], pyh[NQ], pyl[NQ], th1[NQ];
-  {
-    float th = th_h, thl = th_l;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int t = tb + q;
-      if (q < npl && t < T) {
-        float s_, e_;
-        two_sum(px_h, dpx[q], s_, e_);
-        px_h = s_;
-        px_l += e_;
-        two_sum(py_h, dpy[q], s_, e_);
-        py_h = s_;
-        py_l += e_;
-        two_sum(th, a.dt * xpre(q).w, s_, e_);
-        th = s_;
-        thl += e_;
-      }
-      pxh[q] = px_h;
-      pxl[q] = px_l;
-      pyh[q] = py_h;
-      pyl[q] = py_l;
-      th1[q] = th + thl;
+      px[q] = bx + px[q];
+      py[q] = by + py[q];
     }
   }
   // all gathers at once (indices are clamped to the map, steps to [1, T])
   float mv[NQ][4], fxv[NQ], fyv[NQ], dec[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
-    int idx[4];
-    map_taps(a.cost, pxh[q], pxl[q], pyh[q], pyl[q], idx, fxv[q], fyv[q]);
+    uint32_t off[4];
+    map_taps64(a.cost, px[q], py[q], off, fxv[q], fyv[q]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) mv[q][i] = a.map[idx[i]];
+    for (int i = 0; i < 4; ++i)
+      mv[q][i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.map) + off[i]);
     dec[q] = a.decay[min(tb + q, T - 1) + 1];
   }
-  Acc Sacc{0.0f, 0.0f};
+  double S64 = 0.0;
   bool ok = true;
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
     const int t = tb + q;
     if (q < npl && t < T) {
       const float4 xn = xpost(q);
-      const float px1 = pxh[q] + pxl[q], py1 = pyh[q] + pyl[q];
+      const float px1 = (float)px[q], py1 = (float)py[q], th1 = (float)th[q + 1];
       if (a.ckpt && ((t + 1) % a.ckpt_every) == 0 && valid) {
         float* cp = a.ckpt + ((size_t)k * (T / a.ckpt_every + 1) + (t + 1) / a.ckpt_every) * kCkptStride;
-        cp[0] = px1; cp[1] = py1; cp[2] = th1[q];
+        cp[0] = px1; cp[1] = py1; cp[2] = th1;
         cp[3] = xn.x; cp[4] = xn.y; cp[5] = xn.z; cp[6] = xn.w;
       }
       const float zeta = slip_angle(a.cost, xn.y, xn.z);
-      Sacc.add(state_cost_h(a.cost, bilerp(mv[q], fxv[q], fyv[q]), dec[q], xn.y, zeta));
+      S64 += (double)state_cost_h(a.cost, bilerp(mv[q], fxv[q], fyv[q]), dec[q], xn.y, zeta);
       const float u0 = sU[2 * t], u1 = sU[2 * t + 1];
       const float d0 = zm ? myE[2 * t] - u0 : myE[2 * t];
       const float d1 = zm ? myE[2 * t + 1] - u1 : myE[2 * t + 1];
-      Sacc.add(a.gcs0 * (u0 * d0) + a.gcs1 * (u1 * d1));
-      ok = ok && finite_f(px1) && finite_f(py1) && finite_f(th1[q]) && finite_f(xn.x) &&
+      S64 += (double)(a.gcs0 * (u0 * d0) + a.gcs1 * (u1 * d1));
+      ok = ok && finite_f(px1) && finite_f(py1) && finite_f(th1) && finite_f(xn.x) &&
            finite_f(xn.y) && finite_f(xn.z) && finite_f(xn.w);
     }
   }
-  float S_h = Sacc.hi, S_l = Sacc.lo;
-  sum32_2(S_h, S_l);
-  float S = S_h + S_l;
+  float S = (float)sum32_64(S64);
   const bool okc = all32(ok);
   if (!valid || !okc || !finite_f(S)) S = kInf;
   if (valid && c32 == 0) store_through(a.S + k, S);   // read by the host or Algorithm 3's update

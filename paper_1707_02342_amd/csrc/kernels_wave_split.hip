@@ -22,7 +22,7 @@
 //  cost wave (waves 4..7): follows the chain one chunk behind: for chunk c it waits
 //    (acquire) for the chain's counter, forms the compensated states x_d(t) = hi_t + lo_t
 //    (the two-sum errors of the chain's sums, scanned across the lanes), the heading and
-//    the position by compensated scans carried from chunk to chunk, and the state and
+//    the position by 64-bit scans carried from chunk to chunk, and the state and
 //    control costs of the chunk's steps (one step per lane).
 //
 // The cost wave waits only for the chain of its own block, which never waits, so every
@@ -53,7 +53,8 @@
 // What bounds a step (paper-shaped): the latency of the chain (~20 us), then of the
 // exchange.  Replaced: a merger per group of 16 rows (each row written, waited for and
 // flagged, the group row likewise, and all 15 group rows merged again by every rollout
-// block): 32.0 -> 29.9 us per paper-shaped step (basis-function model 28.9 -> 26.2).
+// block): 32.0 -> 29.8 us per paper-shaped step (basis-function model 28.9 -> 26.2); with the
+// cost waves' scans in 64 bits 29.4 (26.0).
 #include "wave_common.hip.h"
 
 namespace mppi {
@@ -95,12 +96,10 @@ __device__ __forceinline__ float last_of_half(float v) {
   return (threadIdx.x & 32) ? hi : lo;
 }
 
-// (hi, lo) += (b_hi, b_lo) with an error-free two-sum of the high parts.
-__device__ __forceinline__ void add2(float& hi, float& lo, float b_hi, float b_lo) {
-  float s_, e_;
-  two_sum(hi, b_hi, s_, e_);
-  hi = s_;
-  lo = lo + (b_lo + e_);
+__device__ __forceinline__ double last_of_half(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = as_u(last_of_half(as_f((uint32_t)b))), hi = as_u(last_of_half(as_f((uint32_t)(b >> 32))));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
 // The controls the chain reads for step t of a sample from its noise e: the clamped
@@ -575,12 +574,10 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
       // ---- cost wave -----------------------------------------------------------------
       if (as.ckpt && valid && c32 < kStateDim)
         as.ckpt[(size_t)k * (T / as.ckpt_every + 1) * kCkptStride + c32] = x0v[c32];
-      // carries from chunk to chunk: the compensation lo of each x_d component, the
-      // heading and the position (hi, lo), the cost (hi, lo)
+      // carries from chunk to chunk: the compensation lo of each x_d component; the heading,
+      // the position and the cost in 64 bits
       float lo[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      float th_h = x0v[2], th_l = 0.0f;
-      float px_h = x0v[0], px_l = 0.0f, py_h = x0v[1], py_l = 0.0f;
-      Acc Sacc{0.0f, 0.0f};
+      double th_c = x0v[2], px_c = x0v[0], py_c = x0v[1], S64 = 0.0;
       bool ok = true;
       for (int c = 0; c < nch; ++c) {
         wait_count(chainCnt, (unsigned)(step * nch + c + 1));
@@ -604,54 +601,38 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
           lo[i] = lo[i] + last_of_half(ex + e_);       // the chunk's errors
         }
         // heading before the step: theta_0 + dt * (sum of the previous steps' theta_dot)
-        const float dth = live ? as.dt * xp[3] : 0.0f;
-        float sh = dth, sl = 0.0f;
-        scan32_excl2(sh, sl, c32);
-        float th = th_h, thl = th_l;
-        add2(th, thl, sh, sl);                         // theta_t
-        {
-          float ih = sh, il = sl;                      // the chunk's total
-          add2(ih, il, dth, 0.0f);
-          add2(th_h, th_l, last_of_half(ih), last_of_half(il));
-        }
-        // position after the step: p_0 + dt * (sum over s <= t of R(theta_s) v_s)
+        const double dth = (double)(live ? as.dt * xp[3] : 0.0f);
+        const double th1 = th_c + scan32_incl64(dth);   // after the step
         float sn, cs;
-        sincosf(th + thl, &sn, &cs);
-        const float dpx = live ? as.dt * (cs * xp[1] - sn * xp[2]) : 0.0f;
-        const float dpy = live ? as.dt * (sn * xp[1] + cs * xp[2]) : 0.0f;
-        float qxh = dpx, qxl = 0.0f, qyh = dpy, qyl = 0.0f;
-        scan32_excl2(qxh, qxl, c32);
-        scan32_excl2(qyh, qyl, c32);
-        add2(qxh, qxl, dpx, 0.0f);                     // inclusive
-        add2(qyh, qyl, dpy, 0.0f);
-        float pxh = px_h, pxl = px_l, pyh = py_h, pyl = py_l;
-        add2(pxh, pxl, qxh, qxl);
-        add2(pyh, pyl, qyh, qyl);
-        add2(px_h, px_l, last_of_half(qxh), last_of_half(qxl));
-        add2(py_h, py_l, last_of_half(qyh), last_of_half(qyl));
-        float th1h = th, th1l = thl;
-        add2(th1h, th1l, dth, 0.0f);
-        const float th1 = th1h + th1l;
+        sincosf((float)(th1 - dth), &sn, &cs);
+        // position after the step: p_0 + dt * (sum over s <= t of R(theta_s) v_s)
+        const double px = px_c + scan32_incl64((double)(live ? as.dt * (cs * xp[1] - sn * xp[2]) : 0.0f));
+        const double py = py_c + scan32_incl64((double)(live ? as.dt * (sn * xp[1] + cs * xp[2]) : 0.0f));
+        th_c = last_of_half(th1);
+        px_c = last_of_half(px);
+        py_c = last_of_half(py);
         // cost of the post-step state and the control cost of the step
-        int idx[4];
+        uint32_t off[4];
         float fx, fy;
-        map_taps(as.cost, pxh, pxl, pyh, pyl, idx, fx, fy);
-        const float mv[4] = {as.map[idx[0]], as.map[idx[1]], as.map[idx[2]], as.map[idx[3]]};
+        map_taps64(as.cost, px, py, off, fx, fy);
+        const char* map = reinterpret_cast<const char*>(as.map);
+        const float mv[4] = {*reinterpret_cast<const float*>(map + off[0]), *reinterpret_cast<const float*>(map + off[1]),
+                             *reinterpret_cast<const float*>(map + off[2]), *reinterpret_cast<const float*>(map + off[3])};
         const float dec = as.decay[tc + 1];
         const float zeta = slip_angle(as.cost, xn[1], xn[2]);   // while the map values arrive
         if (live) {
-          const float px1 = pxh + pxl, py1 = pyh + pyl;
+          const float px1 = (float)px, py1 = (float)py;
           if (as.ckpt && ((t + 1) % as.ckpt_every) == 0 && valid) {
             float* cp = as.ckpt + ((size_t)k * (T / as.ckpt_every + 1) + (t + 1) / as.ckpt_every) * kCkptStride;
-            cp[0] = px1; cp[1] = py1; cp[2] = th1;
+            cp[0] = px1; cp[1] = py1; cp[2] = (float)th1;
             cp[3] = xn[0]; cp[4] = xn[1]; cp[5] = xn[2]; cp[6] = xn[3];
           }
-          Sacc.add(state_cost_h(as.cost, bilerp(mv, fx, fy), dec, xn[1], zeta));
+          S64 += (double)state_cost_h(as.cost, bilerp(mv, fx, fy), dec, xn[1], zeta);
           const float u0 = sU[2 * t], u1 = sU[2 * t + 1];
           const float d0 = zm ? myE[2 * t] - u0 : myE[2 * t];
           const float d1 = zm ? myE[2 * t + 1] - u1 : myE[2 * t + 1];
-          Sacc.add(as.gcs0 * (u0 * d0) + as.gcs1 * (u1 * d1));
-          ok = ok && finite_f(px1) && finite_f(py1) && finite_f(th1) && finite_f(xn[0]) && finite_f(xn[1]) &&
+          S64 += (double)(as.gcs0 * (u0 * d0) + as.gcs1 * (u1 * d1));
+          ok = ok && finite_f(px1) && finite_f(py1) && finite_f((float)th1) && finite_f(xn[0]) && finite_f(xn[1]) &&
                finite_f(xn[2]) && finite_f(xn[3]);
           if (as.cem_zeta > 0 && valid) {
             float* drow = as.D + (size_t)k * 2 * T;
@@ -660,9 +641,7 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
           }
         }
       }
-      float S_h = Sacc.hi, S_l = Sacc.lo;
-      sum32_2(S_h, S_l);
-      float S = S_h + S_l;
+      float S = (float)sum32_64(S64);
       if (!valid || !all32(ok) || !finite_f(S)) S = kInf;
       if (valid && c32 == 0) store_through(as.S + k, S);   // read by the host or Algorithm 3's update
       if (c32 == 0) sS[slot] = S;

@@ -67,35 +67,25 @@ __device__ __forceinline__ float dpp_upd(float old, float v) {
   return as_f((uint32_t)__builtin_amdgcn_update_dpp((int)as_u(old), (int)as_u(v), CTRL, ROWMASK, 0xF, false));
 }
 
-// One step of a compensated scan: (hi, lo) += the pair that DPP control CTRL brings in
-// (lanes outside ROWMASK, or without a source lane, add (0, 0)).
-template <int CTRL, int ROWMASK>
-__device__ __forceinline__ void scan_step2(float& hi, float& lo) {
-  const float oh = dpp_upd<CTRL, ROWMASK>(0.0f, hi);
-  const float ol = dpp_upd<CTRL, ROWMASK>(0.0f, lo);
-  float s_, e_;
-  two_sum(hi, oh, s_, e_);
-  hi = s_;
-  lo = lo + (ol + e_);
+// The same for a 64-bit value, 0 in the lanes without a source.
+template <int CTRL, int ROWMASK = 0xF>
+__device__ __forceinline__ double dpp_zero64(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = as_u(dpp_upd<CTRL, ROWMASK>(0.0f, as_f((uint32_t)b)));
+  const uint32_t hi = as_u(dpp_upd<CTRL, ROWMASK>(0.0f, as_f((uint32_t)(b >> 32))));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// Compensated exclusive scan of (hi, lo) pairs over the 32 lanes of a half-wave
-// (lane 0 of each half gets (0, 0)), in DPP moves: the pairs are shifted up one lane,
-// scanned within each 16-lane row (shifts 1, 2, 4, 8), and the first row's total is
-// added to the second row.
-__device__ __forceinline__ void scan32_excl2(float& hi, float& lo, int c32) {
-  const bool col0 = (c32 & 15) == 0;
-  {
-    const float sh = dpp_upd<kRowShr + 1>(0.0f, hi), sl = dpp_upd<kRowShr + 1>(0.0f, lo);
-    const float bh = dpp_upd<kRowBcast15, 0xA>(0.0f, hi), bl = dpp_upd<kRowBcast15, 0xA>(0.0f, lo);
-    hi = col0 ? bh : sh;
-    lo = col0 ? bl : sl;
-  }
-  scan_step2<kRowShr + 1, 0xF>(hi, lo);
-  scan_step2<kRowShr + 2, 0xF>(hi, lo);
-  scan_step2<kRowShr + 4, 0xF>(hi, lo);
-  scan_step2<kRowShr + 8, 0xF>(hi, lo);
-  scan_step2<kRowBcast15, 0xA>(hi, lo);
+// Inclusive sums of v over the 32 lanes of a half-wave in 64 bits: within each 16-lane row
+// (shifts 1, 2, 4, 8), then the first row's total added to the second row.  An FP64 add
+// takes as long as one FP32 instruction; the error-free FP32 pairs that these sums
+// replace took eight per step.
+__device__ __forceinline__ double scan32_incl64(double v) {
+  v = v + dpp_zero64<kRowShr + 1>(v);
+  v = v + dpp_zero64<kRowShr + 2>(v);
+  v = v + dpp_zero64<kRowShr + 4>(v);
+  v = v + dpp_zero64<kRowShr + 8>(v);
+  return v + dpp_zero64<kRowBcast15, 0xA>(v);
 }
 
 // Exclusive scan of v over the 32 lanes of a half-wave (lane 0 of each half gets 0), in
@@ -114,28 +104,19 @@ __device__ __forceinline__ float scan32_excl(float v, int c32) {
   return v;
 }
 
-// Compensated sum of (hi, lo) over the 32 lanes, the same bits in every lane (the
-// error-free two-sum is symmetric in its operands): butterflies within each row, then
-// the two rows.
-__device__ __forceinline__ void sum32_2(float& hi, float& lo) {
-  auto step = [&](float oh, float ol) {
-    float s_, e_;
-    two_sum(hi, oh, s_, e_);
-    hi = s_;
-    lo = (lo + ol) + e_;
-  };
-  step(dpp_f<kRowRor + 8>(hi), dpp_f<kRowRor + 8>(lo));
-  step(dpp_f<kRowRor + 4>(hi), dpp_f<kRowRor + 4>(lo));
-  step(dpp_f<kQuadXor2>(hi), dpp_f<kQuadXor2>(lo));
-  step(dpp_f<kQuadXor1>(hi), dpp_f<kQuadXor1>(lo));
-  float xh = hi, yh = hi, xl = lo, yl = lo;
-  swap_rows(xh, yh);
+// Sum of v over the 32 lanes, the same bits in every lane: butterflies within each row,
+// then the two rows.
+__device__ __forceinline__ double sum32_64(double v) {
+  v = v + dpp_zero64<kRowRor + 8>(v);
+  v = v + dpp_zero64<kRowRor + 4>(v);
+  v = v + dpp_zero64<kQuadXor2>(v);
+  v = v + dpp_zero64<kQuadXor1>(v);
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  float xl = as_f((uint32_t)b), yl = xl, xh = as_f((uint32_t)(b >> 32)), yh = xh;
   swap_rows(xl, yl);
-  // each lane now holds its own row's (hi, lo) in one operand and the other row's in the other
-  const bool r1 = (threadIdx.x & 16) != 0;
-  hi = r1 ? yh : xh;
-  lo = r1 ? yl : xl;
-  step(r1 ? xh : yh, r1 ? xl : yl);
+  swap_rows(xh, yh);
+  return __builtin_bit_cast(double, ((uint64_t)as_u(xh) << 32) | as_u(xl)) +
+         __builtin_bit_cast(double, ((uint64_t)as_u(yh) << 32) | as_u(yl));
 }
 
 // The value of v in the lane 32 apart (the other half of the wave).
