@@ -495,10 +495,16 @@ struct FinalStage {
         }
         u_new[j] = u_old[j] + upd;
         if (writer && !a.recede) store_through(a.Uout + o, u_new[j]);
+        if constexpr (!RECEDE) {
+          if (a.U_host) a.U_host[o] = u_new[j];
+        }
       }
     }
     if (writer && tid == 0) {
       *a.status = fin ? 0 : kStatusNonfinite;
+      if constexpr (!RECEDE) {
+        if (a.status_host) *a.status_host = fin ? 0 : kStatusNonfinite;
+      }
       a.stats[0] = stat0;
       a.stats[1] = stat1;
       if (a.iter_dev) *a.iter_dev = iter + 1u;

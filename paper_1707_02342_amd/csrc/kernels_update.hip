@@ -82,6 +82,14 @@ __global__ __launch_bounds__(256) void costmap_kernel(CostArgs c, const float* _
   h[i] = costmap_at2(c, map, xy[2 * i], 0.0f, xy[2 * i + 1], 0.0f);
 }
 
+// Copies between device memory and pinned host memory.  A launch behind the work that it
+// waits for costs ~2 us where a copy command (to pageable memory) costs 9-20.
+__global__ __launch_bounds__(256) void copy_words_kernel(CopyArgs c) {
+#pragma unroll
+  for (int r = 0; r < kCopyRanges; ++r)
+    for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < c.words[r]; i += gridDim.x * 256) c.dst[r][i] = c.src[r][i];
+}
+
 // The rollout kernels' perturbations for one iteration, written out ([K][T][2]).
 __global__ __launch_bounds__(256) void noise_kernel(NoiseKey nk, int K, int T, float* eps) {
   const int idx = blockIdx.x * 256 + threadIdx.x;

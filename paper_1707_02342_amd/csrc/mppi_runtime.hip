@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <new>
 #include <string>
@@ -37,6 +38,7 @@ template <int HID>
 __global__ void plant_kernel(const float*, const float*, const float*, float*, float*, float, float,
                              float, float, float);
 __global__ void noise_kernel(NoiseKey, int, int, float*);
+__global__ void copy_words_kernel(CopyArgs);
 __global__ void costmap_kernel(CostArgs, const float*, const float*, int, float*);
 __global__ void adjoint_wave_kernel(AdjointArgs);
 template <int NCOL, int HC> __global__ void cem_update_kernel(RolloutArgs);
@@ -66,6 +68,22 @@ constexpr int32_t kMaxK = 1 << 22;
 // waves per SIMD (latency-bound regime), one lane per sample beyond.
 constexpr int32_t kWaveAutoMaxK = 12288;   // AUTO: WAVE up to here, QUAD above
 constexpr int kNumBasisHost = 25;          // basis functions of the basis-function model
+
+// Pinned host memory of a context: the first kPinnedUpWords words hold inputs on their way to
+// the device, the rest results on their way to the host.  Allocated with the context, grown
+// when a fetch needs more, at most kPinnedMaxWords words for results (1 MiB; larger transfers,
+// and those for which it cannot be had, go directly to the caller's memory).  U and the
+// status took two copy commands to the caller's memory, 39 us with the synchronisation behind
+// a short kernel; one launch that writes them here and a plain copy take 20 (64 KB: 49 and
+// 22; 256 KB: 57 and 30).
+constexpr size_t kPinnedMaxWords = (size_t)1 << 18;
+constexpr size_t kPinnedUpWords = 8192;
+struct Pinned {
+  uint32_t* host = nullptr;
+  uint32_t* dev = nullptr;
+  size_t words = 0;          // for results, behind the first kPinnedUpWords
+  size_t up_used = 0;        // words for inputs that a launch which may not have run yet reads
+};
 
 struct PendingTiming {
   hipEvent_t e0, e1;
@@ -97,8 +115,8 @@ struct mppi_ctx {
   unsigned* d_cnt = nullptr;
   float* d_stats = nullptr;
   float* d_sg = nullptr;
-  float* d_x = nullptr;      // [7] device-resident state for the receding loop
-  float* d_u0 = nullptr;     // [2]
+  float* d_x = nullptr;      // [7] device-resident state for the receding loop, then d_u0
+  float* d_u0 = nullptr;     // [2], in d_x's allocation
   int* d_status = nullptr;
   float* d_hist_u = nullptr;
   float* d_hist_x = nullptr;
@@ -118,6 +136,7 @@ struct mppi_ctx {
   uint32_t iter = 0;
   int schedule = MPPI_SCHED_LANE;
   float sig[2] = {0, 0};
+  Pinned pin;
   std::string err;
   bool timing = false;
   std::vector<PendingTiming> pending;
@@ -137,6 +156,39 @@ mppi_status fail(mppi_ctx* c, mppi_status st, const char* fmt, ...) {
   va_end(ap);
   if (c) c->err = buf; else g_create_error = buf;
   return st;
+}
+
+// Room for `words` words of results.  No launch that uses the memory may be in flight.
+bool pinned_reserve(Pinned& p, size_t words) {
+  if (p.host && words <= p.words) return true;
+  if (words > kPinnedMaxWords) return false;
+  const size_t n = (kPinnedUpWords + words + 4095) / 4096 * 4096;
+  void *h = nullptr, *d = nullptr;
+  // another thread's stream may be under capture, which an allocation must not end
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  if (p.host) (void)hipHostFree(p.host);
+  p = Pinned{};
+  hipError_t e = hipHostMalloc(&h, n * 4, hipHostMallocMapped | hipHostMallocCoherent);
+  if (e == hipSuccess) e = hipHostGetDevicePointer(&d, h, 0);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    if (h) (void)hipHostFree(h);
+  }
+  if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) return false;
+  p.host = static_cast<uint32_t*>(h);
+  p.dev = static_cast<uint32_t*>(d);
+  p.words = n - kPinnedUpWords;
+  return true;
+}
+
+hipError_t launch_copy(const CopyArgs& a, hipStream_t stream) {
+  unsigned most = 0;
+  for (unsigned w : a.words) most = std::max(most, w);
+  const unsigned blocks = std::min(256u, std::max(1u, (most + 1023) / 1024));
+  hipLaunchKernelGGL(copy_words_kernel, dim3(blocks), dim3(256), 0, stream, a);
+  return hipGetLastError();
 }
 
 #define HIP_TRY(ctx, expr)                                                                   \
@@ -621,10 +673,76 @@ mppi_status enqueue_receding_steps(mppi_ctx* c, float* x_dev, int n, float* u_hi
 
 constexpr int kStatusTimeoutHost = 6;   // the split kernel's status when a wait of a multi-step launch gave up
 
-mppi_status read_status(mppi_ctx* c) {
-  int st = 0;
-  HIP_TRY(c, hipMemcpyAsync(&st, c->d_status, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
+// A range of 4-byte words on its way to the host.
+struct Range {
+  const void* src;   // device
+  void* dst;         // host
+  size_t words;
+};
+
+// Copies up to kCopyRanges ranges to the host and synchronises the context's stream: one
+// launch that gathers them in pinned memory, then plain copies.
+mppi_status fetch(mppi_ctx* c, std::initializer_list<Range> ranges) {
+  size_t total = 0;
+  for (const Range& r : ranges) total += r.words;
+  if (total > c->pin.words && total <= kPinnedMaxWords) {
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    pinned_reserve(c->pin, total);
+  }
+  if (total <= c->pin.words) {
+    CopyArgs a{};
+    size_t off = kPinnedUpWords;
+    int n = 0;
+    for (const Range& r : ranges) {
+      a.src[n] = static_cast<const uint32_t*>(r.src);
+      a.dst[n] = c->pin.dev + off;
+      a.words[n++] = (unsigned)r.words;
+      off += r.words;
+    }
+    HIP_TRY(c, launch_copy(a, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    off = kPinnedUpWords;
+    for (const Range& r : ranges) {
+      if (r.words) std::memcpy(r.dst, c->pin.host + off, 4 * r.words);
+      off += r.words;
+    }
+  } else {
+    for (const Range& r : ranges)
+      if (r.words) HIP_TRY(c, hipMemcpyAsync(r.dst, r.src, 4 * r.words, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+  }
+  c->pin.up_used = 0;
+  return MPPI_OK;
+}
+
+// Copies n words to the device behind the stream's work; the caller's memory is free when it
+// returns.  Waits for the stream only when the pinned memory is full of earlier uploads.  A
+// stream that is being captured gets the plain copy and its synchronisation, which HIP
+// refuses there.
+mppi_status upload(mppi_ctx* c, void* dst, const void* src, size_t n) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  HIP_TRY(c, hipStreamIsCapturing(c->stream, &cap));
+  if (cap != hipStreamCaptureStatusNone || !c->pin.host || n > kPinnedUpWords) {
+    HIP_TRY(c, hipMemcpyAsync(dst, src, 4 * n, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    return MPPI_OK;
+  }
+  if (c->pin.up_used + n > kPinnedUpWords) {
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    c->pin.up_used = 0;
+  }
+  std::memcpy(c->pin.host + c->pin.up_used, src, 4 * n);
+  CopyArgs a{};
+  a.src[0] = c->pin.dev + c->pin.up_used;
+  a.dst[0] = static_cast<uint32_t*>(dst);
+  a.words[0] = (unsigned)n;
+  HIP_TRY(c, launch_copy(a, c->stream));
+  c->pin.up_used += n;
+  return MPPI_OK;
+}
+
+// The status that the last iteration left, fetched into st.
+mppi_status status_result(mppi_ctx* c, int st) {
   if (st == MPPI_E_NONFINITE) return fail(c, MPPI_E_NONFINITE, "no sample had a finite cost; U unchanged");
   if (st == kStatusTimeoutHost) {
     // the launch left mid-step; the words it wrote hold step numbers below every later
@@ -634,6 +752,13 @@ mppi_status read_status(mppi_ctx* c) {
     return fail(c, MPPI_E_DEVICE, "a multi-step receding launch gave up waiting for another block");
   }
   return MPPI_OK;
+}
+
+// Ranges as fetch, and the status.
+mppi_status fetch_with_status(mppi_ctx* c, Range a, Range b = {nullptr, nullptr, 0}) {
+  int status = 0;
+  mppi_status st = fetch(c, {a, b, {c->d_status, &status, 1}});
+  return st != MPPI_OK ? st : status_result(c, status);
 }
 
 template <class F>
@@ -664,7 +789,7 @@ mppi_status launch_plant(mppi_ctx* c, const float* x_in_dev, const float* u_dev,
 }
 
 // Copies n parameter floats to the device (reallocating when the count changes) and
-// marks the dynamics as set.  Synchronises.
+// marks the dynamics as set.
 mppi_status upload_params(mppi_ctx* c, const float* params, size_t n) {
   if (c->d_params && c->n_params != n) {
     HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -673,8 +798,8 @@ mppi_status upload_params(mppi_ctx* c, const float* params, size_t n) {
   }
   if (!c->d_params) HIP_TRY(c, hipMalloc(&c->d_params, sizeof(float) * n));
   c->n_params = n;
-  HIP_TRY(c, hipMemcpyAsync(c->d_params, params, sizeof(float) * n, hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  mppi_status st = upload(c, c->d_params, params, n);
+  if (st != MPPI_OK) return st;
   c->objective_ready = false;
   c->have_dyn = true;
   return MPPI_OK;
@@ -682,7 +807,7 @@ mppi_status upload_params(mppi_ctx* c, const float* params, size_t n) {
 
 void free_all(mppi_ctx* c) {
   float** bufs[] = {&c->d_U, &c->d_map, &c->d_params, &c->d_decay, &c->d_S, &c->d_D, &c->d_eps, &c->d_part, &c->d_part2,
-                    &c->d_stats, &c->d_sg, &c->d_x, &c->d_u0, &c->d_hist_u, &c->d_hist_x,
+                    &c->d_stats, &c->d_sg, &c->d_x, &c->d_hist_u, &c->d_hist_x,
                     &c->d_ckpt, &c->d_gpart, &c->d_gout, &c->d_gred};
   for (float** b : bufs) {
     if (*b) (void)hipFree(*b);
@@ -703,6 +828,8 @@ void free_all(mppi_ctx* c) {
   c->pending.clear();
   for (auto e : c->event_pool) (void)hipEventDestroy(e);
   c->event_pool.clear();
+  if (c->pin.host) (void)hipHostFree(c->pin.host);
+  c->pin = Pinned{};
 }
 
 }  // namespace
@@ -763,8 +890,9 @@ mppi_status mppi_create(const mppi_config* cfg, const mppi_cost* cost, int devic
       HIP_TRY(c, hipMalloc(&c->d_sync, sizeof(uint64_t) * words));
       HIP_TRY(c, hipMemsetAsync(c->d_sync, 0, sizeof(uint64_t) * words, c->stream));
     }
-    HIP_TRY(c, hipMalloc(&c->d_x, sizeof(float) * kStateDim));
-    HIP_TRY(c, hipMalloc(&c->d_u0, sizeof(float) * 2));
+    HIP_TRY(c, hipMalloc(&c->d_x, sizeof(float) * (kStateDim + 2)));
+    c->d_u0 = c->d_x + kStateDim;
+    pinned_reserve(c->pin, std::min(kPinnedMaxWords, (size_t)c->cfg.K + 2 * (size_t)c->cfg.T + 2048));
     std::vector<float> decay(T + 1);
     for (int t = 0; t <= T; ++t) decay[t] = (float)std::pow((double)cost->crash_decay, (double)t);
     HIP_TRY(c, hipMalloc(&c->d_decay, sizeof(float) * (T + 1)));
@@ -879,10 +1007,8 @@ mppi_status mppi_set_controls(mppi_ctx* c, const float* U) {
     for (int i = 0; i < 2 * c->cfg.T; ++i)
       if (!finite(U[i])) return fail(c, MPPI_E_INVAL, "U[%d] is not finite", i);
     HIP_TRY(c, hipSetDevice(c->device));
-    HIP_TRY(c, hipMemcpyAsync(c->d_U, U, sizeof(float) * 2 * c->cfg.T, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
     c->objective_ready = false;
-    return MPPI_OK;
+    return upload(c, c->d_U, U, 2 * (size_t)c->cfg.T);
   });
 }
 
@@ -896,8 +1022,7 @@ mppi_status mppi_iterate(mppi_ctx* c, const float x0[7], float* costs_out) {
     mppi_status st = enqueue_iteration(c, x0, nullptr);
     if (st != MPPI_OK) return st;
     if (!costs_out) return MPPI_OK;
-    HIP_TRY(c, hipMemcpyAsync(costs_out, c->d_S, sizeof(float) * c->cfg.K, hipMemcpyDeviceToHost, c->stream));
-    return read_status(c);
+    return fetch_with_status(c, {c->d_S, costs_out, (size_t)c->cfg.K});
   });
 }
 
@@ -915,8 +1040,7 @@ mppi_status mppi_get_controls(mppi_ctx* c, float* U_out) {
   return guarded(c, [&]() -> mppi_status {
     if (!U_out) return fail(c, MPPI_E_INVAL, "U_out is NULL");
     HIP_TRY(c, hipSetDevice(c->device));
-    HIP_TRY(c, hipMemcpyAsync(U_out, c->d_U, sizeof(float) * 2 * c->cfg.T, hipMemcpyDeviceToHost, c->stream));
-    return read_status(c);
+    return fetch_with_status(c, {c->d_U, U_out, 2 * (size_t)c->cfg.T});
   });
 }
 
@@ -927,8 +1051,7 @@ mppi_status mppi_shift(mppi_ctx* c, float u0_out[2]) {
     HIP_TRY(c, hipSetDevice(c->device));
     hipLaunchKernelGGL(shift_kernel, dim3(1), dim3(512), 0, c->stream, c->d_U, c->cfg.T, c->d_u0);
     HIP_TRY(c, hipGetLastError());
-    HIP_TRY(c, hipMemcpyAsync(u0_out, c->d_u0, sizeof(float) * 2, hipMemcpyDeviceToHost, c->stream));
-    return read_status(c);
+    return fetch_with_status(c, {c->d_u0, u0_out, 2});
   });
 }
 
@@ -941,14 +1064,12 @@ mppi_status mppi_plant_step(mppi_ctx* c, const float x[7], const float u[2], flo
     float buf[9];
     std::memcpy(buf, x, 7 * sizeof(float));
     std::memcpy(buf + 7, u, 2 * sizeof(float));
-    // the device state buffer d_x (7) and d_u0 (2) are reused as staging
-    HIP_TRY(c, hipMemcpyAsync(c->d_x, buf, 7 * sizeof(float), hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(c->d_u0, buf + 7, 2 * sizeof(float), hipMemcpyHostToDevice, c->stream));
-    mppi_status st = launch_plant(c, c->d_x, c->d_u0, c->d_x, nullptr);
+    // the device state buffer d_x (7 floats) and d_u0 (2), one allocation, are reused as staging
+    mppi_status st = upload(c, c->d_x, buf, 9);
     if (st != MPPI_OK) return st;
-    HIP_TRY(c, hipMemcpyAsync(x_out, c->d_x, 7 * sizeof(float), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    return MPPI_OK;
+    st = launch_plant(c, c->d_x, c->d_u0, c->d_x, nullptr);
+    if (st != MPPI_OK) return st;
+    return fetch(c, {{c->d_x, x_out, 7}});
   });
 }
 
@@ -999,15 +1120,10 @@ mppi_status mppi_run_receding(mppi_ctx* c, const float x0[7], int32_t n_iter, fl
     }
     HIP_TRY(c, hipMemcpyAsync(c->d_x, x0, 7 * sizeof(float), hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, hipMemcpyAsync(c->d_hist_x, x0, 7 * sizeof(float), hipMemcpyHostToDevice, c->stream));
-    int nonfinite = 0;
     mppi_status st = enqueue_receding_steps(c, c->d_x, n_iter, c->d_hist_u, c->d_hist_x + 7);
     if (st != MPPI_OK) return st;
-    if (u_hist && n_iter > 0)
-      HIP_TRY(c, hipMemcpyAsync(u_hist, c->d_hist_u, sizeof(float) * 2 * n_iter, hipMemcpyDeviceToHost, c->stream));
-    if (x_hist)
-      HIP_TRY(c, hipMemcpyAsync(x_hist, c->d_hist_x, sizeof(float) * 7 * (n_iter + 1), hipMemcpyDeviceToHost, c->stream));
-    (void)nonfinite;
-    return read_status(c);
+    return fetch_with_status(c, {c->d_hist_u, u_hist, u_hist ? 2 * (size_t)n_iter : 0},
+                             {c->d_hist_x, x_hist, x_hist ? 7 * (size_t)(n_iter + 1) : 0});
   });
 }
 
@@ -1016,8 +1132,8 @@ mppi_status mppi_get_stats(mppi_ctx* c, float* rho, float* eta, float* delta_out
   return guarded(c, [&]() -> mppi_status {
     HIP_TRY(c, hipSetDevice(c->device));
     std::vector<float> buf(2 + 2 * c->cfg.T);
-    HIP_TRY(c, hipMemcpyAsync(buf.data(), c->d_stats, sizeof(float) * buf.size(), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    mppi_status st = fetch(c, {{c->d_stats, buf.data(), buf.size()}});
+    if (st != MPPI_OK) return st;
     if (rho) *rho = buf[0];
     if (eta) *eta = buf[1];
     if (delta_out) std::memcpy(delta_out, buf.data() + 2, sizeof(float) * 2 * c->cfg.T);
@@ -1051,8 +1167,8 @@ mppi_status mppi_get_iteration(mppi_ctx* c, uint32_t* iter) {
   return guarded(c, [&]() -> mppi_status {
     HIP_TRY(c, hipSetDevice(c->device));
     unsigned v = 0;
-    HIP_TRY(c, hipMemcpyAsync(&v, c->d_iter, sizeof(unsigned), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    mppi_status st = fetch(c, {{c->d_iter, &v, 1}});
+    if (st != MPPI_OK) return st;
     c->iter = v;
     *iter = v;
     return MPPI_OK;
@@ -1103,9 +1219,7 @@ mppi_status mppi_iterate_partial(mppi_ctx* c, const float x0[7], float* row_dev,
     HIP_TRY(c, hipSetDevice(c->device));
     mppi_status st = enqueue_iteration(c, x0, nullptr, false, nullptr, nullptr, row_dev);
     if (st != MPPI_OK || !costs_out) return st;
-    HIP_TRY(c, hipMemcpyAsync(costs_out, c->d_S, sizeof(float) * c->cfg.K, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    return MPPI_OK;
+    return fetch(c, {{c->d_S, costs_out, (size_t)c->cfg.K}});
   });
 }
 
@@ -1216,9 +1330,7 @@ mppi_status mppi_objective(mppi_ctx* c, const float x0[7], uint32_t iter, int32_
       c->pending.push_back(pt);
     }
     float st2[2];
-    HIP_TRY(c, hipMemcpyAsync(st2, c->d_stats, sizeof(float) * 2, hipMemcpyDeviceToHost, c->stream));
-    if (costs_out) HIP_TRY(c, hipMemcpyAsync(costs_out, c->d_S, sizeof(float) * K, hipMemcpyDeviceToHost, c->stream));
-    mppi_status st = read_status(c);
+    mppi_status st = fetch_with_status(c, {c->d_stats, st2, 2}, {c->d_S, costs_out, costs_out ? (size_t)K : 0});
     if (st != MPPI_OK) return st;
     if (J_out) *J_out = (double)st2[0] - (double)c->cfg.lambda * std::log((double)st2[1] / (double)K);
     c->objective_ready = true;
@@ -1286,8 +1398,8 @@ mppi_status mppi_objective_backward(mppi_ctx* c, float* dJdU, float* dJdtheta) {
                        c->d_gred, R, T, c->d_stats, r.gcs0, r.gcs1, c->d_gout);
     HIP_TRY(c, hipGetLastError());
     std::vector<float> out(stride);
-    HIP_TRY(c, hipMemcpyAsync(out.data(), c->d_gout, sizeof(float) * stride, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    mppi_status st = fetch(c, {{c->d_gout, out.data(), stride}});
+    if (st != MPPI_OK) return st;
     if (dJdtheta) std::memcpy(dJdtheta, out.data(), sizeof(float) * kNP32Host);
     if (dJdU) std::memcpy(dJdU, out.data() + kNP32Host, sizeof(float) * 2 * T);
     return MPPI_OK;
@@ -1331,6 +1443,12 @@ struct mppi_batch {
   RolloutArgs* d_args = nullptr;
   int2* d_items = nullptr;
   unsigned* d_queue = nullptr;           // [2]: next work item, blocks that have found the queue empty
+  // Every instance's U ([Uoff.back()] floats) and status ([n]) in pinned host memory, written
+  // by the launches beside d_U and d_status; null where it could not be had.
+  float* h_U = nullptr;
+  int* h_status = nullptr;
+  float* hd_U = nullptr;                 // their device addresses
+  int* hd_status = nullptr;
   int n_items = 0;
   int H = 0, W = 0;
   float ox = 0, oy = 0, res = 1;
@@ -1376,6 +1494,8 @@ void batch_free(mppi_batch* b) {
                   b->d_decay, b->d_x0, b->d_iter, b->d_map, b->d_params, b->d_args, b->d_items, b->d_queue};
   for (void* p : bufs)
     if (p) (void)hipFree(p);
+  if (b->h_U) (void)hipHostFree(b->h_U);
+  b->h_U = nullptr;
 }
 
 // Per-instance launch arguments (device pointers into the batch's shared buffers).
@@ -1397,6 +1517,8 @@ std::vector<RolloutArgs> batch_args(const mppi_batch* b) {
     a.Uout = b->d_U + b->Uoff[i];
     a.stats = b->d_stats + b->soff[i];
     a.status = b->d_status + i;
+    a.U_host = b->hd_U ? b->hd_U + b->Uoff[i] : nullptr;
+    a.status_host = b->hd_status ? b->hd_status + i : nullptr;
     a.G = b->G[i];
     a.sg_window = b->cfg.sg_window;
     a.update_U = 1;
@@ -1540,6 +1662,7 @@ mppi_status batch_autotune(mppi_batch* b) {
   std::vector<int2> items = batch_items(b, best_order);
   BHIP_TRY(b, hipMemcpy(b->d_items, items.data(), sizeof(int2) * items.size(), hipMemcpyHostToDevice));
   BHIP_TRY(b, hipMemcpy(b->d_U, U0.data(), sizeof(float) * nU, hipMemcpyHostToDevice));
+  if (b->h_U) std::memcpy(b->h_U, U0.data(), sizeof(float) * nU);
   BHIP_TRY(b, hipMemcpy(b->d_iter, it0.data(), sizeof(unsigned) * b->n, hipMemcpyHostToDevice));
   b->grid = best_grid;
   b->order = best_order;
@@ -1653,6 +1776,18 @@ mppi_status mppi_batch_create(const mppi_config* cfg, const mppi_cost* cost, int
     b->n_items = items;
     BHIP_TRY(b, hipMalloc(&b->d_U, sizeof(float) * u));
     BHIP_TRY(b, hipMemset(b->d_U, 0, sizeof(float) * u));
+    void *h = nullptr, *hd = nullptr;
+    if (hipHostMalloc(&h, sizeof(float) * (u + n), hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
+        hipHostGetDevicePointer(&hd, h, 0) == hipSuccess) {
+      b->h_U = static_cast<float*>(h);
+      b->h_status = reinterpret_cast<int*>(b->h_U + u);
+      b->hd_U = static_cast<float*>(hd);
+      b->hd_status = reinterpret_cast<int*>(b->hd_U + u);
+      std::memset(h, 0, sizeof(float) * (u + n));
+    } else {   // results are then copied by command
+      (void)hipGetLastError();
+      if (h) (void)hipHostFree(h);
+    }
     BHIP_TRY(b, hipMalloc(&b->d_S, sizeof(float) * s));
     BHIP_TRY(b, hipMalloc(&b->d_part, sizeof(float) * p));
     BHIP_TRY(b, hipMalloc(&b->d_part2, sizeof(float) * p2));
@@ -1746,6 +1881,7 @@ mppi_status mppi_batch_set_controls(mppi_batch* b, int32_t i, const float* U) {
   BHIP_TRY(b, hipSetDevice(b->device));
   BHIP_TRY(b, hipMemcpyAsync(b->d_U + b->Uoff[i], U, sizeof(float) * 2 * b->T[i], hipMemcpyHostToDevice, b->stream));
   BHIP_TRY(b, hipStreamSynchronize(b->stream));
+  if (b->h_U) std::memcpy(b->h_U + b->Uoff[i], U, sizeof(float) * 2 * b->T[i]);
   return MPPI_OK;
 }
 
@@ -1766,6 +1902,12 @@ mppi_status mppi_batch_get_controls(mppi_batch* b, int32_t i, float* U_out) {
   if (!b || !U_out || i < 0 || i >= b->n) return b ? bfail(b, MPPI_E_INVAL, "bad instance or U_out") : MPPI_E_INVAL;
   BHIP_TRY(b, hipSetDevice(b->device));
   int st = 0;
+  if (b->h_U) {
+    BHIP_TRY(b, hipStreamSynchronize(b->stream));
+    std::memcpy(U_out, b->h_U + b->Uoff[i], sizeof(float) * 2 * b->T[i]);
+    st = b->h_status[i];
+    return st == MPPI_E_NONFINITE ? bfail(b, MPPI_E_NONFINITE, "instance %d: no finite cost", i) : MPPI_OK;
+  }
   BHIP_TRY(b, hipMemcpyAsync(U_out, b->d_U + b->Uoff[i], sizeof(float) * 2 * b->T[i], hipMemcpyDeviceToHost, b->stream));
   BHIP_TRY(b, hipMemcpyAsync(&st, b->d_status + i, sizeof(int), hipMemcpyDeviceToHost, b->stream));
   BHIP_TRY(b, hipStreamSynchronize(b->stream));

@@ -88,6 +88,10 @@ struct RolloutArgs {
   float* Uout;             // [T][2], updated in place by the last block
   float* stats;            // [2 + 2T]: rho, eta~, Delta[T][2]
   int* status;             // 0 or MPPI_E_NONFINITE for this iteration
+  // Batched form (nullable): where the final stage also writes an instance's U and status
+  // in pinned host memory.
+  float* U_host;
+  int* status_host;
   int G;                   // rollout blocks of this launch
   int sg_window;
   int update_U;            // 0: weights and Delta only (objective evaluation)
@@ -132,6 +136,14 @@ struct RolloutArgs {
   unsigned step_base;
   uint64_t* sync;
   unsigned spin_limit;   // polls of one wait before the launch gives up (0: 1 << 20)
+};
+
+// Up to three ranges of 4-byte words copied by one launch.
+constexpr int kCopyRanges = 3;
+struct CopyArgs {
+  const uint32_t* src[kCopyRanges];
+  uint32_t* dst[kCopyRanges];
+  unsigned words[kCopyRanges];
 };
 
 constexpr int kCkptStride = 8;   // floats per checkpointed state (7 + pad)
