@@ -54,7 +54,8 @@
 // exchange.  Replaced: a merger per group of 16 rows (each row written, waited for and
 // flagged, the group row likewise, and all 15 group rows merged again by every rollout
 // block): 32.0 -> 29.8 us per paper-shaped step (basis-function model 28.9 -> 26.2); with the
-// cost waves' scans in 64 bits 29.4 (26.0).
+// cost waves' scans in 64 bits 29.4 (26.0), with the chain's loop where the compiler puts it
+// now 28.6 (25.8; its place is worth up to 1 us).
 #include "wave_common.hip.h"
 
 namespace mppi {
@@ -78,6 +79,14 @@ constexpr bool plant_layout_fits() {
   return (7 * 32) % 4 == 0 && (8 * 32 + 32 * 32) % 4 == 0;
 }
 static_assert(plant_layout_fits(), "the plant layout must permute the 6-32-32-4 parameter vector");
+
+// The chain's network constants in LDS, in the order in which a chain lane holds them
+// (lane 16 r + col, kChainRow words each, read as 16-byte words; scaled): wP[16], wQ[16],
+// w1[6], bb1, the layer-2 bias, wKA, wSA, wKB, wSB, bKA.  kChainRow / 4 is odd, so that the
+// lanes' 16-byte reads fall on different banks.
+constexpr int kChainRow = 52;
+constexpr int kChainW1 = 32, kChainB1 = 38, kChainB2 = 39, kChainW3 = 40, kChainB3 = 44;
+constexpr int kChainWords = 32 * kChainRow;
 
 namespace {
 
@@ -133,9 +142,10 @@ __device__ __forceinline__ void step_controls(const RolloutArgs& a, float u0, fl
 }
 
 // Every block draws the noise of all its samples and steps for iteration `iter` into sE
-// (one (slot, t) pair per thread at a time).
+// (one (slot, t) pair per thread at a time, then passed to `then`).
+template <class F>
 __device__ __forceinline__ void draw_block_noise(const RolloutArgs& a, uint32_t iter, int kb, int T, int eStride,
-                                                 float* sE) {
+                                                 float* sE, F&& then) {
   NoiseKey nk = a.nk;
   nk.iter = iter;
   for (int i = threadIdx.x; i < kWaveSlots * T; i += kSplitBlock) {
@@ -146,6 +156,7 @@ __device__ __forceinline__ void draw_block_noise(const RolloutArgs& a, uint32_t 
     draw_eps<false>((uint32_t)t, (uint32_t)(kb + slot), nk, e0, e1);
     sE[slot * eStride + 2 * t] = e0;
     sE[slot * eStride + 2 * t + 1] = e1;
+    then(slot, t, e0, e1);
   }
 }
 
@@ -322,7 +333,7 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
   constexpr bool kNet = MODEL == kModelNet;
   extern __shared__ float smem[];
   __shared__ unsigned s_abort;
-  __shared__ float s_xn[kStateDim];                  // multi-step: the next step's plant state
+  __shared__ float s_xn[kStateDim];                  // the step's plant state (multi-step: then the next step's)
   const int T = a.T;
   const int T4 = (T + 4) & ~3;
   const int eStride = (2 * T + 3) & ~3;
@@ -336,7 +347,8 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
   unsigned* sFlag = reinterpret_cast<unsigned*>(sX + kWaveSlots * T4 * 8);   // [4] chain progress, [4] spare
   float* sS = reinterpret_cast<float*>(sFlag + 8);   // [8] costs
   float* sB = sS + 8;                                // basis model: [8][T][8] control terms
-  float* sP = sB + (kNet ? 0 : kWaveSlots * T * 8);  // multi-step: the model's parameters (the plant step)
+  float* sC = sB + (kNet ? 0 : kWaveSlots * T * 8);  // network: the chain's constants
+  float* sP = sC + (kNet ? kChainWords : 0);         // basis model, multi-step: the parameters (the plant step)
   // after both roles: the block's N row (the clamped controls or the basis terms are no
   // longer read) and the merge's working row (the states are no longer read)
   float* N_lds = kNet ? sV : sB;
@@ -369,41 +381,82 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
   float* myX = sX + slot * T4 * 8;
   unsigned* chainCnt = sFlag + pair;
 
-  // ---- the chain's network constants, kept in registers over every step -------------
-  const float* W1 = a.params;
-  const float* b1 = W1 + HID * 6;
-  const float* W2 = b1 + HID;
-  const float* b2 = W2 + HID * HID;
-  const float* W3 = b2 + HID;
-  const float* b3 = W3 + 4 * HID;
-  const int j = 16 * r + col;
-  const bool cn = chain && kNet;
-  // layers 1 and 2 form tanh's argument already multiplied by 2 log2(e)
-  float w1[6];
-#pragma unroll
-  for (int i = 0; i < 6; ++i) w1[i] = cn ? kTanhScale * W1[j * 6 + i] : 0.0f;
-  const float bb1 = cn ? kTanhScale * b1[j] : 0.0f;
-  float wP[16], wQ[16];
-  int src[16];
-  src[0] = col;
-  src[1] = ror_src<1>(col);   src[2] = ror_src<2>(col);   src[3] = ror_src<3>(col);
-  src[4] = ror_src<4>(col);   src[5] = ror_src<5>(col);   src[6] = ror_src<6>(col);
-  src[7] = ror_src<7>(col);   src[8] = ror_src<8>(col);   src[9] = ror_src<9>(col);
-  src[10] = ror_src<10>(col); src[11] = ror_src<11>(col); src[12] = ror_src<12>(col);
-  src[13] = ror_src<13>(col); src[14] = ror_src<14>(col); src[15] = ror_src<15>(col);
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    wP[q] = cn ? kTanhScale * W2[col * HID + 16 * r + src[q]] : 0.0f;
-    wQ[q] = cn ? kTanhScale * W2[(16 + col) * HID + 16 * r + src[q]] : 0.0f;
+  // ---- the launch's inputs: every load is issued at once, the ones that the draws and the
+  // controls need first.  The network's weights pass through LDS in the order in which a
+  // chain lane holds them.  Read from global memory by the chain lanes, each load waited for
+  // by itself before the draws, the chain began 4.9 us into the launch at T <= 64 and 5.4 at
+  // T = 100; now 2.6 and 3.4.
+  // (Absent inputs are read from the parameters' addresses, so that no load is in a branch.)
+  const uint32_t* iter_p = a.iter_dev ? a.iter_dev : reinterpret_cast<const uint32_t*>(a.params);
+  const uint32_t iter_in = __hip_atomic_load(iter_p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const float u_in = a.U[min(tid, 2 * T - 1)];   // 2T <= 256
+  float x_in = load_through((a.x0_dev ? a.x0_dev : a.params) + min(tid, kStateDim - 1));
+  constexpr int kRest = kSplitParams - HID * HID;   // W1, b1 and, behind W2, b2, W3, b3
+  constexpr int oW2 = 7 * HID, oB2 = oW2, oW3 = oB2 + HID, oB3 = oW3 + 4 * HID;   // of the parameters; of the rest
+  float w2a = 0.0f, w2b = 0.0f, rest = 0.0f;
+  if constexpr (kNet) {
+    w2a = a.params[oW2 + tid];                   // W2[n][i], 32 n + i = tid
+    w2b = a.params[oW2 + kSplitBlock + tid];     // W2[n + 16][i]
+    rest = a.params[tid < oB2 ? tid : min(tid, kRest - 1) + HID * HID];
   }
-  const float bP = (cn && r == 0) ? kTanhScale * b2[col] : 0.0f;
-  const float bQ = (cn && r == 1) ? kTanhScale * b2[16 + col] : 0.0f;
-  // layer 3 times dt as a reduce-scatter over each quad (see the wave kernel)
-  const float wKA = cn ? a.dt * W3[comp * HID + j] : 0.0f;
-  const float wKB = cn ? a.dt * W3[(comp ^ 2) * HID + j] : 0.0f;
-  const float wSA = cn ? a.dt * W3[(comp ^ 1) * HID + j] : 0.0f;
-  const float wSB = cn ? a.dt * W3[(comp ^ 3) * HID + j] : 0.0f;
-  const float bKA = (cn && c32 < 4) ? a.dt * b3[comp] : 0.0f;
+  if (!a.x0_dev) x_in = a.x0[min(tid, kStateDim - 1)];
+  // the device counter is advanced by the final merge
+  const uint32_t iter0 = a.iter_dev ? (uint32_t)__builtin_amdgcn_readfirstlane((int)iter_in) : a.nk.iter;
+  if (tid < 2 * T) sU[tid] = u_in;
+  if (tid < kStateDim) s_xn[tid] = x_in;
+  if (tid < 2 * kSplitPairs) sFlag[tid] = 0u;
+  if (tid == 0) s_abort = 0u;
+  __syncthreads();
+  // the noise of every sample and step, and (a single step) the controls with it
+  draw_block_noise(a, iter0, kb, T, eStride, sE, [&](int sl, int t, float e0, float e1) {
+    if constexpr (!MULTI)
+      step_controls<MODEL>(a, sU[2 * t], sU[2 * t + 1], e0, e1, kb + sl >= a.K_imp, sV + sl * eStride + 2 * t,
+                           sB + sl * T * 8 + 8 * t);
+  });
+  if constexpr (!MULTI)
+    if (tid < kWaveSlots * 4) sX[(tid >> 2) * T4 * 8 + (tid & 3)] = s_xn[3 + (tid & 3)];
+  if constexpr (kNet) {
+    // W2[n][16 r + s] is lane 16 r + (n & 15)'s weight of the rotation by (n - s) & 15;
+    // layers 1 and 2 form tanh's argument already multiplied by 2 log2(e)
+    float* w2 = sC + ((tid & 16) + (tid >> 5)) * kChainRow + (((tid >> 5) - tid) & 15);
+    w2[0] = kTanhScale * w2a;
+    w2[16] = kTanhScale * w2b;
+    if (tid < oB2) {
+      const int l = tid < 6 * HID ? tid / 6 : tid - 6 * HID;
+      sC[l * kChainRow + (tid < 6 * HID ? kChainW1 + tid - 6 * l : kChainB1)] = kTanhScale * rest;
+    } else if (tid < oW3) {
+      sC[(tid - oB2) * kChainRow + kChainB2] = kTanhScale * rest;
+    } else if (tid < kRest) {   // layer 3 times dt: W3[o][l] is lane l's weight number o ^ (l & 3)
+      const int e = tid - oW3, l = tid < oB3 ? e & 31 : e - 4 * HID;
+      sC[l * kChainRow + (tid < oB3 ? kChainW3 + ((e >> 5) ^ (l & 3)) : kChainB3)] = a.dt * rest;
+    }
+  }
+  if constexpr (MULTI || !kNet)   // the plant step's copy of the parameters (a network in its plant layout)
+    for (int i = tid; i < (kNet ? kSplitParams : kSplitBasisParams); i += kSplitBlock)
+      sP[kNet ? plant_layout_index(i, HID) : i] = a.params[i];
+  __syncthreads();
+
+  // ---- the chain's constants, kept in registers over every step ----------------------
+  float w1[6] = {}, wP[16] = {}, wQ[16] = {};
+  float bb1 = 0.0f, bP = 0.0f, bQ = 0.0f, wKA = 0.0f, wKB = 0.0f, wSA = 0.0f, wSB = 0.0f, bKA = 0.0f;
+  if (kNet && chain) {
+    const float* c = sC + c32 * kChainRow;
+    const auto c4 = [&](int i) { return *reinterpret_cast<const float4*>(c + i); };
+#pragma unroll
+    for (int q = 0; q < 16; q += 4) {
+      const float4 p = c4(q), v = c4(16 + q);
+      wP[q] = p.x; wP[q + 1] = p.y; wP[q + 2] = p.z; wP[q + 3] = p.w;
+      wQ[q] = v.x; wQ[q + 1] = v.y; wQ[q + 2] = v.z; wQ[q + 3] = v.w;
+    }
+    const float4 p = c4(kChainW1), v = c4(kChainW1 + 4), w = c4(kChainW3);
+    w1[0] = p.x; w1[1] = p.y; w1[2] = p.z; w1[3] = p.w; w1[4] = v.x; w1[5] = v.y;
+    bb1 = v.z;
+    bP = r == 0 ? v.w : 0.0f;
+    bQ = r == 1 ? v.w : 0.0f;
+    // layer 3 as a reduce-scatter over each quad (see the wave kernel)
+    wKA = w.x; wSA = w.y; wKB = w.z; wSB = w.w;
+    bKA = c32 < 4 ? c[kChainB3] : 0.0f;
+  }
   // basis-function model: this lane's column of Theta with each normaliser folded in
   constexpr int kRaw = 21;
   constexpr int kRawIdx[kRaw] = {1, 2, 3, 4, 5, 6, 7, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18, 19, 20, 21, 22};
@@ -413,17 +466,11 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
                                      1.0f / (1400.0f * 1400.0f * 1400.0f), 1.0f / 40.0f,
                                      1.0f / (40.0f * 40.0f), 1.0f / (40.0f * 40.0f * 40.0f), 1.0f / 50.0f,
                                      1.0f, 1.0f, 1.0f / 3.0f, 0.2f, 0.01f, 0.001f};
-  float kc[kRaw];
+  float kc[kRaw] = {};
+  if (!kNet && chain) {
 #pragma unroll
-  for (int i = 0; i < kRaw; ++i) kc[i] = (chain && !kNet) ? a.params[kRawIdx[i] * 4 + comp] * kRawScale[i] : 0.0f;
-
-  const uint32_t iter0 = a.iter_dev ? *a.iter_dev : a.nk.iter;   // the device counter, advanced by the final merge
-  if (tid < 2 * kSplitPairs) sFlag[tid] = 0u;
-  if (tid == 0) s_abort = 0u;
-  if constexpr (MULTI)   // the plant step's copy of the parameters (a network in its plant layout)
-    for (int i = tid; i < (kNet ? kSplitParams : kSplitBasisParams); i += kSplitBlock)
-      sP[kNet ? plant_layout_index(i, HID) : i] = a.params[i];
-  draw_block_noise(a, iter0, kb, T, eStride, sE);
+    for (int i = 0; i < kRaw; ++i) kc[i] = sP[kRawIdx[i] * 4 + comp] * kRawScale[i];
+  }
   if (chain) __builtin_amdgcn_s_setprio(2);
 
   for (int step = 0; step < n_steps; ++step) {
@@ -432,22 +479,20 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
     const uint32_t iter = iter0 + (uint32_t)step;
     float* const u0_out = (as.u0_out && MULTI) ? as.u0_out + 2 * step : as.u0_out;
     float* const x_copy = (as.x_copy && MULTI) ? as.x_copy + kStateDim * step : as.x_copy;
-    // ---- this step's U and plant state: from global memory at the first step, from the
-    // block's own final stage of the previous step after that ------------------------------
-    if (step == 0)
-      for (int i = tid; i < 2 * T; i += kSplitBlock) sU[i] = as.U[i];
+    // this step's U (sU) and plant state: the launch's, then the block's own final stage's
     float x0v[kStateDim];
 #pragma unroll
-    for (int i = 0; i < kStateDim; ++i) x0v[i] = step > 0 ? s_xn[i] : (as.x0_dev ? as.x0_dev[i] : as.x0[i]);
-    __syncthreads();
-    // the controls of every sample and step; the state entry 0 of every sample
-    for (int i = tid; i < kWaveSlots * T; i += kSplitBlock) {
-      const int sl = i / T, t = i - sl * T;
-      step_controls<MODEL>(as, sU[2 * t], sU[2 * t + 1], sE[sl * eStride + 2 * t], sE[sl * eStride + 2 * t + 1],
-                           kb + sl >= as.K_imp, sV + sl * eStride + 2 * t, sB + sl * T * 8 + 8 * t);
+    for (int i = 0; i < kStateDim; ++i) x0v[i] = s_xn[i];
+    if constexpr (MULTI) {
+      // the controls of every sample and step; the state entry 0 of every sample
+      for (int i = tid; i < kWaveSlots * T; i += kSplitBlock) {
+        const int sl = i / T, t = i - sl * T;
+        step_controls<MODEL>(as, sU[2 * t], sU[2 * t + 1], sE[sl * eStride + 2 * t], sE[sl * eStride + 2 * t + 1],
+                             kb + sl >= as.K_imp, sV + sl * eStride + 2 * t, sB + sl * T * 8 + 8 * t);
+      }
+      if (tid < kWaveSlots * 4) sX[(tid >> 2) * T4 * 8 + (tid & 3)] = x0v[3 + (tid & 3)];
+      __syncthreads();
     }
-    if (tid < kWaveSlots * 4) sX[(tid >> 2) * T4 * 8 + (tid & 3)] = x0v[3 + (tid & 3)];
-    __syncthreads();
 
     if (chain) {
       // ---- chain wave ----------------------------------------------------------------
@@ -465,10 +510,6 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
       float* xs = myX + ((lane & 4) ? 4 + comp : 8 + comp);
       for (int c = 0; c < nch; ++c) {
         const int t1 = r0 + 32 * c;
-        // multi-step: the step loop on a 64-byte boundary (where it lands is worth 0.9 us per
-        // paper-shaped step): a boundary, 13 no-ops and the three instructions that enter the
-        // loop.  In a single-step launch the no-ops cost 0.3 us and the boundary gives nothing.
-        if constexpr (MULTI) asm volatile(".p2align 6\n\t.fill 13, 4, 0xbf800000");
         for (int t = c > 0 ? t1 - 32 : 0; t < t1; ++t) {
           const int tn = min(t + 1, T - 1);
           float y;   // dt * f of the lane's component
@@ -691,7 +732,7 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
       fs.prefetch_local(as, sU, x0v);
       __syncthreads();   // the block's noise and costs are no longer read
       // the next step's noise does not depend on its U: drawn while the merge completes
-      if (step + 1 < n_steps) draw_block_noise(as, iter + 1u, kb, T, eStride, sE);
+      if (step + 1 < n_steps) draw_block_noise(as, iter + 1u, kb, T, eStride, sE, [](int, int, float, float) {});
       float rho_m = 0.0f, eta_m = 0.0f;
       if (tid < 256) {   // whole waves: every thread of a column polls its own word and its line's head
         const uint64_t* src = as.sync + (size_t)(as.G + (int)(blockIdx.x % kMergeCopies)) * M * LW;
@@ -739,7 +780,7 @@ size_t wave_split_smem_bytes(int T, int model) {
   const size_t e = (size_t)((2 * T + 3) & ~3);
   const size_t T4 = (size_t)((T + 4) & ~3);
   const size_t v = model == kModelNet ? (size_t)kWaveSlots * e : 0;
-  const size_t basis = model == kModelBasis ? (size_t)kWaveSlots * T * 8 : 0;
+  const size_t basis = model == kModelBasis ? (size_t)kWaveSlots * T * 8 : (size_t)kChainWords;
   return sizeof(float) * (e + kWaveSlots * e + v + (size_t)kWaveSlots * T4 * 8 + 8 + 8 + basis + kSplitParams);
 }
 
