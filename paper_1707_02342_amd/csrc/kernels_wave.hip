@@ -45,9 +45,9 @@ namespace mppi {
 // Waves per SIMD: with its 64-bit sums the compiler's own choice is one less than the bound
 // here (137 and 210 registers), which costs more than the few registers that then spill:
 // K = 6001, T = 150 124 -> 110 us (114 with error-free FP32 sums), K = 8192, T = 100 85 -> 82.
+// With the weights staged through LDS (ChainStage) 105 and 78, K = 4096, T = 100 55 -> 51.5.
 template <int HID, int NQ, int MODEL>
 __global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kernel(RolloutArgs a) {
-  if (a.iter_dev) a.nk.iter = *a.iter_dev;   // the device counter, advanced by the final merge
   static_assert(HID == 32, "the wave schedule maps 32 hidden units onto 32 lanes");
   extern __shared__ float smem[];
   // Up to 128 steps (NQ = 4) the chain stores the uncompensated state hi_t and each
@@ -84,47 +84,26 @@ __global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kern
   float* myV = sV + slot * eStride;
   float4* myX = reinterpret_cast<float4*>(sX + slot * T4 * kXW);   // [T4] (NQ = 8) or [T4][2] (hi, y)
 
-  for (int i = threadIdx.x; i < 2 * T; i += kWaveBlock) sU[i] = a.U[i];
-
-  // ---- per-lane network constants (network model only: with the basis-function
-  // model params holds Theta, and none of these is read) --------------------------
+  // ---- the launch's inputs: every load is issued at once, the ones that the draws and the
+  // controls need first.  (Absent inputs are read from the parameters' addresses, so that no
+  // load is in a branch.)
   constexpr bool kNet = MODEL == kModelNet;
-  const float* W1 = a.params;
-  const float* b1 = W1 + HID * 6;
-  const float* W2 = b1 + HID;
-  const float* b2 = W2 + HID * HID;
-  const float* W3 = b2 + HID;
-  const float* b3 = W3 + 4 * HID;
-  const int j = 16 * r + col;
-  // layers 1 and 2 form tanh's argument already multiplied by 2 log2(e)
-  float w1[6];
+  constexpr int kURegs = (64 * NQ + kWaveBlock - 1) / kWaveBlock;   // 2T <= 64 NQ
+  const int tid = threadIdx.x;
+  const uint32_t* iter_p = a.iter_dev ? a.iter_dev : reinterpret_cast<const uint32_t*>(a.params);
+  const uint32_t iter_in = __hip_atomic_load(iter_p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  float u_in[kURegs];
 #pragma unroll
-  for (int i = 0; i < 6; ++i) w1[i] = kNet ? kTanhScale * W1[j * 6 + i] : 0.0f;
-  const float bb1 = kNet ? kTanhScale * b1[j] : 0.0f;
-  float wP[16], wQ[16];
-  int src[16];
-  src[0] = col;
-  src[1] = ror_src<1>(col);   src[2] = ror_src<2>(col);   src[3] = ror_src<3>(col);
-  src[4] = ror_src<4>(col);   src[5] = ror_src<5>(col);   src[6] = ror_src<6>(col);
-  src[7] = ror_src<7>(col);   src[8] = ror_src<8>(col);   src[9] = ror_src<9>(col);
-  src[10] = ror_src<10>(col); src[11] = ror_src<11>(col); src[12] = ror_src<12>(col);
-  src[13] = ror_src<13>(col); src[14] = ror_src<14>(col); src[15] = ror_src<15>(col);
+  for (int i = 0; i < kURegs; ++i) u_in[i] = a.U[min(tid + i * kWaveBlock, 2 * T - 1)];
+  ChainStage<kWaveBlock> stage;
+  if constexpr (kNet) stage.load(a.params);
+  // the device counter is advanced by the final merge
+  if (a.iter_dev) a.nk.iter = (uint32_t)__builtin_amdgcn_readfirstlane((int)iter_in);
 #pragma unroll
-  for (int s = 0; s < 16; ++s) {
-    wP[s] = kNet ? kTanhScale * W2[col * HID + 16 * r + src[s]] : 0.0f;
-    wQ[s] = kNet ? kTanhScale * W2[(16 + col) * HID + 16 * r + src[s]] : 0.0f;
-  }
-  const float bP = (kNet && r == 0) ? kTanhScale * b2[col] : 0.0f;
-  const float bQ = (kNet && r == 1) ? kTanhScale * b2[16 + col] : 0.0f;
-  // layer 3 times dt, as a reduce-scatter over each quad with the weights placed per lane:
-  // lane L keeps output oA = L & 3 (its final one) and oB = oA ^ 2 (passed on in the second
-  // exchange), and sends outputs oA ^ 1 and oA ^ 3 to its partner L ^ 1, whose oA and oB they
-  // are; dt b3 enters once per output, in the lanes 0..3 of each sample
-  const float wKA = kNet ? a.dt * W3[comp * HID + j] : 0.0f;
-  const float wKB = kNet ? a.dt * W3[(comp ^ 2) * HID + j] : 0.0f;
-  const float wSA = kNet ? a.dt * W3[(comp ^ 1) * HID + j] : 0.0f;
-  const float wSB = kNet ? a.dt * W3[(comp ^ 3) * HID + j] : 0.0f;
-  const float bKA = (kNet && c32 < 4) ? a.dt * b3[comp] : 0.0f;
+  for (int i = 0; i < kURegs; ++i)
+    if (tid + i * kWaveBlock < 2 * T) sU[tid + i * kWaveBlock] = u_in[i];
+  __syncthreads();
+
   // basis-function model: this lane's column of Theta with each basis function's
   // normaliser folded in (the chain multiplies raw products such as sin(u_delta) tan(alpha_f))
   constexpr int kRaw = 21;
@@ -165,7 +144,7 @@ __global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kern
       myE[2 * t + 1] = eb[i];
       if constexpr (kNetV) {
         // g(v) of the step (v = u + eps, or eps for an exploration sample), for the chain
-        const float u0 = a.U[2 * t], u1 = a.U[2 * t + 1];
+        const float u0 = sU[2 * t], u1 = sU[2 * t + 1];
         myV[2 * t] = fminf(fmaxf(zm ? ea[i] : u0 + ea[i], a.u_lo0), a.u_hi0);
         myV[2 * t + 1] = fminf(fmaxf(zm ? eb[i] : u1 + eb[i], a.u_lo1), a.u_hi1);
       }
@@ -180,7 +159,7 @@ __global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kern
     for (int i = 0; i < NQ; ++i) {
       const int t = 32 * i + c32;
       if (i < NT && t < T) {
-        const float u0 = a.U[2 * t], u1 = a.U[2 * t + 1];
+        const float u0 = sU[2 * t], u1 = sU[2 * t + 1];
         const float vc0 = fminf(fmaxf(zm ? ea[i] : u0 + ea[i], a.u_lo0), a.u_hi0);
         const float vc1 = fminf(fmaxf(zm ? eb[i] : u1 + eb[i], a.u_lo1), a.u_hi1);
         const float sd = sinf(vc0);
@@ -199,6 +178,19 @@ __global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kern
       }
     }
   }
+  // the network's constants, staged where the states go
+  ChainWeights cw;
+  if constexpr (kNet) {
+    stage.store(sX, a.dt);
+    __syncthreads();
+    cw.read(sX, c32);
+    __syncthreads();
+  }
+  const auto& w1 = cw.w1;
+  const auto& wP = cw.wP;
+  const auto& wQ = cw.wQ;
+  const float bb1 = cw.bb1, bP = cw.bP, bQ = cw.bQ;
+  const float wKA = cw.wKA, wKB = cw.wKB, wSA = cw.wSA, wSB = cw.wSB, bKA = cw.bKA;
   float xh = x0v[3 + comp];           // the FP32 running sum hi_t that the network reads
   double xd = xh;                     // NQ = 8: the state's exact sum, kept by the chain
   if (c32 < 4) sX[slot * T4 * kXW + c32] = x0v[3 + c32];
@@ -530,7 +522,8 @@ size_t wave_smem_bytes(int T, int model) {
   const size_t x = (size_t)kWaveSlots * T4 * (defer ? 8 : 4);
   const size_t red = defer ? 0 : 4 * e;
   const size_t basis = model == kModelBasis ? (size_t)kWaveSlots * T * 8 : 0;
-  return sizeof(float) * (e + kWaveSlots * e + v + x + red + 16 + basis);
+  const size_t behind = x + red + 16 + basis;   // the chain's constants pass through here
+  return sizeof(float) * (e + kWaveSlots * e + v + (behind > kChainWords ? behind : (size_t)kChainWords));
 }
 
 }  // namespace mppi

@@ -55,7 +55,7 @@
 // flagged, the group row likewise, and all 15 group rows merged again by every rollout
 // block): 32.0 -> 29.8 us per paper-shaped step (basis-function model 28.9 -> 26.2); with the
 // cost waves' scans in 64 bits 29.4 (26.0), with the chain's loop where the compiler puts it
-// now 28.6 (25.8; its place is worth up to 1 us).
+// 28.6 (25.8), with four steps per turn of that loop 28.0 (24.0).
 #include "wave_common.hip.h"
 
 namespace mppi {
@@ -79,14 +79,6 @@ constexpr bool plant_layout_fits() {
   return (7 * 32) % 4 == 0 && (8 * 32 + 32 * 32) % 4 == 0;
 }
 static_assert(plant_layout_fits(), "the plant layout must permute the 6-32-32-4 parameter vector");
-
-// The chain's network constants in LDS, in the order in which a chain lane holds them
-// (lane 16 r + col, kChainRow words each, read as 16-byte words; scaled): wP[16], wQ[16],
-// w1[6], bb1, the layer-2 bias, wKA, wSA, wKB, wSB, bKA.  kChainRow / 4 is odd, so that the
-// lanes' 16-byte reads fall on different banks.
-constexpr int kChainRow = 52;
-constexpr int kChainW1 = 32, kChainB1 = 38, kChainB2 = 39, kChainW3 = 40, kChainB3 = 44;
-constexpr int kChainWords = 32 * kChainRow;
 
 namespace {
 
@@ -391,14 +383,8 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
   const uint32_t iter_in = __hip_atomic_load(iter_p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const float u_in = a.U[min(tid, 2 * T - 1)];   // 2T <= 256
   float x_in = load_through((a.x0_dev ? a.x0_dev : a.params) + min(tid, kStateDim - 1));
-  constexpr int kRest = kSplitParams - HID * HID;   // W1, b1 and, behind W2, b2, W3, b3
-  constexpr int oW2 = 7 * HID, oB2 = oW2, oW3 = oB2 + HID, oB3 = oW3 + 4 * HID;   // of the parameters; of the rest
-  float w2a = 0.0f, w2b = 0.0f, rest = 0.0f;
-  if constexpr (kNet) {
-    w2a = a.params[oW2 + tid];                   // W2[n][i], 32 n + i = tid
-    w2b = a.params[oW2 + kSplitBlock + tid];     // W2[n + 16][i]
-    rest = a.params[tid < oB2 ? tid : min(tid, kRest - 1) + HID * HID];
-  }
+  ChainStage<kSplitBlock> stage;
+  if constexpr (kNet) stage.load(a.params);
   if (!a.x0_dev) x_in = a.x0[min(tid, kStateDim - 1)];
   // the device counter is advanced by the final merge
   const uint32_t iter0 = a.iter_dev ? (uint32_t)__builtin_amdgcn_readfirstlane((int)iter_in) : a.nk.iter;
@@ -415,48 +401,20 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
   });
   if constexpr (!MULTI)
     if (tid < kWaveSlots * 4) sX[(tid >> 2) * T4 * 8 + (tid & 3)] = s_xn[3 + (tid & 3)];
-  if constexpr (kNet) {
-    // W2[n][16 r + s] is lane 16 r + (n & 15)'s weight of the rotation by (n - s) & 15;
-    // layers 1 and 2 form tanh's argument already multiplied by 2 log2(e)
-    float* w2 = sC + ((tid & 16) + (tid >> 5)) * kChainRow + (((tid >> 5) - tid) & 15);
-    w2[0] = kTanhScale * w2a;
-    w2[16] = kTanhScale * w2b;
-    if (tid < oB2) {
-      const int l = tid < 6 * HID ? tid / 6 : tid - 6 * HID;
-      sC[l * kChainRow + (tid < 6 * HID ? kChainW1 + tid - 6 * l : kChainB1)] = kTanhScale * rest;
-    } else if (tid < oW3) {
-      sC[(tid - oB2) * kChainRow + kChainB2] = kTanhScale * rest;
-    } else if (tid < kRest) {   // layer 3 times dt: W3[o][l] is lane l's weight number o ^ (l & 3)
-      const int e = tid - oW3, l = tid < oB3 ? e & 31 : e - 4 * HID;
-      sC[l * kChainRow + (tid < oB3 ? kChainW3 + ((e >> 5) ^ (l & 3)) : kChainB3)] = a.dt * rest;
-    }
-  }
+  if constexpr (kNet) stage.store(sC, a.dt);
   if constexpr (MULTI || !kNet)   // the plant step's copy of the parameters (a network in its plant layout)
     for (int i = tid; i < (kNet ? kSplitParams : kSplitBasisParams); i += kSplitBlock)
       sP[kNet ? plant_layout_index(i, HID) : i] = a.params[i];
   __syncthreads();
 
   // ---- the chain's constants, kept in registers over every step ----------------------
-  float w1[6] = {}, wP[16] = {}, wQ[16] = {};
-  float bb1 = 0.0f, bP = 0.0f, bQ = 0.0f, wKA = 0.0f, wKB = 0.0f, wSA = 0.0f, wSB = 0.0f, bKA = 0.0f;
-  if (kNet && chain) {
-    const float* c = sC + c32 * kChainRow;
-    const auto c4 = [&](int i) { return *reinterpret_cast<const float4*>(c + i); };
-#pragma unroll
-    for (int q = 0; q < 16; q += 4) {
-      const float4 p = c4(q), v = c4(16 + q);
-      wP[q] = p.x; wP[q + 1] = p.y; wP[q + 2] = p.z; wP[q + 3] = p.w;
-      wQ[q] = v.x; wQ[q + 1] = v.y; wQ[q + 2] = v.z; wQ[q + 3] = v.w;
-    }
-    const float4 p = c4(kChainW1), v = c4(kChainW1 + 4), w = c4(kChainW3);
-    w1[0] = p.x; w1[1] = p.y; w1[2] = p.z; w1[3] = p.w; w1[4] = v.x; w1[5] = v.y;
-    bb1 = v.z;
-    bP = r == 0 ? v.w : 0.0f;
-    bQ = r == 1 ? v.w : 0.0f;
-    // layer 3 as a reduce-scatter over each quad (see the wave kernel)
-    wKA = w.x; wSA = w.y; wKB = w.z; wSB = w.w;
-    bKA = c32 < 4 ? c[kChainB3] : 0.0f;
-  }
+  ChainWeights cw;
+  if (kNet && chain) cw.read(sC, c32);
+  const auto& w1 = cw.w1;
+  const auto& wP = cw.wP;
+  const auto& wQ = cw.wQ;
+  const float bb1 = cw.bb1, bP = cw.bP, bQ = cw.bQ;
+  const float wKA = cw.wKA, wKB = cw.wKB, wSA = cw.wSA, wSB = cw.wSB, bKA = cw.bKA;
   // basis-function model: this lane's column of Theta with each normaliser folded in
   constexpr int kRaw = 21;
   constexpr int kRawIdx[kRaw] = {1, 2, 3, 4, 5, 6, 7, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18, 19, 20, 21, 22};
@@ -510,7 +468,10 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
       float* xs = myX + ((lane & 4) ? 4 + comp : 8 + comp);
       for (int c = 0; c < nch; ++c) {
         const int t1 = r0 + 32 * c;
-        for (int t = c > 0 ? t1 - 32 : 0; t < t1; ++t) {
+        // four steps per turn of the loop: between branches the compiler moves one step's loads,
+        // stores and counters into the next step's chain (20 us of chain at T = 100 -> 19; with a
+        // branch after each step, taken or not, 22).  Eight gain no more.
+        const auto step_of = [&](int t) __attribute__((always_inline)) {
           const int tn = min(t + 1, T - 1);
           float y;   // dt * f of the lane's component
           if constexpr (MODEL == kModelBasis) {
@@ -608,7 +569,13 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
           }
           xh = xh + y;
           xs[8 * t] = (lane & 4) ? y : xh;   // y_t at entry t, hi_{t+1} at entry t + 1
+        };
+        int t = c > 0 ? t1 - 32 : 0;
+        for (; t + 4 <= t1; t += 4) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) step_of(t + u);
         }
+        for (; t < t1; ++t) step_of(t);
         publish_count(chainCnt, (unsigned)(step * nch + c + 1));
       }
     } else {

@@ -133,4 +133,86 @@ __device__ __forceinline__ bool all32(bool p) {
   return half == 0xFFFFFFFFu;
 }
 
+// The network constants of the chain (the 6-32-32-4 network on 32 lanes per sample, see the
+// wave kernel's phase B), staged through LDS in the order in which a chain lane holds them:
+// lane 16 r + col, kChainRow words each (kChainRow / 4 is odd: the lanes' 16-byte reads fall
+// on different banks), scaled: wP[16], wQ[16], w1[6], bb1, the layer-2 bias, wKA, wSA, wKB,
+// wSB, bKA.  Each lane gathering its 45 weights from global memory took 3 us of a launch.
+constexpr int kChainRow = 52;
+constexpr int kChainW1 = 32, kChainB1 = 38, kChainB2 = 39, kChainW3 = 40, kChainB3 = 44;
+constexpr int kChainWords = 32 * kChainRow;
+
+// One block's part in it, NT threads: load() issues the loads, store() writes to LDS.
+template <int NT>
+struct ChainStage {
+  static constexpr int H = 32, kW2 = H * H / NT;
+  static constexpr int kRest = 6 * H + H + H + 4 * H + 4;   // W1, b1 and, behind W2, b2, W3, b3
+  static constexpr int kRestRegs = (kRest + NT - 1) / NT;
+  static_assert(NT % H == 0 && H * H % NT == 0, "");
+  float w2[kW2], rest[kRestRegs];
+
+  __device__ __forceinline__ void load(const float* params) {
+#pragma unroll
+    for (int i = 0; i < kW2; ++i) w2[i] = params[7 * H + threadIdx.x + i * NT];
+#pragma unroll
+    for (int i = 0; i < kRestRegs; ++i) {
+      const int e = threadIdx.x + i * NT;
+      rest[i] = params[e < 7 * H ? e : min(e, kRest - 1) + H * H];
+    }
+  }
+
+  __device__ __forceinline__ void store(float* sC, float dt) const {
+    const int tid = threadIdx.x;
+    // W2[n][16 r + s] is lane 16 r + (n & 15)'s weight of the rotation by (n - s) & 15;
+    // layers 1 and 2 form tanh's argument already multiplied by 2 log2(e)
+#pragma unroll
+    for (int i = 0; i < kW2; ++i) {
+      const int n = (tid + i * NT) >> 5;
+      sC[((tid & 16) + (n & 15)) * kChainRow + (n & 16) + ((n - tid) & 15)] = kTanhScale * w2[i];
+    }
+    constexpr int oB2 = 7 * H, oW3 = oB2 + H, oB3 = oW3 + 4 * H;
+#pragma unroll
+    for (int i = 0; i < kRestRegs; ++i) {
+      const int e = tid + i * NT;
+      if (e < oB2) {
+        const int l = e < 6 * H ? e / 6 : e - 6 * H;
+        sC[l * kChainRow + (e < 6 * H ? kChainW1 + e - 6 * l : kChainB1)] = kTanhScale * rest[i];
+      } else if (e < oW3) {
+        sC[(e - oB2) * kChainRow + kChainB2] = kTanhScale * rest[i];
+      } else if (e < kRest) {   // layer 3 times dt: W3[o][l] is lane l's weight number o ^ (l & 3)
+        const int q = e - oW3, l = e < oB3 ? q & 31 : q - 4 * H;
+        sC[l * kChainRow + (e < oB3 ? kChainW3 + ((q >> 5) ^ (l & 3)) : kChainB3)] = dt * rest[i];
+      }
+    }
+  }
+};
+
+struct ChainWeights {
+  float w1[6] = {}, wP[16] = {}, wQ[16] = {};
+  float bb1 = 0.0f, bP = 0.0f, bQ = 0.0f;
+  // layer 3 times dt, as a reduce-scatter over each quad with the weights placed per lane:
+  // lane L keeps output oA = L & 3 (its final one) and oB = oA ^ 2 (passed on in the second
+  // exchange), and sends outputs oA ^ 1 and oA ^ 3 to its partner L ^ 1, whose oA and oB they
+  // are; dt b3 enters once per output, in the lanes 0..3 of each sample
+  float wKA = 0.0f, wKB = 0.0f, wSA = 0.0f, wSB = 0.0f, bKA = 0.0f;
+
+  __device__ __forceinline__ void read(const float* sC, int c32) {
+    const float* c = sC + c32 * kChainRow;
+    const auto c4 = [&](int i) { return *reinterpret_cast<const float4*>(c + i); };
+#pragma unroll
+    for (int q = 0; q < 16; q += 4) {
+      const float4 p = c4(q), v = c4(16 + q);
+      wP[q] = p.x; wP[q + 1] = p.y; wP[q + 2] = p.z; wP[q + 3] = p.w;
+      wQ[q] = v.x; wQ[q + 1] = v.y; wQ[q + 2] = v.z; wQ[q + 3] = v.w;
+    }
+    const float4 p = c4(kChainW1), v = c4(kChainW1 + 4), w = c4(kChainW3);
+    w1[0] = p.x; w1[1] = p.y; w1[2] = p.z; w1[3] = p.w; w1[4] = v.x; w1[5] = v.y;
+    bb1 = v.z;
+    bP = c32 < 16 ? v.w : 0.0f;
+    bQ = c32 < 16 ? 0.0f : v.w;
+    wKA = w.x; wSA = w.y; wKB = w.z; wSB = w.w;
+    bKA = c32 < 4 ? c[kChainB3] : 0.0f;
+  }
+};
+
 }  // namespace mppi

@@ -1,7 +1,8 @@
-"""The split wave kernel's prologue (weights through LDS in the chain's order, noise and
-controls in one pass) at its edges: horizons around what one pass of 512 threads draws (64
-steps of 8 samples) and the longest, partial blocks, both models, host and device state,
-context and context-free entry.  Bars: the parity checks' own for the oracle; the entry
+"""The wave kernels' prologue (weights through LDS in the chain's order, noise and controls
+in one pass) and step loop (four steps a turn) at their edges: horizons around what one pass
+of 512 threads draws (64 steps of 8 samples), the longest of each form, remainders of the
+loop, partial blocks, more blocks than compute units, host and device state, context and
+context-free entry.  Bars: the parity checks' own for the oracle; the entry
 points agree bit for bit."""
 import numpy as np
 import pytest
@@ -29,6 +30,15 @@ def M():
 def test_split_prologue_edges(M, orc, K, T, explore):
     prob = synth.with_(synth.c1_problem(seed=K), K=K, T=T, explore=explore, lam=5.0)
     print(f"split K={K} T={T} explore {explore}", flush=True)
+    pc.check_iteration(M, orc, prob, synth.ring_map(), synth.mlp_params(32, 2, bias_scale=0.2), synth.C1_X0,
+                       synth.random_controls(T, K, scale=0.2), WAVE, it=3)
+
+
+@pytest.mark.parametrize("K,T,explore", [(2049, 1, 0.0), (2056, 7, 0.5), (3001, 128, 0.0), (9, 129, 0.3),
+                                         (2100, 150, 0.0), (17, 256, 1.0)])
+def test_wave_prologue_edges(M, orc, K, T, explore):
+    prob = synth.with_(synth.c1_problem(seed=K), K=K, T=T, explore=explore, lam=5.0)
+    print(f"wave K={K} T={T} explore {explore}", flush=True)
     pc.check_iteration(M, orc, prob, synth.ring_map(), synth.mlp_params(32, 2, bias_scale=0.2), synth.C1_X0,
                        synth.random_controls(T, K, scale=0.2), WAVE, it=3)
 
