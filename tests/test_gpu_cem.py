@@ -59,6 +59,15 @@ def test_cem_ragged(M, orc, schedule, K, T, elite):
                synth.random_controls(T, K), schedule)
 
 
+@pytest.mark.parametrize("K,elite", [(1024, 0.8), (1025, 0.999), (2048, 0.9), (2049, 0.5), (4096, 0.8),
+                                     (4097, 0.99), (8192, 0.9), (8193, 0.9)])
+def test_cem_keys_per_thread_edges(M, orc, K, elite):
+    """One, two, four and eight costs per thread, then several chunks."""
+    prob = synth.with_(synth.c1_problem(seed=K), K=K, T=6, weighting=1, elite=elite)
+    _check_cem(M, orc, prob, synth.ring_map(), synth.mlp_params(32, 0), synth.C1_X0,
+               synth.random_controls(6, K), 2)
+
+
 @pytest.mark.parametrize("schedule,K", [(2, 32768), (4, 70000), (1, 70000)])
 def test_cem_many_blocks(M, orc, schedule, K):
     prob = synth.with_(synth.c1_problem(seed=K), K=K, T=12, weighting=1, elite=0.8)
