@@ -266,29 +266,6 @@ __device__ __forceinline__ void basis_f(const float* __restrict__ th, const floa
 // Cost map and state cost (Section VI-C)
 // ---------------------------------------------------------------------------
 
-// Bilinear lookup, cell (i, j) at world (ox + j res, oy + i res), indices clamped
-// to the map edge.  The grid coordinate is clamped to [-1, W] x [-1, H] first,
-// which changes nothing inside the map and keeps the integer conversion in range.
-__device__ __forceinline__ float costmap_at(const CostArgs& c, const float* __restrict__ map,
-                                            float px, float py) {
-  float gx = (px - c.ox) / c.res;
-  float gy = (py - c.oy) / c.res;
-  gx = fminf(fmaxf(gx, -1.0f), (float)c.W);
-  gy = fminf(fmaxf(gy, -1.0f), (float)c.H);
-  const float fj = floorf(gx), fi = floorf(gy);
-  const int j0 = (int)fj, i0 = (int)fi;
-  const float fx = gx - fj, fy = gy - fi;
-  const int ja = min(max(j0, 0), c.W - 1), jb = min(max(j0 + 1, 0), c.W - 1);
-  const int ia = min(max(i0, 0), c.H - 1), ib = min(max(i0 + 1, 0), c.H - 1);
-  const float m00 = map[(size_t)ia * c.W + ja];
-  const float m01 = map[(size_t)ia * c.W + jb];
-  const float m10 = map[(size_t)ib * c.W + ja];
-  const float m11 = map[(size_t)ib * c.W + jb];
-  const float top = (1.0f - fx) * m00 + fx * m01;
-  const float bot = (1.0f - fx) * m10 + fx * m11;
-  return (1.0f - fy) * top + fy * bot;
-}
-
 // Exact sum and its rounding error (Knuth's two-sum).
 __device__ __forceinline__ void two_sum(float a, float b, float& s, float& e) {
   s = a + b;
@@ -296,10 +273,13 @@ __device__ __forceinline__ void two_sum(float a, float b, float& s, float& e) {
   e = (a - (s - bb)) + (b - bb);
 }
 
+// Bilinear lookup: cell (i, j) at world (ox + j res, oy + i res), indices clamped to the
+// map edge.
 // Grid coordinate (p - o) / res of a position given as hi + lo, split into an integer
 // cell and a fraction in [0, 1) that keeps the low part: the quotient's rounding
 // remainder is exact (fma), so the fraction is good to ~1e-7 of a cell even where
-// the coordinate itself needs all 24 bits.  Clamped to [-1, n] like costmap_at.  The
+// the coordinate itself needs all 24 bits.  Clamped to [-1, n], which
+// changes nothing inside the map and keeps the integer conversion in range.  The
 // quotient comes from the reciprocal inv_res = fl(1/res) and one correction with the
 // residual (within an ulp of d / res, which keeps the next residual exact), not from
 // a division.
