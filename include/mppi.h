@@ -175,7 +175,9 @@ mppi_status mppi_set_basis_dynamics(mppi_ctx* ctx, const float* theta);
  * n outside [0, 1<<24] or a non-finite position.  STATE: no cost map set. */
 mppi_status mppi_costmap_values(mppi_ctx* ctx, const float* xy, int32_t n, float* h_out);
 
-/* Replace the nominal control sequence U ([T][2], steer/throttle per step).  Copied. */
+/* Replace the nominal control sequence U ([T][2], steer/throttle per step).  Copied, on the
+ * context's stream; the copy is complete when the call returns (as with every set_ call),
+ * so a captured step that is then replayed on another stream reads the new U. */
 mppi_status mppi_set_controls(mppi_ctx* ctx, const float* U);
 
 /* One MPPI iteration from state x0[7] (host).  Enqueued; returns without waiting
