@@ -69,17 +69,21 @@ constexpr int32_t kMaxK = 1 << 22;
 constexpr int32_t kWaveAutoMaxK = 12288;   // AUTO: WAVE up to here, QUAD above
 constexpr int kNumBasisHost = 25;          // basis functions of the basis-function model
 
-// Pinned host memory of a context, for results on their way to the host.  Allocated with the
-// context, grown when a fetch needs more, at most kPinnedMaxWords words (1 MiB; larger
-// transfers, and those for which it cannot be had, go directly to the caller's memory).  U and the
-// status took two copy commands to the caller's memory, 39 us with the synchronisation behind
-// a short kernel; one launch that writes them here and a plain copy take 20 (64 KB: 49 and
-// 22; 256 KB: 57 and 30).
+// Pinned host memory of a context, for results on their way to the host: at most
+// kPinnedMaxWords words (1 MiB; larger transfers, and those for which it cannot be had, go
+// directly to the caller's memory), grown when a fetch needs more.  U and the status took two
+// copy commands to the caller's memory, 39 us with the synchronisation behind a short kernel;
+// one launch that writes them here and a plain copy take 20 (64 KB: 49 and 22; 256 KB: 57 and
+// 30).  Allocating and freeing it takes 40-50 us, so a context gets it with its
+// kPinnedAtFetch-th fetch, when the copies have cost about as much: a context that is read
+// once or twice, or only by device pointers, pays nothing.
 constexpr size_t kPinnedMaxWords = (size_t)1 << 18;
+constexpr int kPinnedAtFetch = 3;
 struct Pinned {
   uint32_t* host = nullptr;
   uint32_t* dev = nullptr;
   size_t words = 0;
+  int fetches = 0;           // so far, up to kPinnedAtFetch
 };
 
 struct PendingTiming {
@@ -165,7 +169,8 @@ bool pinned_reserve(Pinned& p, size_t words) {
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
   if (p.host) (void)hipHostFree(p.host);
-  p = Pinned{};
+  p.host = p.dev = nullptr;
+  p.words = 0;
   hipError_t e = hipHostMalloc(&h, n * 4, hipHostMallocMapped | hipHostMallocCoherent);
   if (e == hipSuccess) e = hipHostGetDevicePointer(&d, h, 0);
   if (e != hipSuccess) {
@@ -682,9 +687,11 @@ struct Range {
 mppi_status fetch(mppi_ctx* c, std::initializer_list<Range> ranges) {
   size_t total = 0;
   for (const Range& r : ranges) total += r.words;
-  if (total > c->pin.words && total <= kPinnedMaxWords) {
+  c->pin.fetches = std::min(c->pin.fetches + 1, kPinnedAtFetch);
+  if (total > c->pin.words && total <= kPinnedMaxWords && c->pin.fetches == kPinnedAtFetch) {
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    pinned_reserve(c->pin, total);
+    // at first room for the costs or the controls and more, so that it seldom grows
+    pinned_reserve(c->pin, std::max(total, std::min(kPinnedMaxWords, (size_t)c->cfg.K + 2 * (size_t)c->cfg.T + 2048)));
   }
   if (total <= c->pin.words) {
     CopyArgs a{};
@@ -872,7 +879,6 @@ mppi_status mppi_create(const mppi_config* cfg, const mppi_cost* cost, int devic
     }
     HIP_TRY(c, hipMalloc(&c->d_x, sizeof(float) * (kStateDim + 2)));
     c->d_u0 = c->d_x + kStateDim;
-    pinned_reserve(c->pin, std::min(kPinnedMaxWords, (size_t)c->cfg.K + 2 * (size_t)c->cfg.T + 2048));
     std::vector<float> decay(T + 1);
     for (int t = 0; t <= T; ++t) decay[t] = (float)std::pow((double)cost->crash_decay, (double)t);
     HIP_TRY(c, hipMalloc(&c->d_decay, sizeof(float) * (T + 1)));

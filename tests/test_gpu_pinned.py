@@ -1,0 +1,65 @@
+"""Reading a context back before, while and after it gets its pinned memory (with its third
+read), when that memory has to grow, and beyond what it may hold: the same values as a
+second context that is read once, or as the histories a device-side run leaves in device
+memory, bit for bit."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def M():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_1707_02342_amd import mppi
+    mppi.lib()
+    return mppi
+
+
+@pytest.mark.parametrize("K,T", [(1, 1), (256, 30), (9000, 3)])
+def test_every_read_returns_the_same(M, K, T):
+    prob = synth.with_(synth.c1_problem(seed=1), K=K, T=T)
+    with M.Controller(prob, synth.ring_map(), synth.mlp_params(32, 0)) as c:
+        S, _ = c.iterate(synth.C1_X0, want_costs=True)
+        U = c.controls()
+        rho, eta, delta = c.stats()
+        for _ in range(4):
+            assert np.array_equal(c.controls(), U) and c.iteration == 1
+            r, e, d = c.stats()
+            assert r == rho == S.min() and e == eta and np.array_equal(d, delta)
+    for reads in range(1, 5):                       # the costs at each read in turn
+        with M.Controller(prob, synth.ring_map(), synth.mlp_params(32, 0)) as c:
+            for _ in range(reads - 1):
+                assert not c.controls().any()
+            assert np.array_equal(c.iterate(synth.C1_X0, want_costs=True)[0], S)
+            assert np.array_equal(c.controls(), U)
+
+
+@pytest.mark.parametrize("reads", [0, 1, 2, 5])
+@pytest.mark.parametrize("n", [1000, 29200])        # 9 n + 8 words: above the first size, above the largest
+def test_histories_grow_the_memory(M, n, reads):
+    import torch
+    prob = synth.with_(synth.c1_problem(seed=2), K=16, T=8)
+    U = synth.random_controls(8, 0, scale=0.2)
+    with M.Controller(prob, synth.ring_map(), synth.mlp_params(32, 1)) as c:
+        c.set_controls(U)
+        x = torch.tensor(np.asarray(synth.C1_X0, np.float32), device="cuda")
+        uh, xh = torch.zeros(n, 2, device="cuda"), torch.zeros(n, 7, device="cuda")
+        M.mppi_run_receding_device(c.ctx, x.data_ptr(), n, uh.data_ptr(), xh.data_ptr())
+        torch.cuda.synchronize()
+    with M.Controller(prob, synth.ring_map(), synth.mlp_params(32, 0)) as c:
+        for _ in range(reads):
+            assert not c.controls().any()
+        for i in range(4):
+            c.set_controls(synth.random_controls(8, i + 1, scale=0.2))
+            c.set_dynamics(synth.mlp_params(32, 4 - i))
+        c.set_controls(U)
+        u, xs = M.mppi_run_receding(c.ctx, synth.C1_X0, n)[:2]
+        assert np.array_equal(u, uh.cpu().numpy()) and np.array_equal(xs[1:], xh.cpu().numpy())
+        V = synth.random_controls(8, 9, scale=0.2)
+        c.set_controls(V)
+        assert np.array_equal(c.controls(), V)
