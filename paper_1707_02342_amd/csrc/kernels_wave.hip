@@ -224,7 +224,6 @@ __global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kern
       u_next = *reinterpret_cast<const float2*>(sU + 2 * tn);
       e_next = *reinterpret_cast<const float2*>(myE + 2 * tn);
     }
-    const float vc0 = vc.x, vc1 = vc.y;
     float y;   // dt * f of the lane's component
     const float xcur = xh;
     if constexpr (MODEL == kModelBasis) {
@@ -258,18 +257,7 @@ __global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kern
       cq = cq_next;
     } else {
       // layer 1
-      float acc1 = __builtin_fmaf(w1[4], vc0, bb1);
-      acc1 = __builtin_fmaf(w1[5], vc1, acc1);
-      // one asm block, so that no wait states are inserted between the four; the DPP
-      // source xcur was written before this step's two fmas of acc1 above, the two wait
-      // states a DPP read of a VALU result needs
-      asm volatile(
-          "v_fmac_f32_dpp %0, %1, %2 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %0, %1, %3 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %0, %1, %4 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %0, %1, %5 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf"
-          : "+v"(acc1) : "v"(xcur), "v"(w1[0]), "v"(w1[1]), "v"(w1[2]), "v"(w1[3]));
-      const float h1 = tanh_prescaled(acc1);
+      const float h1 = tanh_prescaled(chain_layer1(xcur, vc, bb1, w1));
       // layer 2: four interleaved chains (P, Q for even and odd rotations) so that no
       // accumulator is read by the instruction right after the one that wrote it
       float P = __builtin_fmaf(wP[0], h1, bP);

@@ -55,7 +55,8 @@
 // flagged, the group row likewise, and all 15 group rows merged again by every rollout
 // block): 32.0 -> 29.8 us per paper-shaped step (basis-function model 28.9 -> 26.2); with the
 // cost waves' scans in 64 bits 29.4 (26.0), with the chain's loop where the compiler puts it
-// 28.6 (25.8), with four steps per turn of that loop 28.0 (24.0).
+// 28.6 (25.8), with four steps per turn of that loop 28.0 (24.0), with layer 1 as one block
+// 27.1.
 #include "wave_common.hip.h"
 
 namespace mppi {
@@ -505,17 +506,7 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
           } else {
             const float2 vc_next = *reinterpret_cast<const float2*>(myV + 2 * tn);
             // layer 1
-            float acc1 = __builtin_fmaf(w1[4], vc.x, bb1);
-            acc1 = __builtin_fmaf(w1[5], vc.y, acc1);
-            // the DPP source xh was written before the two fmas of acc1 above: the two
-            // wait states a DPP read of a VALU result needs, so no s_nop here
-            asm volatile(
-                "v_fmac_f32_dpp %0, %1, %2 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n\t"
-                "v_fmac_f32_dpp %0, %1, %3 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n\t"
-                "v_fmac_f32_dpp %0, %1, %4 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n\t"
-                "v_fmac_f32_dpp %0, %1, %5 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf"
-                : "+v"(acc1) : "v"(xh), "v"(w1[0]), "v"(w1[1]), "v"(w1[2]), "v"(w1[3]));
-            const float h1 = tanh_prescaled(acc1);
+            const float h1 = tanh_prescaled(chain_layer1(xh, vc, bb1, w1));
             // layer 2: four interleaved chains over the row's rotations, then the two rows
             float P = __builtin_fmaf(wP[0], h1, bP);
             float Q = __builtin_fmaf(wQ[0], h1, bQ);

@@ -133,6 +133,26 @@ __device__ __forceinline__ bool all32(bool p) {
   return half == 0xFFFFFFFFu;
 }
 
+// Layer 1 of the chain: b + W1 (x_d, g(v)) for the lane's hidden unit, x the lane's component
+// of x_d.  One block, the controls' two products first: x is its input, so they stand between
+// the instruction that wrote x and the first DPP read of it, which needs two wait states.
+// (The compiler does not look for that inside a block, and products formed outside depend on
+// the controls alone: it moved them above the write.  A paper-shaped multi-step step takes
+// 27.1 us so, 28.0 with them outside; the wave kernel the same either way.)
+__device__ __forceinline__ float chain_layer1(float x, float2 v, float b, const float (&w)[6]) {
+  float acc;
+  asm volatile(
+      "v_fma_f32 %0, %6, %8, %10\n\t"
+      "v_fmac_f32 %0, %7, %9\n\t"
+      "v_fmac_f32_dpp %0, %1, %2 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %1, %3 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %1, %4 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %1, %5 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf"
+      : "=&v"(acc)
+      : "v"(x), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]), "v"(v.x), "v"(v.y), "v"(b));
+  return acc;
+}
+
 // The network constants of the chain (the 6-32-32-4 network on 32 lanes per sample, see the
 // wave kernel's phase B), staged through LDS in the order in which a chain lane holds them:
 // lane 16 r + col, kChainRow words each (kChainRow / 4 is odd: the lanes' 16-byte reads fall
