@@ -36,6 +36,7 @@ constexpr int kQuadChunk = 16;     // steps per chunk
 // chunk) and [16][4] of (v_0, v_1, 1, 0), the clamped control and the constants of lane
 // groups 2 and 3.  One address serves both and the state's write to the next row.
 constexpr int kQuadRow = 128;
+constexpr double kFp32Range = 0x1.ffffffp127;   // the smallest value that rounds to infinity in FP32
 constexpr int kQuadWaveLds = (kQuadChunk + 1) * kQuadRow;
 
 __device__ __forceinline__ float q_as_f(uint32_t v) { return __builtin_bit_cast(float, v); }
@@ -344,9 +345,9 @@ struct QuadNet {
 // waves issue together, 8.2 per exp or rcp), so a step of 16 samples costs its 704 (h = 32)
 // matrix cycles plus every vector instruction.  Hence everything that does not belong to
 // the chain is done once per sample and step, in the lane that draws the step's noise (the
-// clamped control and the control cost) or that evaluates its cost; poses are checked for
-// non-finite values once per chunk and x_d at the end: what is not finite stays so, since
-// every step adds to it.  242 -> ~170 vector instructions per wave-step beside the matrix
+// clamped control and the control cost) or that evaluates its cost; the heading is checked
+// for non-finite values once per chunk and x_d at the end: what is not finite there stays
+// so or makes the position so, since every step adds to it.  242 -> ~170 vector instructions per wave-step beside the matrix
 // products (a third of that from the 64-bit sums); with tanh4 above, before -> after: batched
 // form (512 instances, 1.01e8 steps) 4.69 -> 4.07 ms; T = 100, h = 64: FP32 K = 65536 759 -> 678
 // us, BF16 332 -> 264 us, FP16 365 -> 296 us, K = 16384 (one wave per SIMD) FP32 226 -> 188, BF16
@@ -385,6 +386,7 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
   float xh = x0v[3 + g];
   double xd = xh, th_c = x0v[2], px_c = x0v[0], py_c = x0v[1], S64 = 0.0;
   bool ok = true;
+  uint64_t in_range = ~0ull;         // the wave's lanes whose positions were inside FP32's range
   wX[j * 4 + g] = xh;                // row 0 = the state entering the chunk
 #pragma unroll
   for (int q = 0; q < 4; ++q)
@@ -473,8 +475,15 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
       for (int q = 0; q < 4; ++q) {
         px[q] = bx + px[q];
         py[q] = by + py[q];
+        // a position outside FP32's range at any step makes the sample non-finite, also where
+        // a later step leads back
+        in_range &= __ballot(fabs(px[q]) < kFp32Range) & __ballot(fabs(py[q]) < kFp32Range);
       }
     }
+    // (held as the wave's masks, and before the loads: as a condition per lane, which the
+    // compiler moves behind them, it spilled ten more registers at h = 32: batched form 4.24 ms
+    // against 4.13, now 4.13)
+    __builtin_amdgcn_sched_barrier(0);
     // every map and decay load at once
     float mv[4][4], fxv[4], fyv[4], dec[4];
 #pragma unroll
@@ -500,7 +509,7 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
     th_c += th_sum;
     px_c += px_sum;
     py_c += py_sum;
-    ok = ok && finite_f((float)th_c) && finite_f((float)px_c) && finite_f((float)py_c);
+    ok = ok && finite_f((float)th_c);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -510,7 +519,7 @@ __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, flo
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  ok = ok && finite_f(xh) && finite_f((float)xd);
+  ok = ok && ((in_range >> lane) & 1) && finite_f(xh) && finite_f((float)xd);
 
   // S_k: the four lanes' sums
   double S4[4];
