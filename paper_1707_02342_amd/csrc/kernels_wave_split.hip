@@ -42,10 +42,10 @@
 // that step s + 1 starts from U and the plant state in its own LDS with no further memory
 // round trip.  Every block computes the same values in the same order; block 0 alone
 // writes U, the plant state, the statistics and the histories.  A merger block owns a
-// sixteenth of the columns: it reads these of all G rows (one 128-byte line each), merges
-// them in the two levels of finish_iteration in the same order, and writes its part of the
-// merged row.  A word is never overwritten while another block may still need it: a
-// rollout block writes step s + 1's row after it has read step s's merged row, which
+// sixteenth of the columns (several on a device with fewer free units): it reads these of
+// all G rows (one 128-byte line each), merges them in the two levels of finish_iteration in
+// the same order, and writes its part of the merged row.  A word is never overwritten while
+// another block may still need it: a rollout block writes step s + 1's row after it has read step s's merged row, which
 // every merger wrote after reading all of step s's rows.  Every wait is bounded: a block
 // that gives up sets the status and leaves.  The results equal those of one launch per
 // step bit for bit.
@@ -198,23 +198,23 @@ constexpr int kStatusTimeout = 6;   // a multi-step launch gave up waiting for a
 // 1 << 20: each poll waits for its load, so of the order of a second).
 __device__ __forceinline__ unsigned spin_limit(const RolloutArgs& a) { return a.spin_limit ? a.spin_limit : (1u << 20); }
 
-// Multi-step launch, merger block m = blockIdx.x - G (8 waves, G <= 256 rows): at every step
-// reads its columns of every rollout block's row as they arrive, merges them as the
+// Multi-step launch, one of the merger blocks (8 waves, G <= 256 rows): at every step takes the
+// parts first, first + stride, ... (one where the device has a unit for each merger):
+// reads the part's columns of every rollout block's row as they arrive, merges them as the
 // blocks of one launch are merged -- per group of 16 rows relative to the group's minimum,
 // then the group rows, every sum in row order, so that the merged row has the same bits --
-// and writes its part of the merged row in kMergeCopies copies.  lds: (cw + 3) G +
+// and writes the part of the merged row in kMergeCopies copies.  lds: (cw + 3) G +
 // 18 * 32 floats.  Inlined into the kernel, since it reads the arguments with
 // reload_args().
-__device__ __forceinline__ void merge_columns_block(int n_steps, float* lds) {
+__device__ __forceinline__ void merge_columns_block(int n_steps, int first, int stride, float* lds) {
   constexpr int kPass = 8;   // rows per thread: 256 rows of at most 16 lanes over 512 threads
   __shared__ unsigned s_stop;
   const int tid = threadIdx.x, lane = tid & 63;
   if (tid == 0) s_stop = 0u;
   __syncthreads();
-  for (int step = 0; step < n_steps; ++step) {
+  for (int step = 0, m = first; step < n_steps;) {
     const RolloutArgs& as = reload_args();
-    const int G = as.G, T2 = 2 * as.T, M = merge_blocks(as.T), cw = merge_columns(as.T), LW = merge_line_words(cw);
-    const int m = (int)blockIdx.x - G;
+    const int G = as.G, T2 = 2 * as.T, M = merge_parts(as.T), cw = merge_columns(as.T), LW = merge_line_words(cw);
     const int words = 2 + min(cw, T2 - m * cw);   // of the line that carry a value
     const unsigned target = as.step_base + (unsigned)step + 1u;
     const unsigned limit = spin_limit(as);
@@ -317,6 +317,11 @@ __device__ __forceinline__ void merge_columns_block(int n_steps, float* lds) {
         for (int c = lane >> (sh + 1); c < kMergeCopies; c += 64 >> (sh + 1)) store_word(dst + (size_t)c * M * LW, out, target);
       }
     }
+    m += stride;
+    if (m >= M) {
+      m = first;
+      ++step;
+    }
   }
 }
 
@@ -348,7 +353,7 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
   float* lds = sX;
   if constexpr (MULTI) {
     if ((int)blockIdx.x >= a.G) {   // a merger block
-      merge_columns_block(n_steps, smem);
+      merge_columns_block(n_steps, (int)blockIdx.x - a.G, (int)gridDim.x - a.G, smem);
       return;
     }
   }
@@ -675,7 +680,7 @@ __global__ __launch_bounds__(kSplitBlock) void rollout_wave_split_kernel(Rollout
     if constexpr (MULTI) {
       // ---- multi-step launch: the row goes to the merger blocks, the merged row comes back
       // and this block runs the final stage itself (2T <= 256: a column per thread) -------
-      const int T2 = 2 * T, M = merge_blocks(T), cw = merge_columns(T), LW = merge_line_words(cw);
+      const int T2 = 2 * T, M = merge_parts(T), cw = merge_columns(T), LW = merge_line_words(cw);
       const unsigned target = as.step_base + (unsigned)step + 1u;
       uint64_t* const row = as.sync + (size_t)blockIdx.x * M * LW;
       const int m = tid / cw;

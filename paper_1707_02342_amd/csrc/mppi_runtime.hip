@@ -28,7 +28,6 @@ size_t wave_smem_bytes(int T, int model);
 template <int MODEL, bool MULTI> __global__ void rollout_wave_split_kernel(RolloutArgs);
 size_t wave_split_smem_bytes(int T, int model);
 constexpr int kWaveSplitBlockThreads = 512;   // 4 chain waves + 4 cost waves
-constexpr int kWaveSplitMaxT = 128;
 size_t wide_smem_bytes(int T);
 template <int NQ> __global__ void rollout_wide_kernel(RolloutArgs);
 template <int PREC, int HID> __global__ void rollout_quad_kernel(RolloutArgs);
@@ -376,7 +375,7 @@ int device_cus() {
 // kernel, which keeps each lane's share of the steps (ceil(T/32) of them) in registers
 // and is compiled for up to 4 (T <= 128) and up to 8 (T <= 256).
 void launch_wave(int G, int T, hipStream_t stream, const RolloutArgs& a) {
-  if (T <= kWaveSplitMaxT && G <= device_cus()) {
+  if (T <= kSplitMaxT && G <= device_cus()) {
     const size_t smem = wave_split_smem_bytes(T, a.model);
     if (a.model == kModelBasis)
       hipLaunchKernelGGL((rollout_wave_split_kernel<kModelBasis, false>), dim3(G), dim3(kWaveSplitBlockThreads),
@@ -602,16 +601,6 @@ mppi_status enqueue_iteration(mppi_ctx* c, const float* x0_host, const float* x0
   return MPPI_OK;
 }
 
-// Whether the split wave kernel's multi-step launch can hold this context's problem: T <=
-// 128 (a column of the merged row per thread) and one block per compute unit for its
-// rollout blocks and one merger block per merge group (K <= 1920 on 256 CUs; the mergers
-// number at most 16, and at most 256 rows are merged in groups of 16).
-bool multi_step_fits(const mppi_ctx* c) {
-  const int T = c->cfg.T, G = blocks_for(c, MPPI_SCHED_WAVE);
-  return c->cfg.weighting == MPPI_WEIGHTS_IT && T <= kWaveSplitMaxT && G <= 256 &&
-         G + std::max(merge_groups(G), merge_blocks(T)) <= device_cus();
-}
-
 // Whether n receding steps can run as one multi-step launch of the split wave kernel: the
 // wave schedule, a problem that fits, and a device that launches cooperatively (every block
 // resident at once).
@@ -651,6 +640,9 @@ mppi_status enqueue_receding_steps(mppi_ctx* c, float* x_dev, int n, float* u_hi
   // polls of a step-signal wait (0: the kernel's default), for tests of the give-up path
   if (const char* e = std::getenv("MPPI_STEP_SPIN_LIMIT")) a.spin_limit = (unsigned)std::strtoul(e, nullptr, 10);
   a.step_base = c->step_count;
+  int mergers = merger_blocks(G, c->cfg.T, device_cus());
+  // as on a device with fewer compute units, for tests of that form
+  if (const char* e = std::getenv("MPPI_STEP_MERGERS")) mergers = std::max(1, std::min(mergers, std::atoi(e)));
   PendingTiming pt{};
   if (c->timing) {
     pt.e0 = take_event(c);
@@ -662,7 +654,7 @@ mppi_status enqueue_receding_steps(mppi_ctx* c, float* x_dev, int n, float* u_hi
   const void* fn = c->model == kModelBasis
                        ? reinterpret_cast<const void*>(&rollout_wave_split_kernel<kModelBasis, true>)
                        : reinterpret_cast<const void*>(&rollout_wave_split_kernel<kModelNet, true>);
-  HIP_TRY(c, hipLaunchCooperativeKernel(fn, dim3(G + merge_blocks(c->cfg.T)), dim3(kWaveSplitBlockThreads), args,
+  HIP_TRY(c, hipLaunchCooperativeKernel(fn, dim3(G + mergers), dim3(kWaveSplitBlockThreads), args,
                                         (unsigned)wave_split_smem_bytes(c->cfg.T, c->model), c->stream));
   if (c->timing) {
     HIP_TRY(c, hipEventRecord(pt.e1, c->stream));
@@ -872,8 +864,10 @@ mppi_status mppi_create(const mppi_config* cfg, const mppi_cost* cost, int devic
     HIP_TRY(c, hipMemsetAsync(c->d_status, 0, sizeof(int), c->stream));
     HIP_TRY(c, hipMalloc(&c->d_iter, sizeof(unsigned)));
     HIP_TRY(c, hipMemsetAsync(c->d_iter, 0, sizeof(unsigned), c->stream));
-    if (multi_step_fits(c)) {
-      const size_t words = merge_words(blocks_for(c, MPPI_SCHED_WAVE), T);
+    // Algorithm 2's multi-step launches (K <= 1920 on 256 compute units)
+    const int Gw = blocks_for(c, MPPI_SCHED_WAVE);
+    if (cfg->weighting == MPPI_WEIGHTS_IT && multi_step_fits(Gw, T, device_cus())) {
+      const size_t words = merge_words(Gw, T);
       HIP_TRY(c, hipMalloc(&c->d_sync, sizeof(uint64_t) * words));
       HIP_TRY(c, hipMemsetAsync(c->d_sync, 0, sizeof(uint64_t) * words, c->stream));
     }

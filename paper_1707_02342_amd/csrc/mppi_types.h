@@ -15,18 +15,19 @@ constexpr int kStateDim = 7;
 // holds its step's value: no flag, no wait for the writer's stores and no second round
 // trip.  The words of a context are zero when it is created and step numbers start at 1
 // and grow over its launches, so none is ever reset.
-//   M merger blocks share the 2T columns, cw = merge_columns(T) of them each (the last
+//   The 2T columns form M = merge_parts(T) parts of cw = merge_columns(T) each (the last
 //   fewer); a line of merge_line_words(cw) words holds {rho, eta, cw columns}:
-//   rows    [G][M] lines: rollout block b's partial row, split over the mergers;
-//   merged  [kMergeCopies][M] lines: merger m's columns of the merged row (rollout block b
-//           reads copy b mod kMergeCopies, so that not every block polls the same memory).
+//   rows    [G][M] lines: rollout block b's partial row, in parts;
+//   merged  [kMergeCopies][M] lines: the parts of the merged row (rollout block b reads copy
+//           b mod kMergeCopies, so that not every block polls the same memory).
+//   A merger block takes part m, or every N-th part where only N blocks are there to merge.
 constexpr int kMergeCopies = 16;
-constexpr int kMaxMergers = 16;
-__host__ __device__ constexpr inline int merge_columns(int T) { return (2 * T + kMaxMergers - 1) / kMaxMergers; }
-__host__ __device__ constexpr inline int merge_blocks(int T) { return (2 * T + merge_columns(T) - 1) / merge_columns(T); }
+constexpr int kMaxMergeParts = 16;
+__host__ __device__ constexpr inline int merge_columns(int T) { return (2 * T + kMaxMergeParts - 1) / kMaxMergeParts; }
+__host__ __device__ constexpr inline int merge_parts(int T) { return (2 * T + merge_columns(T) - 1) / merge_columns(T); }
 __host__ __device__ constexpr inline int merge_line_words(int cw) { return cw + 2 <= 16 ? 16 : 32; }   // whole 128-byte lines
 constexpr inline size_t merge_words(int G, int T) {
-  return (size_t)(G + kMergeCopies) * merge_blocks(T) * merge_line_words(merge_columns(T));
+  return (size_t)(G + kMergeCopies) * merge_parts(T) * merge_line_words(merge_columns(T));
 }
 constexpr int kCtrlDim = 2;
 constexpr int kNetIn = 6;
@@ -45,6 +46,18 @@ __host__ __device__ constexpr inline int merge_group_size(int G) {
 __host__ __device__ constexpr inline int merge_groups(int G) {
   const int s = merge_group_size(G);
   return (G + s - 1) / s;
+}
+
+// Whether a multi-step receding launch of G rollout blocks fits a device of `cus` compute
+// units at one block each -- with one unit for every 16 of them to merge on -- and how many
+// merger blocks it then has: one per part of the row where the units suffice.  A launch that
+// wanted a unit per part whatever G is would serve 32 units up to K = 128 instead of 240.
+constexpr int kSplitMaxT = 128;   // the split wave kernel's longest horizon
+constexpr inline bool multi_step_fits(int G, int T, int cus) {
+  return T <= kSplitMaxT && G <= 256 && G + merge_groups(G) <= cus;
+}
+constexpr inline int merger_blocks(int G, int T, int cus) {
+  return merge_parts(T) < cus - G ? merge_parts(T) : cus - G;
 }
 
 // Philox key and counter words that are fixed within one iteration, plus the
@@ -128,7 +141,7 @@ struct RolloutArgs {
   // to a later merge of every shard's row (merge_update_kernel).
   float* row_out;
   // Multi-step receding launch (the split wave kernel, launched cooperatively with G
-  // rollout blocks and merge_blocks(T) merger blocks): n_steps receding steps in one launch
+  // rollout blocks, the others merging): n_steps receding steps in one launch
   // (0 or 1: one step), step s numbered step_base + s + 1 in the words of sync
   // ([merge_words(G, T)], see kMergeCopies); u0_out and x_copy then point to [n_steps][2]
   // and [n_steps][7] histories (step s writes entry s).
