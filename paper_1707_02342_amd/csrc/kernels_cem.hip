@@ -21,7 +21,6 @@
 namespace mppi {
 
 constexpr int kCemBlock = 1024;
-constexpr int kCemMaxBlocks = 8;                  // of a launch
 constexpr int kCemWaves = kCemBlock / 64;
 constexpr int kCemKeys = 8;                       // keys per thread and chunk
 constexpr int kCemChunk = kCemBlock * kCemKeys;   // samples per chunk

@@ -576,9 +576,9 @@ mppi_status enqueue_iteration(mppi_ctx* c, const float* x0_host, const float* x0
   HIP_TRY(c, launch_rollout(sched, c->cfg.precision, G, c->stream, a));
   // Algorithm 3: the rollout launch leaves costs and delta rows; the update follows
   if (a.cem_zeta > 0) {
-    // blocks sharing the elite-row sum: one per ~48 elite rows, at most 8, and never more
-    // than the partial rows allocated (their counter a.cnt[0] is zero between launches)
-    const int nb = std::max(1, std::min({8, (a.cem_zeta + 47) / 48, c->part_cap}));
+    // blocks sharing the elite-row sum: one per ~48 elite rows, at most kCemMaxBlocks, and never
+    // more than the partial rows allocated (their counter a.cnt[0] is zero between launches)
+    const int nb = std::max(1, std::min({kCemMaxBlocks, (a.cem_zeta + 47) / 48, c->part_cap}));
     const bool h32 = c->model == kModelNet && c->hidden == 32;   // plant step unrolled
     if (c->cfg.T <= 128) {
       if (h32) hipLaunchKernelGGL((cem_update_kernel<2, 32>), dim3(nb), dim3(kCemBlockThreads), 0, c->stream, a);

@@ -159,6 +159,8 @@ struct CopyArgs {
   unsigned words[kCopyRanges];
 };
 
+constexpr int kCemMaxBlocks = 8;   // blocks of a cross-entropy update, whose shares its last block sums
+
 constexpr int kCkptStride = 8;   // floats per checkpointed state (7 + pad)
 
 // Adjoint of the free-energy objective J = rho - lambda log(eta~/K) through every
