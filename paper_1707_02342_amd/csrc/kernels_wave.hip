@@ -200,8 +200,6 @@ __global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kern
 
   // ---- B: serial chain of the dynamic states ---------------------------------------
   {
-  float2 u = *reinterpret_cast<const float2*>(sU);
-  float2 e = *reinterpret_cast<const float2*>(myE);
   float2 vc = make_float2(0.0f, 0.0f);
   if constexpr (kNetV) vc = *reinterpret_cast<const float2*>(myV);
   // the lane's store slot in sX: hi_{t+1} (lanes with bit 2 clear) or y_t (bit 2 set)
@@ -215,15 +213,10 @@ __global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kern
     cq = myB[4 + comp];
   }
   for (int t = 0; t < T; ++t) {
-    // next step's control and noise are read one step ahead (LDS latency off the chain)
+    // next step's control is read one step ahead (LDS latency off the chain)
     const int tn = min(t + 1, T - 1);
-    float2 u_next = u, e_next = e, vc_next = vc;
-    if constexpr (kNetV) {
-      vc_next = *reinterpret_cast<const float2*>(myV + 2 * tn);
-    } else {
-      u_next = *reinterpret_cast<const float2*>(sU + 2 * tn);
-      e_next = *reinterpret_cast<const float2*>(myE + 2 * tn);
-    }
+    float2 vc_next = vc;
+    if constexpr (kNetV) vc_next = *reinterpret_cast<const float2*>(myV + 2 * tn);
     float y;   // dt * f of the lane's component
     const float xcur = xh;
     if constexpr (MODEL == kModelBasis) {
@@ -258,50 +251,7 @@ __global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kern
     } else {
       // layer 1
       const float h1 = tanh_prescaled(chain_layer1(xcur, vc, bb1, w1));
-      // layer 2: four interleaved chains (P, Q for even and odd rotations) so that no
-      // accumulator is read by the instruction right after the one that wrote it
-      float P = __builtin_fmaf(wP[0], h1, bP);
-      float Q = __builtin_fmaf(wQ[0], h1, bQ);
-      float P2 = wP[1] * dpp_f<kRowRor + 1>(h1);
-      float Q2 = wQ[1] * dpp_f<kRowRor + 1>(h1);
-      // rotations 2..15 in one asm block (no wait states inserted between them); the
-      // DPP source h1 was written before the four instructions forming P, Q, P2 and Q2,
-      // which are the block's inputs: more than the two wait states a DPP read needs
-      asm volatile(
-          "v_fmac_f32_dpp %0, %4, %5 row_ror:2 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %1, %4, %6 row_ror:2 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %2, %4, %7 row_ror:3 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %3, %4, %8 row_ror:3 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %0, %4, %9 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %1, %4, %10 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %2, %4, %11 row_ror:5 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %3, %4, %12 row_ror:5 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %0, %4, %13 row_ror:6 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %1, %4, %14 row_ror:6 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %2, %4, %15 row_ror:7 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %3, %4, %16 row_ror:7 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %0, %4, %17 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %1, %4, %18 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %2, %4, %19 row_ror:9 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %3, %4, %20 row_ror:9 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %0, %4, %21 row_ror:10 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %1, %4, %22 row_ror:10 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %2, %4, %23 row_ror:11 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %3, %4, %24 row_ror:11 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %0, %4, %25 row_ror:12 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %1, %4, %26 row_ror:12 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %2, %4, %27 row_ror:13 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %3, %4, %28 row_ror:13 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %0, %4, %29 row_ror:14 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %1, %4, %30 row_ror:14 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %2, %4, %31 row_ror:15 row_mask:0xf bank_mask:0xf\n\t"
-          "v_fmac_f32_dpp %3, %4, %32 row_ror:15 row_mask:0xf bank_mask:0xf"
-          : "+v"(P), "+v"(Q), "+v"(P2), "+v"(Q2)
-          : "v"(h1), "v"(wP[2]), "v"(wQ[2]), "v"(wP[3]), "v"(wQ[3]), "v"(wP[4]), "v"(wQ[4]), "v"(wP[5]), "v"(wQ[5]), "v"(wP[6]), "v"(wQ[6]), "v"(wP[7]), "v"(wQ[7]), "v"(wP[8]), "v"(wQ[8]), "v"(wP[9]), "v"(wQ[9]), "v"(wP[10]), "v"(wQ[10]), "v"(wP[11]), "v"(wQ[11]), "v"(wP[12]), "v"(wQ[12]), "v"(wP[13]), "v"(wQ[13]), "v"(wP[14]), "v"(wQ[14]), "v"(wP[15]), "v"(wQ[15]));
-      P = P + P2;
-      Q = Q + Q2;
-      swap_rows(P, Q);                    // row 0: (P0, P1) -> out c;  row 1: (Q0, Q1) -> out 16+c
-      const float h2 = tanh_prescaled(P + Q);
+      const float h2 = tanh_prescaled(mul32(bP, bQ, h1, wP, wQ));   // layer 2
       // layer 3 (times dt): reduce-scatter of the four outputs over each quad, then the
       // quads of the row and the two rows
       const float A = __builtin_fmaf(wKA, h2, bKA) + dpp_f<kQuadXor1>(wSA * h2);   // output oA, lanes L, L^1
@@ -320,8 +270,6 @@ __global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kern
       xd = xd + (double)y;
       sX[slot * T4 * kXW + (t + 1) * kXW + comp] = (float)xd;
     }
-    u = u_next;
-    e = e_next;
     vc = vc_next;
   }
   }

@@ -9,7 +9,6 @@ namespace mppi {
 
 constexpr int kWaveBlock = 256;
 constexpr int kWaveSlots = 8;        // samples per block
-constexpr int kWaveNT = kTMax / 32;  // chunks of 32 steps
 
 __device__ __forceinline__ float as_f(uint32_t v) { return __builtin_bit_cast(float, v); }
 __device__ __forceinline__ uint32_t as_u(float v) { return __builtin_bit_cast(uint32_t, v); }
@@ -133,6 +132,13 @@ __device__ __forceinline__ bool all32(bool p) {
   return half == 0xFFFFFFFFu;
 }
 
+// LDS that only one wave writes and reads: the order of its accesses for the compiler.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Layer 1 of the chain: b + W1 (x_d, g(v)) for the lane's hidden unit, x the lane's component
 // of x_d.  One block, the controls' two products first: x is its input, so they stand between
 // the instruction that wrote x and the first DPP read of it, which needs two wait states.
@@ -151,6 +157,57 @@ __device__ __forceinline__ float chain_layer1(float x, float2 v, float b, const 
       : "=&v"(acc)
       : "v"(x), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]), "v"(v.x), "v"(v.y), "v"(b));
   return acc;
+}
+
+// One row's part of a 32 x 32 product: P += sum_s wP[s] h[ror s], Q likewise (the row's
+// 16 values of h through row_ror), then the sums of the sample's two rows: lane (r, c)
+// returns output 16 r + c.  Four interleaved accumulators, so that none is read by the
+// instruction right after the one that wrote it, and rotations 2..15 in one block (no wait
+// states inserted between them): the DPP source h was written before the four instructions
+// forming P, Q, P2 and Q2, the block's inputs, more than the two wait states a DPP read needs.
+__device__ __forceinline__ float mul32(float P, float Q, float h, const float (&wP)[16], const float (&wQ)[16]) {
+  P = __builtin_fmaf(wP[0], h, P);
+  Q = __builtin_fmaf(wQ[0], h, Q);
+  float P2 = wP[1] * dpp_f<kRowRor + 1>(h);
+  float Q2 = wQ[1] * dpp_f<kRowRor + 1>(h);
+  asm volatile(
+      "v_fmac_f32_dpp %0, %4, %5 row_ror:2 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %6 row_ror:2 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %7 row_ror:3 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %8 row_ror:3 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %9 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %10 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %11 row_ror:5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %12 row_ror:5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %13 row_ror:6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %14 row_ror:6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %15 row_ror:7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %16 row_ror:7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %17 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %18 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %19 row_ror:9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %20 row_ror:9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %21 row_ror:10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %22 row_ror:10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %23 row_ror:11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %24 row_ror:11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %25 row_ror:12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %26 row_ror:12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %27 row_ror:13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %28 row_ror:13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %29 row_ror:14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %30 row_ror:14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %31 row_ror:15 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %32 row_ror:15 row_mask:0xf bank_mask:0xf"
+      : "+v"(P), "+v"(Q), "+v"(P2), "+v"(Q2)
+      : "v"(h), "v"(wP[2]), "v"(wQ[2]), "v"(wP[3]), "v"(wQ[3]), "v"(wP[4]), "v"(wQ[4]), "v"(wP[5]), "v"(wQ[5]),
+        "v"(wP[6]), "v"(wQ[6]), "v"(wP[7]), "v"(wQ[7]), "v"(wP[8]), "v"(wQ[8]), "v"(wP[9]), "v"(wQ[9]),
+        "v"(wP[10]), "v"(wQ[10]), "v"(wP[11]), "v"(wQ[11]), "v"(wP[12]), "v"(wQ[12]), "v"(wP[13]), "v"(wQ[13]),
+        "v"(wP[14]), "v"(wQ[14]), "v"(wP[15]), "v"(wQ[15]));
+  P = P + P2;
+  Q = Q + Q2;
+  swap_rows(P, Q);
+  return P + Q;
 }
 
 // The network constants of the chain (the 6-32-32-4 network on 32 lanes per sample, see the
