@@ -87,8 +87,9 @@ __device__ __forceinline__ float noise_ln(uint32_t w) {
     e += 1;
   }
   // s = (f - 1) / (f + 1), rounded as the division rounds it: a Newton step on the
-  // reciprocal and one residual correction of the quotient (no scaling: the operands are
-  // of order one; equal for all 2^23 words)
+  // reciprocal and one residual correction of the quotient (Markstein, IBM J. Res. Dev. 34,
+  // 1990; no scaling: the operands are of order one).  The test that draws every word
+  // compares it with the division.
   const float num = f - 1.0f, den = f + 1.0f;
   float y = __builtin_amdgcn_rcpf(den);
   y = __builtin_fmaf(__builtin_fmaf(-den, y, 1.0f), y, y);
@@ -106,7 +107,7 @@ __device__ __forceinline__ float noise_ln(uint32_t w) {
 
 // sqrt of x = -2 ln u, rounded as sqrtf rounds it: x is between 2^-23 and 34, so the reciprocal
 // square root needs no scaling; one coupled Newton step and one residual correction
-// (equal for all 2^23 words).
+// (Markstein, as above), compared with sqrtf by the same test.
 __device__ __forceinline__ float noise_sqrt(float x) {
   const float y = __builtin_amdgcn_rsqf(x);
   float g = x * y;
