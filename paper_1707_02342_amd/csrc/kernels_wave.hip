@@ -46,8 +46,11 @@ namespace mppi {
 // here (137 and 210 registers), which costs more than the few registers that then spill:
 // K = 6001, T = 150 124 -> 110 us (114 with error-free FP32 sums), K = 8192, T = 100 85 -> 82.
 // With the weights staged through LDS (ChainStage) 105 and 78, K = 4096, T = 100 55 -> 51.5.
+// (That is the network; for the basis-function model: up to 128 steps K = 8192, T = 64 53.7 us
+// without and 44.0 with, the error-free sums took 45.8; beyond, where 34 registers would
+// spill, 254 with and 250 without at K = 8192, T = 256 and 134 and 130 at K = 9000, T = 150.)
 template <int HID, int NQ, int MODEL>
-__global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kernel(RolloutArgs a) {
+__global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : MODEL == kModelNet ? 3 : 1) void rollout_wave_kernel(RolloutArgs a) {
   static_assert(HID == 32, "the wave schedule maps 32 hidden units onto 32 lanes");
   extern __shared__ float smem[];
   // Up to 128 steps (NQ = 4) the chain stores the uncompensated state hi_t and each
@@ -86,12 +89,14 @@ __global__ __launch_bounds__(kWaveBlock, NQ <= 4 ? 4 : 3) void rollout_wave_kern
 
   // ---- the launch's inputs: every load is issued at once, the ones that the draws and the
   // controls need first.  (Absent inputs are read from the parameters' addresses, so that no
-  // load is in a branch.)
+  // load is in a branch.  The basis-function model has no weights to wait for with it and reads
+  // the counter as a scalar: K = 8500-10500, T <= 20, where a fifth block per compute unit
+  // starts late, 31.8 -> 29.1 us at K = 9000, T = 10.)
   constexpr bool kNet = MODEL == kModelNet;
   constexpr int kURegs = (64 * NQ + kWaveBlock - 1) / kWaveBlock;   // 2T <= 64 NQ
   const int tid = threadIdx.x;
   const uint32_t* iter_p = a.iter_dev ? a.iter_dev : reinterpret_cast<const uint32_t*>(a.params);
-  const uint32_t iter_in = __hip_atomic_load(iter_p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint32_t iter_in = kNet ? __hip_atomic_load(iter_p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *iter_p;
   float u_in[kURegs];
 #pragma unroll
   for (int i = 0; i < kURegs; ++i) u_in[i] = a.U[min(tid + i * kWaveBlock, 2 * T - 1)];
