@@ -254,10 +254,11 @@ def measure_precision(M, stream, iters: int = 30):
     cmap = synth.ring_map()
     flop = NET_FLOP_PER_STEP[64]
     # rooflines: FP32 on the matrix cores against the FP32 matrix peak; BF16/FP16 are
-    # bound by the vector ALU (tanh: exp and rcp at quarter rate + 3 FMA = 11 slots, 128
-    # per step at h = 64, plus ~150 other slots) -- reported against that bound and,
-    # for reference, as a fraction of the BF16/FP16 matrix peak
-    valu_steps_peak = VALU_LANE_SLOTS_PER_S / (128 * 11 + 150)
+    # bound by the vector ALU (tanh: exp and rcp of two slots each, an add and an fma = 6
+    # slots, 24 cycles of a wave as measured alone; 128 per step at h = 64, plus ~150 other
+    # slots) -- reported against that bound and, for reference, as a fraction of the
+    # BF16/FP16 matrix peak
+    valu_steps_peak = VALU_LANE_SLOTS_PER_S / (128 * 6 + 150)
 
     def precision_at(K):
         prob = synth.c3_problem(K=K, seed=0)

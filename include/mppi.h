@@ -170,8 +170,9 @@ mppi_status mppi_set_dynamics(mppi_ctx* ctx, const int32_t dims[4], const float*
 mppi_status mppi_set_basis_dynamics(mppi_ctx* ctx, const float* theta);
 
 /* The cost map h at n world positions xy ([n][2] (p_x, p_y), host) into h_out ([n],
- * host), with the rollout kernels' bilinear interpolation (for closed-loop evaluation:
- * where an executed trajectory left the track).  Synchronises.  INVAL: NULL pointers,
+ * host), with the cost's bilinear interpolation, grid coordinates in FP32 as the LANE and
+ * WIDE schedules form them (WAVE and QUAD form them in 64 bits: a value can differ by
+ * rounding).  For closed-loop evaluation: where an executed trajectory left the track.  Synchronises.  INVAL: NULL pointers,
  * n outside [0, 1<<24] or a non-finite position.  STATE: no cost map set. */
 mppi_status mppi_costmap_values(mppi_ctx* ctx, const float* xy, int32_t n, float* h_out);
 

@@ -63,9 +63,12 @@ namespace {
 thread_local std::string g_create_error;
 
 constexpr int32_t kMaxK = 1 << 22;
-// Automatic schedule: 32 lanes per sample while that still fits the chip in a few
-// waves per SIMD (latency-bound regime), one lane per sample beyond.
-constexpr int32_t kWaveAutoMaxK = 12288;   // AUTO: WAVE up to here, QUAD above
+// Automatic schedule: 32 lanes per sample while that still fits the chip in a few waves per
+// SIMD (latency-bound regime), beyond it the matrix cores (network) or one lane per sample.
+// The line was drawn where WAVE and QUAD met at T = 100.  Both have become faster since,
+// QUAD more (93 us up to K = 16384; WAVE 78 at K = 8192, 92 at 9000, 110 at 12288), and meet
+// near K = 9000 now.
+constexpr int32_t kWaveAutoMaxK = 12288;   // AUTO: WAVE up to here, QUAD or LANE above
 constexpr int kNumBasisHost = 25;          // basis functions of the basis-function model
 
 // Pinned host memory of a context, for results on their way to the host: at most
