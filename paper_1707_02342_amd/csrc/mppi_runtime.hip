@@ -187,12 +187,13 @@ bool pinned_reserve(Pinned& p, size_t words) {
   return true;
 }
 
-hipError_t launch_copy(const CopyArgs& a, hipStream_t stream) {
+// The launch's own result: the thread's last error may be another call's.
+hipError_t launch_copy(CopyArgs a, hipStream_t stream) {
   unsigned most = 0;
   for (unsigned w : a.words) most = std::max(most, w);
   const unsigned blocks = std::min(256u, std::max(1u, (most + 1023) / 1024));
-  hipLaunchKernelGGL(copy_words_kernel, dim3(blocks), dim3(256), 0, stream, a);
-  return hipGetLastError();
+  void* args[] = {&a};
+  return hipLaunchKernel(reinterpret_cast<const void*>(&copy_words_kernel), dim3(blocks), dim3(256), args, 0, stream);
 }
 
 #define HIP_TRY(ctx, expr)                                                                   \
