@@ -401,8 +401,9 @@ def measure_forms(M, stream, iters: int = 30, laps_per_setting: int = 3):
             M.mppi_set_timing(c.ctx, False)
         st = prob.K * prob.T / (ms * 1e-3)
         launch_ms = float(np.mean(launch))
+        kernel_ms = float(np.sum(launch)) / 100        # per step: a launch may run many
         flop = BASIS_FLOP_PER_STEP if prob.model == 1 else NET_FLOP_PER_STEP[32]
-        tf = flop * prob.K * prob.T / (launch_ms * 1e-3) / 1e12
+        tf = flop * prob.K * prob.T / (kernel_ms * 1e-3) / 1e12
         out[name] = {"ms_per_step": ms, "steps_per_s": st, "schedule": sched,
                      "launch_us": {"mean": launch_ms * 1e3, "p50": float(np.percentile(launch, 50)) * 1e3,
                                    "p99": float(np.percentile(launch, 99)) * 1e3},
