@@ -76,17 +76,66 @@ constexpr int kNumBasisHost = 25;          // basis functions of the basis-funct
 // directly to the caller's memory), grown when a fetch needs more.  U and the status took two
 // copy commands to the caller's memory, 39 us with the synchronisation behind a short kernel;
 // one launch that writes them here and a plain copy take 20 (64 KB: 49 and 22; 256 KB: 57 and
-// 30).  Allocating and freeing it takes 40-50 us, so a context gets it with its
-// kPinnedAtFetch-th fetch, when the copies have cost about as much: a context that is read
-// once or twice, or only by device pointers, pays nothing.
+// 30).  Allocating and freeing it takes 40-50 us, as much as two or three such reads gain, so
+// a context's first read takes memory that a destroyed context left (PinnedPool), and
+// without any a context allocates with its kPinnedAtFetch-th read: one that is read once or
+// twice, or only by device pointers, never pays for it.
 constexpr size_t kPinnedMaxWords = (size_t)1 << 18;
 constexpr int kPinnedAtFetch = 3;
 struct Pinned {
   uint32_t* host = nullptr;
   uint32_t* dev = nullptr;
   size_t words = 0;
-  int fetches = 0;           // so far, up to kPinnedAtFetch
 };
+
+// Pinned memory of destroyed contexts, for the next ones on the same device: at most kSpares
+// blocks, freed with the last context.  A block comes here only behind a synchronisation of
+// its context's stream, so nothing writes to it any more.
+struct PinnedPool {
+  static constexpr int kSpares = 8;
+  std::mutex m;
+  int contexts = 0;          // alive
+  int n = 0;
+  Pinned spare[kSpares];
+  int device[kSpares] = {};
+
+  void opened() {
+    std::lock_guard<std::mutex> lock(m);
+    ++contexts;
+  }
+  // The smallest spare block of at least `words` words, or an empty one.
+  Pinned take(int dev, size_t words) {
+    std::lock_guard<std::mutex> lock(m);
+    int best = -1;
+    for (int i = 0; i < n; ++i)
+      if (device[i] == dev && spare[i].words >= words && (best < 0 || spare[i].words < spare[best].words)) best = i;
+    if (best < 0) return {};
+    const Pinned p = spare[best];
+    spare[best] = spare[--n];
+    device[best] = device[n];
+    return p;
+  }
+  // Keeps p, or returns false where there is no room.
+  bool give(int dev, const Pinned& p) {
+    std::lock_guard<std::mutex> lock(m);
+    if (n == kSpares) return false;
+    spare[n] = p;
+    device[n++] = dev;
+    return true;
+  }
+  void closed() {
+    Pinned last[kSpares];
+    int k = 0;
+    {
+      std::lock_guard<std::mutex> lock(m);
+      if (--contexts == 0)
+        for (; n > 0; --n) last[k++] = spare[n - 1];
+    }
+    while (k > 0) (void)hipHostFree(last[--k].host);
+  }
+};
+
+PinnedPool g_pinned;
 
 struct PendingTiming {
   hipEvent_t e0, e1;
@@ -140,6 +189,7 @@ struct mppi_ctx {
   int schedule = MPPI_SCHED_LANE;
   float sig[2] = {0, 0};
   Pinned pin;
+  int fetches = 0;           // so far, up to kPinnedAtFetch
   std::string err;
   bool timing = false;
   std::vector<PendingTiming> pending;
@@ -161,30 +211,44 @@ mppi_status fail(mppi_ctx* c, mppi_status st, const char* fmt, ...) {
   return st;
 }
 
-// Room for `words` words of results.  No launch that uses the memory may be in flight.
-bool pinned_reserve(Pinned& p, size_t words) {
-  if (p.host && words <= p.words) return true;
-  if (words > kPinnedMaxWords) return false;
+// New pinned memory of at least `words` words, or an empty block.
+Pinned pinned_alloc(size_t words) {
+  Pinned p;
   const size_t n = (words + 4095) / 4096 * 4096;
   void *h = nullptr, *d = nullptr;
   // another thread's stream may be under capture, which an allocation must not end
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-  if (p.host) (void)hipHostFree(p.host);
-  p.host = p.dev = nullptr;
-  p.words = 0;
   hipError_t e = hipHostMalloc(&h, n * 4, hipHostMallocMapped | hipHostMallocCoherent);
   if (e == hipSuccess) e = hipHostGetDevicePointer(&d, h, 0);
-  if (e != hipSuccess) {
+  if (e == hipSuccess) {
+    p.host = static_cast<uint32_t*>(h);
+    p.dev = static_cast<uint32_t*>(d);
+    p.words = n;
+  } else {
     (void)hipGetLastError();
     if (h) (void)hipHostFree(h);
   }
   if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
-  if (e != hipSuccess) return false;
-  p.host = static_cast<uint32_t*>(h);
-  p.dev = static_cast<uint32_t*>(d);
-  p.words = n;
-  return true;
+  return p;
+}
+
+// Puts the context's pinned memory back.  Its stream has been synchronised.
+void pinned_release(mppi_ctx* c) {
+  if (c->pin.host && !g_pinned.give(c->device, c->pin)) (void)hipHostFree(c->pin.host);
+  c->pin = Pinned{};
+}
+
+// Before a fetch of `words` words that the context's pinned memory does not hold: sees to it,
+// where the rule above allows.  If it holds any, the stream has been synchronised.
+void pinned_reserve(mppi_ctx* c, size_t words) {
+  // room for the costs or the controls and more, so that it seldom grows
+  const size_t want = std::max(words, std::min(kPinnedMaxWords, (size_t)c->cfg.K + 2 * (size_t)c->cfg.T + 2048));
+  Pinned p = g_pinned.take(c->device, want);
+  if (!p.host && c->fetches == kPinnedAtFetch) p = pinned_alloc(want);
+  if (!p.host) return;
+  pinned_release(c);
+  c->pin = p;
 }
 
 // The launch's own result: the thread's last error may be another call's.
@@ -683,11 +747,10 @@ struct Range {
 mppi_status fetch(mppi_ctx* c, std::initializer_list<Range> ranges) {
   size_t total = 0;
   for (const Range& r : ranges) total += r.words;
-  c->pin.fetches = std::min(c->pin.fetches + 1, kPinnedAtFetch);
-  if (total > c->pin.words && total <= kPinnedMaxWords && c->pin.fetches == kPinnedAtFetch) {
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    // at first room for the costs or the controls and more, so that it seldom grows
-    pinned_reserve(c->pin, std::max(total, std::min(kPinnedMaxWords, (size_t)c->cfg.K + 2 * (size_t)c->cfg.T + 2048)));
+  c->fetches = std::min(c->fetches + 1, kPinnedAtFetch);
+  if (total > c->pin.words && total <= kPinnedMaxWords) {
+    if (c->pin.host) HIP_TRY(c, hipStreamSynchronize(c->stream));
+    pinned_reserve(c, total);
   }
   if (total <= c->pin.words) {
     CopyArgs a{};
@@ -811,8 +874,6 @@ void free_all(mppi_ctx* c) {
   c->pending.clear();
   for (auto e : c->event_pool) (void)hipEventDestroy(e);
   c->event_pool.clear();
-  if (c->pin.host) (void)hipHostFree(c->pin.host);
-  c->pin = Pinned{};
 }
 
 }  // namespace
@@ -895,6 +956,7 @@ mppi_status mppi_create(const mppi_config* cfg, const mppi_cost* cost, int devic
     delete c;
     return st;
   }
+  g_pinned.opened();
   *out = c;
   return MPPI_OK;
 }
@@ -902,9 +964,11 @@ mppi_status mppi_create(const mppi_config* cfg, const mppi_cost* cost, int devic
 void mppi_destroy(mppi_ctx* ctx) {
   if (!ctx) return;
   (void)hipSetDevice(ctx->device);
-  (void)hipStreamSynchronize(ctx->stream);
+  if (hipStreamSynchronize(ctx->stream) == hipSuccess) pinned_release(ctx);
+  else if (ctx->pin.host) (void)hipHostFree(ctx->pin.host);
   free_all(ctx);
   delete ctx;
+  g_pinned.closed();
 }
 
 mppi_status mppi_set_costmap(mppi_ctx* c, const float* map, int32_t H, int32_t W, float origin_x,

@@ -1,7 +1,9 @@
 """Reading a context back before, while and after it gets its pinned memory (with its third
-read), when that memory has to grow, and beyond what it may hold: the same values as a
-second context that is read once, or as the histories a device-side run leaves in device
-memory, bit for bit."""
+read, or with the first from what a destroyed context left), when that memory has to grow,
+and beyond what it may hold: the same values as a second context that is read once, or as
+the histories a device-side run leaves in device memory, bit for bit."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -63,3 +65,49 @@ def test_histories_grow_the_memory(M, n, reads):
         V = synth.random_controls(8, 9, scale=0.2)
         c.set_controls(V)
         assert np.array_equal(c.controls(), V)
+
+
+@pytest.mark.parametrize("threads", [1, 4])
+def test_memory_passes_between_contexts(M, threads):
+    """Contexts of several sizes and streams that come and go, in one thread and in several at
+    once, more at a time than the pool keeps blocks for."""
+    import torch
+    shapes = [(256, 30), (9000, 3), (1, 1), (60000, 2), (70, 200)]
+    probs = [synth.with_(synth.c1_problem(seed=i), K=K, T=T) for i, (K, T) in enumerate(shapes)]
+    cmap, params = synth.ring_map(), synth.mlp_params(32, 0)
+
+    def read(c):
+        S, _ = c.iterate(synth.C1_X0, want_costs=True)
+        return S, c.controls(), c.stats()[2]
+
+    want = []
+    for prob in probs:
+        with M.Controller(prob, cmap, params) as c:
+            want.append(read(c))
+    bad = []
+
+    def work(seed):
+        rng = np.random.default_rng(seed)
+        stream = torch.cuda.Stream()
+        held = []
+        try:
+            for i in range(60):
+                j = int(rng.integers(len(probs)))
+                c = M.Controller(probs[j], cmap, params, stream=int(stream.cuda_stream))
+                held.append(c)
+                got = read(c)
+                if not all(np.array_equal(a, b) for a, b in zip(got, want[j])):
+                    bad.append((seed, i, shapes[j]))
+                while len(held) > int(rng.integers(12)):
+                    held.pop(int(rng.integers(len(held)))).close()
+        except Exception as e:
+            bad.append((seed, repr(e)))
+        for c in held:
+            c.close()
+
+    ts = [threading.Thread(target=work, args=(s,)) for s in range(threads)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not bad
