@@ -347,11 +347,11 @@ struct QuadNet {
 // the chain is done once per sample and step, in the lane that draws the step's noise (the
 // clamped control and the control cost) or that evaluates its cost; the heading is checked
 // for non-finite values once per chunk and x_d at the end: what is not finite there stays
-// so or makes the position so, since every step adds to it.  242 -> ~170 vector instructions per wave-step beside the matrix
-// products (a third of that from the 64-bit sums); with tanh4 above, before -> after: batched
-// form (512 instances, 1.01e8 steps) 4.69 -> 4.07 ms; T = 100, h = 64: FP32 K = 65536 759 -> 678
+// so, since every step adds to it.  242 -> ~170 vector instructions per wave-step beside the
+// matrix products (a third of that from the 64-bit sums); with tanh4 above, before -> after:
+// batched form (512 instances, 1.01e8 steps) 4.69 -> 4.07 ms; T = 100, h = 64: FP32 K = 65536 759 -> 678
 // us, BF16 332 -> 264 us, FP16 365 -> 296 us, K = 16384 (one wave per SIMD) FP32 226 -> 188, BF16
-// 124 -> 91, FP16 129 -> 99 us; h = 32, FP32, K = 16384 131 -> 91 us.
+// 124 -> 91, FP16 129 -> 99 us; h = 32, FP32, K = 16384 131 -> 93 us.
 template <int PREC, int HID, bool RECEDE = true>
 __device__ void quad_rollout_tile(const RolloutArgs& a, int tile, float* sU, float* sX, float* red) {
   const int T = __builtin_amdgcn_readfirstlane(a.T);
